@@ -202,26 +202,30 @@ po_status po_tree_bind_codebook(const po_tree_desc* desc, int64_t n_nodes, const
                                 po_tree** out);
 /* po_tree_build_index: builds the handle's traversal index, a derived copy
  * of the child array that the renders, gradients and the filter walk
- * instead of the caller's array.  The nodes above level M = D - 3 keep
- * their child entries; each internal node of level M becomes a brick of
- * 8 x 8 x 8 entries, one per finest cell of its cube, naming the leaf (or
- * empty space) that holds the cell and that leaf's level.  A walk step
- * inside one brick then needs one dependent read instead of one per level
- * below the common ancestor; the segments, samples and results are those of
- * the plain octree walk (Sec. 4.2, "Rendering": the exact voxel crossings).
+ * instead of the caller's array.  Each internal node of level M = D - 3
+ * becomes a brick of 8 x 8 x 8 entries, one per finest cell of its cube, naming
+ * the leaf (or empty space) that holds the cell and that leaf's level; a grid
+ * of 8^G entries, G = min(M, 8), names the brick, leaf or empty space of each
+ * level-G cell (deeper trees keep the nodes between).  A walk step then needs
+ * one dependent read inside a brick and two elsewhere.  Empty entries name a
+ * box of empty space around their cell, which a walk crosses in one step; the
+ * segments, samples and results are those of the plain octree walk (Sec. 4.2,
+ * "Rendering": the exact voxel crossings), which renders that report or cap
+ * their steps (PO_OUT_AUX, max_steps) still take cell by cell.
  * Reads the child array back to the host on `stream` (waiting for the
  * stream), checks it as po_tree_validate does, and allocates the index on
- * the current device (n_top * 32 + n_bricks * 2048 bytes, a few percent of
- * the leaf records); the handle owns it until po_tree_destroy.  Trees of
- * depth < 4 need none (PO_OK, nothing built); a second call is a no-op.  Must
- * not run while work that uses the handle is queued or running.  Errors:
- * PO_ERR_INVALID (NULL), PO_ERR_TREE (malformed child array: the handle is
- * unchanged and renders walk the caller's array, counting malformed entries
- * as device errors), PO_ERR_UNSUPPORTED (2^29 - 2 leaves or more, or an
- * index of 4 GiB or more), PO_ERR_OOM, PO_ERR_DEVICE. */
-po_status po_tree_build_index(po_tree* t, void* stream);
-/* po_tree_index_host: host only.  The traversal index po_tree_build_index
- * builds, from a host copy of a child array of depth D >= 4: writes *n_top
+ * the current device (8^G * 4 + n_bricks * 2048 bytes, and n_top * 32 where
+ * G < M, a few percent of the leaf records); the handle owns it until
+ * po_tree_destroy.  Trees of depth < 4 need none (PO_OK, nothing built); a
+ * second call is a no-op.  Must not run while work that uses the handle is
+ * queued or running.  Errors: PO_ERR_INVALID (NULL), PO_ERR_TREE (malformed
+ * child array: the handle is unchanged and renders walk the caller's array,
+ * counting malformed entries as device errors), PO_ERR_UNSUPPORTED (2^29 - 2
+ * leaves or more, or nodes and bricks of 4 GiB or more), PO_ERR_OOM,
+ * PO_ERR_DEVICE. */
+/* po_tree_index_host: host only.  The nodes and bricks that
+ * po_tree_build_index starts from (before it adds the grid and the empty
+ * boxes), from a host copy of a child array of depth D >= 4: writes *n_top
  * (nodes above level D - 3) and *n_bricks, and, when h_index is not NULL,
  * h_index[n_top * 8 + n_bricks * 512]: the renumbered nodes' child entries
  * (an entry >= n_top names brick entry - n_top), then the bricks, entry
@@ -253,8 +257,8 @@ po_status po_render_rays(const po_tree* t, int64_t n, const float* d_origins, co
 /* po_render_camera: renders a camera image into d_rgb[height][width][3]
  * (and d_aux[height][width][4] with PO_OUT_AUX).  width, height in
  * [1, 16384]; fx, fy non-zero.
- * Images of at least 65536 pixels are rendered in pieces: every ray is walked for a bounded number of cells, the rays with
- * cells left are cut into parameter intervals walked in parallel, and the
+ * Images of at least 65536 pixels are rendered in pieces: every ray is walked
+ * for a bounded number of data samples, the rays with cells left are cut into parameter intervals walked in parallel, and the
  * pieces are composited front to back (compositing is associative, Sec. 3
  * eqn:quad), the piece holding the early stop walked again with the known
  * transmittance.  The colour equals the one-pass render (po_render_batch)

@@ -123,11 +123,7 @@ void po_split_layout(void* base, int region_slots, KSplit* S) {
     S->part2 = p + n * 48;
     S->view_part2 = reinterpret_cast<int4*>(p + n * 80);
     S->region_slots = region_slots;
-    S->split_steps = PO_SPLIT_STEPS;
-    S->chunk_steps = PO_CHUNK_STEPS;
-    S->sub_steps = PO_SUB_STEPS;
-    S->chunk_cap = PO_CHUNK_CAP;
-    S->ub_frac = PO_SPLIT_UB_FRAC;
+    po_frame_piece_sizes(0, false, S);
     S->ray_o = nullptr;
     S->ray_d = nullptr;
     S->n_rays = 0;
@@ -184,7 +180,7 @@ KOpts kopts(const po_tree* t, const po_render_opts* o) {
     for (int i = 0; i < 3; ++i) k.bg[i] = o->bg[i];
     k.stop_T = o->stop_T;
     k.max_steps = o->max_steps ? o->max_steps : 3 * (1 << t->desc.depth) + 8;
-    k.flags = o->flags;
+    k.flags = o->flags | ((o->flags & PO_OUT_AUX) || o->max_steps ? kOptExact : 0u);
     k.sh_off = o->sh_off;
     for (int i = 0; i < 4; ++i) k.clip[i] = o->clip[i];
     return k;
@@ -527,11 +523,12 @@ static po_status bind_impl(const po_tree_desc* desc, int64_t n_nodes, const int3
         k.lobes = d_lobes;
     k.cb_entries = cb ? cb_entries : 0;
     k.n_top = (int32_t)n_nodes;
-    k.brick_level = (int16_t)desc->depth;  // no bricks until po_tree_build_index
+    k.brick_level = (int8_t)desc->depth;  // no bricks and no grid until po_tree_build_index
+    k.grid_level = 0;
     k.index_bytes = (uint32_t)(n_nodes * 32);
     k.n_leaves = (int32_t)n_leaves;
     k.stride = t->stride;
-    k.depth = (int16_t)desc->depth;
+    k.depth = (int8_t)desc->depth;
     k.sigma_bytes = (uint32_t)(n_leaves * es);
     k.sh_bytes = (uint32_t)(n_leaves * (int64_t)t->stride * es);
     for (int a = 0; a < 3; ++a) k.lo[a] = (double)desc->center[a] - (double)desc->half_size;
@@ -637,6 +634,30 @@ static po_status index_of(const po_tree_desc* desc, bool codebook, int64_t n, co
     return ok();
 }
 
+// The nodes of an index (index_of) as the grid is made from them: entries of
+// leaves of level <= G replaced by -(number) - 1 of their place in `coarse`,
+// which gets {leaf, level} of each, last first (the device table is read
+// backwards from its end).
+static std::vector<int32_t> grid_nodes(const std::vector<int32_t>& index, int64_t n_top, int G,
+                                       std::vector<int32_t>& coarse) {
+    std::vector<int32_t> nodes(index.begin(), index.begin() + (ptrdiff_t)(n_top * 8));
+    std::vector<int8_t> lvl((size_t)n_top, 0);  // parents come before their children
+    for (int64_t v = 0; v < n_top; ++v)
+        for (int c = 0; c < 8; ++c) {
+            int32_t& e = nodes[(size_t)v * 8 + c];
+            if (e > 0 && e < n_top) {
+                lvl[e] = (int8_t)(lvl[v] + 1);
+            } else if (e < 0 && lvl[v] < G) {
+                const int32_t leaf = -(e + 1);
+                e = -(int32_t)(coarse.size() / 2) - 1;
+                coarse.push_back(lvl[v] + 1);
+                coarse.push_back(leaf);
+            }
+        }
+    std::reverse(coarse.begin(), coarse.end());
+    return nodes;
+}
+
 po_status po_tree_index_host(const po_tree_desc* desc, int64_t n_nodes, const int32_t* h_child, int64_t n_leaves,
                              int64_t* n_top, int64_t* n_bricks, int32_t* h_index) {
     if (po_status s = check_desc(desc)) return s;
@@ -660,7 +681,7 @@ po_status po_tree_build_index(po_tree* t, void* stream) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return device_fail(e, "traversal index: current device");
-    std::vector<int32_t> h, index;
+    std::vector<int32_t> h, index, coarse;
     int64_t n_top = 0, n_bricks = 0;
     try {
         h.resize((size_t)n * 8);
@@ -671,14 +692,47 @@ po_status po_tree_build_index(po_tree* t, void* stream) {
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return device_fail(e, "traversal index: reading the child array");
     if (po_status st = index_of(&t->desc, t->codebook, n, h.data(), t->n_leaves, index, n_top, n_bricks)) return st;
-    const size_t bytes = index.size() * sizeof(int32_t);
-    void* d = nullptr;
-    if ((e = hipMalloc(&d, bytes)) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(PO_ERR_OOM, "traversal index: %zu bytes of device memory", bytes);
+    // The grid reaches the bricks for D <= 11; deeper trees keep the nodes
+    // below it.  An index that the grid would take past 4 GiB does without.
+    const int M = D - 3;
+    int G = std::min(M, kIdxMaxGrid);
+    const size_t node_bytes = (size_t)n_top * 32, brick_bytes = (size_t)n_bricks * 2048;
+    size_t grid_bytes = (size_t)4 << (3 * G), kept_nodes = G < M ? node_bytes : 0;
+    std::vector<int32_t> nodes;
+    try {
+        nodes = grid_nodes(index, n_top, G, coarse);
+    } catch (const std::bad_alloc&) {
+        return fail(PO_ERR_OOM, "traversal index: host allocation");
     }
-    e = hipMemcpyAsync(d, index.data(), bytes, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (grid_bytes + kept_nodes + brick_bytes + coarse.size() * 4 >= ((size_t)1 << 32) - 256) {
+        G = 0;
+        grid_bytes = 0;
+        kept_nodes = node_bytes;
+        coarse.clear();
+    }
+    const size_t bytes = grid_bytes + kept_nodes + brick_bytes + coarse.size() * 4;
+    char* d = nullptr;
+    char* tmp = nullptr;  // the grid's nodes, then scratch for its boxes
+    if ((e = hipMalloc(&d, bytes)) != hipSuccess || (G > 0 && (e = hipMalloc(&tmp, node_bytes + grid_bytes)) != hipSuccess)) {
+        (void)hipGetLastError();
+        if (d) (void)hipFree(d);
+        return fail(PO_ERR_OOM, "traversal index: %zu bytes of device memory", bytes + (G > 0 ? node_bytes + grid_bytes : 0));
+    }
+    auto put = [&](void* to, const void* from, size_t len) {
+        if (e == hipSuccess && len > 0) e = hipMemcpyAsync(to, from, len, hipMemcpyHostToDevice, s);
+    };
+    e = hipSuccess;
+    if (G > 0) put(tmp, nodes.data(), node_bytes);
+    put(d + grid_bytes, index.data(), kept_nodes);
+    put(d + grid_bytes + kept_nodes, index.data() + n_top * 8, brick_bytes);
+    put(d + grid_bytes + kept_nodes + brick_bytes, coarse.data(), coarse.size() * 4);
+    if (e == hipSuccess)
+        e = po_launch_index(reinterpret_cast<const int32_t*>(tmp), (int)n_top, G, n_bricks,
+                            reinterpret_cast<int32_t*>(d), reinterpret_cast<int32_t*>(d + grid_bytes + kept_nodes),
+                            reinterpret_cast<int32_t*>(tmp + node_bytes), s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    if (tmp) (void)hipFree(tmp);
     if (e != hipSuccess) {
         (void)hipFree(d);
         return device_fail(e, "traversal index: upload");
@@ -686,9 +740,10 @@ po_status po_tree_build_index(po_tree* t, void* stream) {
     t->d_index = d;
     t->index_device = dev;
     t->n_bricks = n_bricks;
-    t->kt.child = static_cast<const int32_t*>(d);
-    t->kt.n_top = (int32_t)n_top;
-    t->kt.brick_level = (int16_t)(D - 3);
+    t->kt.child = reinterpret_cast<const int32_t*>(d);
+    t->kt.n_top = G == M ? 0 : (int32_t)n_top;
+    t->kt.brick_level = (int8_t)M;
+    t->kt.grid_level = (int8_t)G;
     t->kt.index_bytes = (uint32_t)bytes;
     return ok();
 }
@@ -726,7 +781,7 @@ po_status po_render_rays(const po_tree* t, int64_t n, const float* d_origins, co
     const int variant = po_fwd_variant(k, aux, t->kt);
     KSplit S;
     hipError_t e;
-    if (!(k.flags & PO_ONE_PASS) && n >= kSplitMinRays && n < (1ll << 31) && k.max_steps > PO_SPLIT_STEPS &&
+    if (!(k.flags & PO_ONE_PASS) && n >= kSplitMinRays && n < (1ll << 31) && k.max_steps > kSplitMinMaxSteps &&
         split_queue(stream, &S))
         e = po_launch_rays_split(t, n, d_origins, d_dirs, k, d_rgb, variant == PO_FWD_VIEW ? aux : nullptr, S,
                                  (hipStream_t)stream);
@@ -766,13 +821,13 @@ static po_status render_camera_impl(const po_tree* t, const po_camera* cam, cons
     KSplit S;
     hipError_t e;
     const bool split = !(j.op.flags & PO_ONE_PASS) && (int64_t)cam->width * cam->height >= kSplitMinPixels &&
-                       j.op.max_steps > PO_SPLIT_STEPS;
+                       j.op.max_steps > kSplitMinMaxSteps;
     if (split && noalloc) {
         if ((e = po_noalloc_queue(&S)) != hipSuccess) return device_fail(e, "locating the fixed work queue");
-        S.split_steps = po_camera_split_steps(4 * (int64_t)tiles_of(cam));
+        po_frame_piece_sizes(4 * (int64_t)tiles_of(cam), (j.op.flags & kOptExact) != 0u, &S);
         e = po_launch_camera_split(t, j, 4 * tiles_of(cam), variant, S, (hipStream_t)stream);
     } else if (split && split_queue(stream, &S)) {
-        S.split_steps = po_camera_split_steps(4 * (int64_t)tiles_of(cam));
+        po_frame_piece_sizes(4 * (int64_t)tiles_of(cam), (j.op.flags & kOptExact) != 0u, &S);
         e = po_launch_camera_split(t, j, 4 * tiles_of(cam), variant, S, (hipStream_t)stream);
     } else {
         e = po_launch_camera_jobs(t, 1, &j, 4 * tiles_of(cam), variant, (hipStream_t)stream);
@@ -807,7 +862,7 @@ po_status po_render_rays_backward(const po_tree* t, int64_t n, const float* d_or
     const KOpts k = kopts(t, opts);
     KSplit S;
     hipError_t e;
-    if (!(k.flags & PO_ONE_PASS) && n >= kSplitMinBackward && n < (1ll << 31) && k.max_steps > PO_SPLIT_STEPS &&
+    if (!(k.flags & PO_ONE_PASS) && n >= kSplitMinBackward && n < (1ll << 31) && k.max_steps > kSplitMinMaxSteps &&
         split_queue(stream, &S))
         e = po_launch_backward_split(t, n, d_origins, d_dirs, k, d_rgb_fwd, d_grad_rgb, d_grad_sigma, d_grad_sh, S,
                                      (hipStream_t)stream);
@@ -833,7 +888,7 @@ po_status po_render_rays_keep(const po_tree* t, int64_t n, const float* d_origin
     if (hipError_t e = hipGetDevice(&dev)) return device_fail(e, "hipGetDevice");
     const KOpts k = kopts(t, opts);
     KSplit S;
-    bool split = !(k.flags & PO_ONE_PASS) && n >= kSplitMinRays && n < (1ll << 31) && k.max_steps > PO_SPLIT_STEPS &&
+    bool split = !(k.flags & PO_ONE_PASS) && n >= kSplitMinRays && n < (1ll << 31) && k.max_steps > kSplitMinMaxSteps &&
                  split_queue(stream, &S);
     hipError_t e;
     if (split) {
@@ -996,7 +1051,7 @@ po_status po_render_batch(int32_t n_jobs, const po_job* jobs, void* stream) {
         const KOpts k = kopts(J.tree, &J.opts);
         KSplit S;
         if ((k.flags & PO_ONE_PASS) || (int64_t)nt * PO_TILE * PO_TILE < kSplitMinPixels ||
-            k.max_steps <= PO_SPLIT_STEPS || !split_queue(stream, &S))
+            k.max_steps <= kSplitMinMaxSteps || !split_queue(stream, &S))
             continue;
         done[i] = true;
         KJob kj;
@@ -1009,7 +1064,7 @@ po_status po_render_batch(int32_t n_jobs, const po_job* jobs, void* stream) {
         kj.tile_begin = J.tile_begin;
         kj.block_begin = 0;
         kj.tiles_x = (J.cam.width + PO_TILE - 1) / PO_TILE;
-        S.split_steps = po_camera_split_steps(4 * (int64_t)nt);
+        po_frame_piece_sizes(4 * (int64_t)nt, (k.flags & kOptExact) != 0u, &S);
         hipError_t e = po_launch_camera_split(J.tree, kj, 4 * nt, variant(i) % 4, S, (hipStream_t)stream);
         if (e != hipSuccess) return device_fail(e, "render_batch launch");
     }

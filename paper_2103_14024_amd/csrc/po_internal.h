@@ -6,18 +6,33 @@
 #include <hip/hip_vector_types.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "plenoctree.h"
 
 // Kernel-side view of a bound tree (plain data, passed by value).
 struct KTree {
-    // Child entries the walk reads: the caller's child array [n_top][8], or
-    // the library's traversal index (po_tree_build_index): the nodes above
-    // brick_level, renumbered, [n_top][8], then one brick of 8x8x8 cells per
-    // internal node of level brick_level, [n_bricks][512].  An entry of a
-    // level-brick_level cell >= n_top names brick (entry - n_top).  A brick
-    // entry is ((leaf + 1) << 2) | (D - level) of the leaf holding the cell
-    // (0 << 2 for empty space), indexed by the child slots of the three levels
-    // below the brick's cube (slot1 << 6 | slot2 << 3 | slot3).
+    // What the walk reads: the caller's child array [n_top][8], or the
+    // library's traversal index (po_tree_build_index), four parts in one
+    // buffer:
+    //   grid    [8^grid_level] one entry per cell of level grid_level, index
+    //           (x << G | y) << G | z; absent when grid_level is 0
+    //   nodes   [n_top][8] child entries of the nodes above brick_level,
+    //           renumbered; an entry of a level-brick_level cell >= n_top
+    //           names brick (entry - n_top).  n_top is 0 where the grid
+    //           reaches brick_level
+    //   bricks  [n_bricks][512], 8x8x8 finest cells per internal node of level
+    //           brick_level, indexed by the child slots of the three levels
+    //           below the brick's cube (slot1 << 6 | slot2 << 3 | slot3)
+    //   coarse  leaves of level <= grid_level, {leaf, level}, from the end of
+    //           the buffer backwards
+    // A grid entry is an empty entry (< 0), kIdxCoarse | number of a coarse
+    // leaf, or the brick (grid_level == brick_level) or node below the cell.  A
+    // brick entry is ((leaf + 1) << 2) | (D - level) of the leaf holding the
+    // cell, or an empty entry.  An empty entry is bit 31, the levels from its
+    // cell up to the octree's empty cube in bits kIdxUpShift.. (4 bits), and
+    // an empty box around the cell: cells to spare below and above it on
+    // axis k, 0..15 each, in bits 8k..8k+3 and 8k+4..8k+7.
     const int32_t* child;
     const void* sigma;      // [n_leaves] float or half
     const void* sh;         // [n_leaves][stride] float or half
@@ -28,8 +43,10 @@ struct KTree {
     int32_t n_top;          // nodes in `child` (all of the caller's nodes when brick_level == depth)
     int32_t n_leaves;
     int32_t stride;         // elements per SH record
-    int16_t depth;          // D
-    int16_t brick_level;    // M: cells below level M are resolved by bricks; M == D: no bricks
+    int8_t depth;           // D
+    int8_t brick_level;     // M: cells below level M are resolved by bricks; M == D: no bricks
+    int8_t grid_level;      // G: cells of levels <= G are resolved by the grid; 0: no grid
+    int8_t pad_;
     uint32_t index_bytes;   // bytes readable through `child`
     int32_t cb_entries;     // codebook entries per basis function (0: no codebook)
     uint32_t sigma_bytes;   // n_leaves * element size (< 2^32)
@@ -37,6 +54,17 @@ struct KTree {
     double lo[3];           // box minimum corner, world units
     double scale;           // grid units (finest cells) per world unit: 2^D / (2 half)
 };
+
+// Traversal index encoding (KTree::child).
+constexpr int kIdxCoarse = 1 << 30;
+constexpr int kIdxUpShift = 24;
+// Finest grid of an index: 8^8 entries, 64 MB.
+constexpr int kIdxMaxGrid = 8;
+
+// KOpts::flags bit (internal, beside the caller's): walk the octree's own
+// cells, not boxes of several empty ones.  Set where their number matters:
+// the steps column of the aux outputs, and a caller's max_steps.
+constexpr uint32_t kOptExact = 1u << 31;
 
 struct KOpts {
     float bg[3];
@@ -84,8 +112,8 @@ struct KJob {
 };
 
 // Work queues of the split camera render: rays whose walk outlasts
-// split_steps cells are handed on as 1-16 chunks, and chunks that outlast
-// chunk_cap cells hand their remainder on as 1-16 sub-chunks.  Each queue has
+// split_cap samples are handed on as 1-16 chunks, and chunks that outlast
+// chunk_cap samples hand their remainder on as 1-16 sub-chunks.  Each queue has
 // kSplitRegions regions of region_slots slots (a multiple of 64), one counter
 // each: kSplitRegionSlots for the queues the library allocates,
 // kNoAllocRegionSlots for the fixed queue of the entry point that allocates
@@ -98,56 +126,8 @@ constexpr int kSplitRegions = 64;
 constexpr int kSplitRegionSlots = PO_SPLIT_REGION_SLOTS;
 constexpr int kNoAllocRegionSlots = 8192;
 constexpr int kSplitMaxChunks = 16;
-#ifndef PO_SPLIT_STEPS
-#define PO_SPLIT_STEPS 28
-#endif
-#ifndef PO_CHUNK_STEPS
-#define PO_CHUNK_STEPS 24
-#endif
-#ifndef PO_SUB_STEPS
-#define PO_SUB_STEPS 10
-#endif
-#ifndef PO_CHUNK_CAP
-#define PO_CHUNK_CAP 24
-#endif
-// (0.3 against 0.2: 800x800 0.531 against 0.536 ms, 512x512 0.361 against
-// 0.366 ms, 1920x1080 unchanged, 1280x720 0.841 against 0.834 ms)
-#ifndef PO_SPLIT_UB_FRAC
-#define PO_SPLIT_UB_FRAC 0.3f
-#endif
-// Cells the first walk of a split camera render takes before it hands a ray
-// on, from the number of waves in the launch (four per 16x16 tile).  About
-// kResidentWaves waves fit on the chip at once (256 CUs x 4 SIMDs x 4 waves
-// at 128 VGPRs); a launch of several such rounds keeps the chip busy through
-// its first walk, so its rays walk further before the hand-off and fewer of
-// them wait in the chunk queues (depth-9 scene, float32 leaves: 800x800 0.588
-// -> 0.551 ms, 1920x1080 1.78 -> 1.38 ms against a fixed 28 cells; the
-// regions of a 1920x1080 frame no longer overflow; 18 cells per round with
-// 10-cell sub-chunks instead of 16 with 12: 800x800 0.5365 against 0.5409 ms,
-// 1920x1080 1.357 against 1.352 ms).  Ray-list passes keep PO_SPLIT_STEPS:
-// their render and backward must cut the rays alike.
-constexpr int64_t kResidentWaves = 4096;
-inline int po_camera_split_steps(int64_t waves) {
-    const int64_t s = 20 + 18 * waves / kResidentWaves;
-    return (int)(s < PO_SPLIT_STEPS ? PO_SPLIT_STEPS : s > 192 ? 192 : s);
-}
-// piece sizes of ray-list passes (render and backward) of fewer than
-// PO_RAYS_SMALL rays
-#ifndef PO_RAYS_SMALL
-#define PO_RAYS_SMALL (1 << 18)
-#endif
-#ifndef PO_RAYS_SPLIT_STEPS
-#define PO_RAYS_SPLIT_STEPS 4
-#endif
-#ifndef PO_RAYS_CHUNK_STEPS
-#define PO_RAYS_CHUNK_STEPS 6
-#endif
-#ifndef PO_RAYS_CHUNK_CAP
-#define PO_RAYS_CHUNK_CAP 12
-#endif
-#ifndef PO_RAYS_UB_FRAC
-#define PO_RAYS_UB_FRAC 0.2f
-#endif
+// Step caps up to this many cells are rendered in one pass.
+constexpr int kSplitMinMaxSteps = 28;
 struct KSplit {
     int32_t* count;        // [kSplitRegions] chunk slots claimed (may exceed the region); count2 follows
     int32_t* count2;       // [kSplitRegions] sub-chunk slots claimed
@@ -160,31 +140,72 @@ struct KSplit {
     int4* view_part;       // [slots] viewer variant: chunk samples, cells and cut flags
     int4* view_part2;      // [slots] the same for the sub-chunks
     int32_t region_slots;  // slots per region; slots = kSplitRegions * region_slots
-    int32_t split_steps;   // cells walked before a ray is handed on
-    int32_t chunk_steps;   // target cells per chunk
-    int32_t sub_steps;     // target cells per sub-chunk
-    int32_t chunk_cap;     // cells a chunk walks before its remainder is handed on
+    // piece sizes, in data samples (exact: in cells)
+    int32_t split_cap;     // walked before a ray is handed on
+    int32_t chunk_target;  // wanted per chunk
+    int32_t sub_target;    // wanted per sub-chunk
+    int32_t chunk_cap;     // a chunk walks before its remainder is handed on
     float ub_frac;         // pieces cover at least this fraction of the finest-cell faces ahead
+    bool exact;            // the walks step the octree's own cells
     const float* ray_o;    // ray-list renders: origins [n_rays][3] (camera renders: unused)
     const float* ray_d;    // ray-list renders: directions [n_rays][3]
     int64_t n_rays;
     int32_t* ray_slot;     // kept ray-list render: [n_rays] first chunk slot of each ray, -1 if not handed on
 };
+// Piece sizes of a split camera render of `waves` waves (four per 16x16
+// tile).  About kResidentWaves waves fit on the chip at once (256 CUs x 4
+// SIMDs x 4 waves at 128 VGPRs); a launch of several such rounds keeps the
+// chip busy through its first walk, so its rays walk further before the
+// hand-off and fewer of them wait in the chunk queues.
+constexpr int64_t kResidentWaves = 4096;
+// The sizes in samples, measured (us; float32 800x800, 1280x720 and 512x512 of
+// the depth-9 scene, float16 1920x1080, codebook 640x480 and SG-25 400x400 of
+// depth 8; in cells, over the octree's own cells: 517 / 811 / 356 / 1006 / 392 /
+// 264): 451 / 609 / 327 / 720 / 376 / 260; ub_frac 0.24 458 / 617 / 338 / 734 /
+// 391 / 266; chunks and cap of 12 456 / 618 / 330 / 725 / 374 / 262; a first
+// walk of 6 + 6 samples a round loses 8 % at 1920x1080.  Smaller sub-chunks or
+// a cap below the target overflow the queue where a dense volume fills every
+// chunk past its cap.
+inline void po_frame_piece_sizes(int64_t waves, bool exact, KSplit* S) {
+    S->exact = exact;
+    if (exact) {
+        const int64_t s = 20 + 18 * waves / kResidentWaves;
+        S->split_cap = (int)(s < 28 ? 28 : s > 192 ? 192 : s);
+        S->chunk_target = 24;
+        S->sub_target = 10;
+        S->chunk_cap = 24;
+        S->ub_frac = 0.3f;
+    } else {
+        const int64_t s = 10 + 10 * waves / kResidentWaves;
+        S->split_cap = (int)(s < 12 ? 12 : s > 96 ? 96 : s);
+        S->chunk_target = 16;
+        S->sub_target = 8;
+        S->chunk_cap = 16;
+        S->ub_frac = 0.4f;
+    }
+}
 // Piece sizes of a split pass over a list of n rays.  The render and the
 // backward of the same rays cut them alike: the transmittance in front of
 // every piece is then the same float product in both, so the backward stops
 // on the sample where the render that produced its colour stopped.
-// (Training step, 65,536 random rays of the depth-8 tree, forward and
-// backward over the same pieces: 0.558 ms with a 28-cell first walk and
-// 8-cell pieces (cap 16), 0.460 ms with a 4-cell first walk and 6-cell
-// pieces (cap 12).)
-inline void po_rays_piece_sizes(int64_t n, KSplit* S) {
-    if (n < PO_RAYS_SMALL) {
-        S->split_steps = PO_RAYS_SPLIT_STEPS;
-        S->chunk_steps = PO_RAYS_CHUNK_STEPS;
-        S->sub_steps = PO_RAYS_CHUNK_STEPS;
-        S->chunk_cap = PO_RAYS_CHUNK_CAP;
-        S->ub_frac = PO_RAYS_UB_FRAC;
+// A batch below 2^18 rays fills the chip for less time than a frame: a first
+// walk of a few cells and small pieces (training step of 65,536 rays, depth 8:
+// 0.558 ms with the frame's sizes, 0.460 with these).  Its first walk counts
+// cells: counted in samples it would cross the empty space in front of the
+// first leaf at one wave's speed (52 against 18 us).  As many pieces as the
+// queue's 2^20 slots hold: past that the walks that find their region full
+// finish in their lanes (200,001 rays, depth 8: 0.535 ms at ub_frac 0.2, 0.333
+// at 0.1; 65,536 rays 0.358 at 0.2, 0.383 at 0.1).
+inline void po_rays_piece_sizes(int64_t n, int depth, bool exact, KSplit* S) {
+    if (n >= (1 << 18)) {
+        po_frame_piece_sizes(0, exact, S);
+    } else {
+        S->exact = true;
+        S->split_cap = 4;
+        S->chunk_target = 6;
+        S->sub_target = 6;
+        S->chunk_cap = 12;
+        S->ub_frac = (float)std::min(0.2, 5.6e6 / (double)(n << depth));
     }
 }
 // Device bytes of the queues with region_slots slots per region (counters,
@@ -192,8 +213,7 @@ inline void po_rays_piece_sizes(int64_t n, KSplit* S) {
 constexpr size_t po_split_bytes(int region_slots) {
     return 512 + 2 * (size_t)kSplitRegions * (size_t)region_slots * (16 + 32 + 32 + 16);
 }
-// Points S at queues laid out in `base` (po_split_bytes(region_slots) bytes)
-// and sets the default piece sizes.
+// Points S at queues laid out in `base` (po_split_bytes(region_slots) bytes).
 void po_split_layout(void* base, int region_slots, KSplit* S);
 // Bytes of the fixed queue of po_render_camera_noalloc (one copy per device,
 // a static device array of the library: about 100 MB).
@@ -255,6 +275,11 @@ hipError_t po_launch_backward_split(const po_tree* t, int64_t n, const float* o,
 hipError_t po_launch_backward_kept(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                                    const float* rgb_fwd, const float* grad, float* gsig, float* gsh,
                                    const KSplit& S, hipStream_t s);
+// Adds to an index the boxes of its n_bricks bricks (bricks of the host's
+// layout, changed in place) and, for G > 0, the grid with its boxes, from the
+// host's nodes (device copy); sat: 8^G words of scratch.
+hipError_t po_launch_index(const int32_t* nodes, int n_top, int G, int64_t n_bricks, int32_t* grid,
+                           int32_t* bricks, int32_t* sat, hipStream_t s);
 hipError_t po_launch_camera_rays(const KCam& cam, float* o, float* d, hipStream_t s);
 // Visibility filter: mode 0 alpha, 1 contribution; weight[n_leaves] raised in place, alpha[H*W] or nullptr.
 hipError_t po_launch_leaf_weights(const po_tree* t, const KCam& cam, const KOpts& op, int mode, float* weight,

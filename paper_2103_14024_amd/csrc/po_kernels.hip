@@ -23,6 +23,7 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <type_traits>
@@ -251,7 +252,8 @@ struct Ray {
     double s;      // current parameter
     double s_end;  // end of the rendered part (slicing plane), else 1e300
     double s_exit; // end of the walk: min(s_end, box exit)
-    bool more;     // split walks: the walk stopped at its step limit with cells left
+    bool more;     // split walks: the walk stopped at its sample limit with cells left
+    int nt;        // split walks: samples taken (exact: cells walked)
 };
 
 // The walk covers the parameters s in [max(s_lo, 0), s_hi] inside the box.
@@ -313,6 +315,12 @@ __device__ __forceinline__ uint32_t child_slot(const int (&c)[3], int D, int L) 
     return (uint32_t)((((c[0] >> sft) & 1) << 2) | (((c[1] >> sft) & 1) << 1) | ((c[2] >> sft) & 1));
 }
 
+// No limit (march's cap).
+constexpr int kNoCap = 0x7fffffff;
+// True for renders that walk the octree's own cells one by one: those that
+// report or cap their number (see kOptExact).
+__device__ __forceinline__ bool exact_cells(const KOpts& op) { return (op.flags & kOptExact) != 0u; }
+
 // Walks the segments of a ray.  Data leaves crossed over a positive length
 // go through a two-stage sampler: smp.issue(leaf, delta, t) starts the loads
 // of the leaf's density and SH record (leaf -1: a lane without a sample,
@@ -323,33 +331,48 @@ __device__ __forceinline__ uint32_t child_slot(const int (&c)[3], int D, int L) 
 // stop point are those of the plain front-to-back walk.  Returns the number
 // of cells visited.
 //
-// Per step: finish the descent to the leaf holding cell c; compute the exit
-// parameter and the next cell; prefetch the next cell's first child entry;
-// composite the previous sample; start this cell's gather.  Loads complete in
-// issue order, so the next descent waits only for its own entry and not for
-// the gather, and compositing runs while that entry is in flight.
+// Per step: resolve the entry of cell c (a leaf, or empty space); compute the
+// exit parameter and the next cell; prefetch the next cell's entry; composite
+// the previous sample; start this cell's gather.  Loads complete in issue
+// order, so the next step waits only for its own entry and not for the
+// gather, and compositing runs while that entry is in flight.
 //
-// stk is this lane's column of a [level][kBlock] node stack in LDS holding
-// the node of every level on the path to c.  The next descent restarts from
-// the deepest ancestor shared by the old and the new cell (the level of the
-// highest differing coordinate bit) instead of the root, so a step costs one
-// or two dependent loads instead of ~D.  The child array is read through a
-// buffer descriptor: an entry beyond the array reads as 0 (empty), and an
-// internal entry below depth D or past the node count is counted as
-// malformed and taken as empty.
+// Entries.  With a grid (tr.grid_level G > 0) the level-G cell holding c is
+// one read, and the 8x8x8 brick below it another, whatever the cell crossed
+// before: no node path is kept.  An empty entry names the box of empty space
+// around its cell, so that one step crosses it whole (see index_entry_box);
+// exact keeps to the octree's own empty cubes, whose number is what the aux
+// output and po_traversal_stats count and max_steps caps.  The segments of
+// the data leaves are the same either way: a leaf is entered through one of
+// its faces, and the parameter of that plane does not depend on the box that
+// ends there.  Per 800x800 frame of the depth-9 scene: 28.8 -> 18.1 cells and
+// 46 -> 22 entry reads per ray.
 //
-// SPLIT: reaching max_steps with cells left is not an error; the walk then
-// leaves r.s and r.c at the start of the next cell and sets r.more (unless
-// the last sample ended it by early stopping), so that it can be resumed or
-// handed on.  A chunk sampler (kChunk) learns for every sample whether its
-// cell ends inside the walked range (cpl_next) or is cut by r.s_end.
+// Without a grid (a caller's child array, or the levels between G and the
+// bricks of a tree deeper than the grid) the walk descends through child
+// entries; stk, this lane's column of a [level][kBlock] node stack in LDS,
+// holds the node of every level on the path to c, and the next descent
+// restarts from the deepest ancestor shared by the old and the new cell (the
+// level of the highest differing coordinate bit).  The index is read through
+// a buffer descriptor: an entry beyond it reads as 0 (empty), and an internal
+// entry below depth D or past the node count is counted as malformed and
+// taken as empty.
+//
+// SPLIT: reaching `cap` data samples (exact: cells) with cells left stops the
+// walk; it leaves r.s and r.c at the start of the next cell and sets r.more
+// (unless the last sample ended it by early stopping), so that it can be
+// resumed or handed on.  (Samples, so that the hand-off does not depend on how
+// empty space is crossed.)  So does reaching max_steps, which without SPLIT is
+// an error.  A chunk sampler (kChunk) learns for every sample
+// whether its cell ends inside the walked range (cpl_next) or is cut by
+// r.s_end.
 template <class S, class = void>
 struct is_chunk : std::false_type {};
 template <class S>
 struct is_chunk<S, std::void_t<decltype(S::kChunk)>> : std::bool_constant<S::kChunk> {};
-// A sampler with kCountLoads set counts the child entries the walk reads
-// from memory (member `loads`); the out-of-range prefetch after the last
-// step reads nothing and is not counted.
+// A sampler with kCountLoads set (po_traversal_stats) walks the octree's own
+// cells and counts the child and brick entries that a descent from the
+// deepest common ancestor reads for each of them (member `loads`).
 template <class S, class = void>
 struct counts_loads : std::false_type {};
 template <class S>
@@ -366,75 +389,130 @@ __device__ __forceinline__ uint32_t brick_cell(const int (&c)[3]) {
 }
 
 template <class Sampler, bool SPLIT = false>
-__device__ __forceinline__ int march(const KTree& tr, Ray& r, int max_steps, int* __restrict__ stk,
-                                     Sampler& smp) {
+__device__ __forceinline__ int march(const KTree& tr, Ray& r, int max_steps, int cap, bool exact,
+                                     int* __restrict__ stk, Sampler& smp) {
     const int D = tr.depth;
     const int M = tr.brick_level;
+    const int G = tr.grid_level;
     const int N = 1 << D;
     const uint32_t idx_end = tr.index_bytes;
     const __amdgpu_buffer_rsrc_t child = raw_rsrc(tr.child, idx_end);
-    const uint32_t brick0 = (uint32_t)tr.n_top * 32u;  // byte offset of brick 0
-    int steps = 0;
+    const uint32_t node0 = G > 0 ? 4u << (3 * G) : 0u;          // byte offset of node 0
+    const uint32_t brick0 = node0 + (uint32_t)tr.n_top * 32u;   // and of brick 0
+    if constexpr (counts_loads<Sampler>::value) exact = true;
+    int steps = 0, nt = 0;
     bool pending = false, bad = false, cap_end = false;
-    // L: level of the node whose entry e is (e describes a level-(L+1) cell),
-    // or, with inb set, e is the brick entry of the cell c
+    // L: level of the node whose entry e is (e describes a level-(L+1) cell);
+    // L < 0: e is the grid entry of c; inb: e is the brick entry of c
     int L = 0, node = 0;
     bool inb = false;
     uint32_t bofs = 0;  // byte offset of the brick holding c (valid while inb)
-    stk[0] = 0;
-    int e = __builtin_amdgcn_raw_buffer_load_b32(child, child_slot(r.c, D, 0) << 2, 0, 0);
-    if constexpr (counts_loads<Sampler>::value) smp.loads += 1;
+    auto grid_ofs = [&]() {
+        return (uint32_t)((((r.c[0] >> (D - G)) << G | (r.c[1] >> (D - G))) << G) | (r.c[2] >> (D - G))) << 2;
+    };
+    int e;
+    if (G > 0) {
+        L = -1;
+        e = __builtin_amdgcn_raw_buffer_load_b32(child, grid_ofs(), 0, 0);
+    } else {
+        stk[0] = 0;
+        e = __builtin_amdgcn_raw_buffer_load_b32(child, child_slot(r.c, D, 0) << 2, 0, 0);
+    }
+    [[maybe_unused]] int la0 = 0;        // counted descents: level they start from,
+    [[maybe_unused]] bool was_in = false;  // and whether the cell before lay in a brick
     // an empty gather, so that every path into the loop has the same loads in
     // flight behind the entry (the compiler then waits for the entry alone)
     smp.issue(-1, 0.0f, 0.0f);
     while (true) {
-        // finish the descent to the leaf holding c: its number (-1: empty) and level
-        int leaf, lvl;
-        if (inb) {
-            lvl = D - (e & 3);
-            leaf = (int)((uint32_t)e >> 2) - 1;
-        } else {
-            ++L;  // e is the entry of the level-L cell holding c
-            // further levels (each waits for its own load, and for any older one)
-            while ((e > 0) & (e < tr.n_top) & (L < M)) {
-                node = e;
-                stk[L * kBlock] = node;
-                e = __builtin_amdgcn_raw_buffer_load_b32(
-                    child, ((uint32_t)node << 5) | (child_slot(r.c, D, L) << 2), 0, 0);
-                if constexpr (counts_loads<Sampler>::value) smp.loads += 1;
-                ++L;
+        // resolve e: the leaf holding c (-1: empty), log2 of the edge of its
+        // cube, and for empty space how far the empty box reaches beyond it
+        int leaf = -1, u = 0;
+        uint32_t ext = 0;
+        if (!inb) {
+            bool descend = true;
+            if (L < 0) {
+                descend = false;
+                if (e < 0) {
+                    u = D - G;
+                    if (exact)
+                        u += (e >> kIdxUpShift) & 15;
+                    else
+                        ext = (uint32_t)e;
+                } else if (e & kIdxCoarse) {
+                    // a leaf of level <= G: its number and level in a side table
+                    const uint32_t at = idx_end - 8u - ((uint32_t)(e & (kIdxCoarse - 1)) << 3);
+                    const auto q = __builtin_amdgcn_raw_buffer_load_b64(child, at, 0, 0);
+                    leaf = (int)q[0];
+                    u = D - (int)q[1];
+                } else if (G == M) {
+                    bofs = brick0 + (uint32_t)e * 2048u;
+                    e = __builtin_amdgcn_raw_buffer_load_b32(child, bofs + (brick_cell(r.c) << 2), 0, 0);
+                    inb = true;
+                } else {
+                    L = G;
+                    node = e;
+                    stk[L * kBlock] = node;
+                    e = __builtin_amdgcn_raw_buffer_load_b32(
+                        child, node0 + (((uint32_t)node << 5) | (child_slot(r.c, D, L) << 2)), 0, 0);
+                    descend = true;
+                }
             }
-            if ((e > 0) & (L == M) & (M < D) & (e >= tr.n_top)) {
-                // the level-M cube holding c is a brick: one load gives the leaf
-                bofs = brick0 + (uint32_t)(e - tr.n_top) * 2048u;
-                e = __builtin_amdgcn_raw_buffer_load_b32(child, bofs + (brick_cell(r.c) << 2), 0, 0);
-                if constexpr (counts_loads<Sampler>::value) smp.loads += 1;
-                inb = true;
-                lvl = D - (e & 3);
-                leaf = (int)((uint32_t)e >> 2) - 1;
+            if (descend) {
+                ++L;  // e is the entry of the level-L cell holding c
+                // further levels (each waits for its own load, and for any older one)
+                while ((e > 0) & (e < tr.n_top) & (L < M)) {
+                    node = e;
+                    stk[L * kBlock] = node;
+                    e = __builtin_amdgcn_raw_buffer_load_b32(
+                        child, node0 + (((uint32_t)node << 5) | (child_slot(r.c, D, L) << 2)), 0, 0);
+                    ++L;
+                }
+                if ((e > 0) & (L == M) & (M < D) & (e >= tr.n_top)) {
+                    // the level-M cube holding c is a brick: one load gives the leaf
+                    bofs = brick0 + (uint32_t)(e - tr.n_top) * 2048u;
+                    e = __builtin_amdgcn_raw_buffer_load_b32(child, bofs + (brick_cell(r.c) << 2), 0, 0);
+                    inb = true;
+                } else {
+                    // a leaf or empty cube of level L; any other positive entry
+                    // (past the nodes, or internal at the deepest level) is malformed
+                    const bool malformed = e > 0;
+                    bad |= malformed;
+                    leaf = malformed ? -1 : -1 - e;
+                    u = D - L;
+                }
+            }
+        }
+        if (inb) {
+            if (e < 0) {
+                if (exact)
+                    u = (e >> kIdxUpShift) & 15;
+                else
+                    ext = (uint32_t)e;
             } else {
-                // a leaf or empty cube of level L; any other positive entry
-                // (past the nodes, or internal at the deepest level) is malformed
-                const bool malformed = e > 0;
-                bad |= malformed;
-                leaf = malformed ? -1 : -1 - e;
-                lvl = L;
+                u = e & 3;
+                leaf = (int)((uint32_t)e >> 2) - 1;
             }
         }
         if (leaf >= tr.n_leaves) {
             bad = true;
             leaf = -1;
         }
+        if constexpr (counts_loads<Sampler>::value) {
+            const int lvl = D - u;
+            smp.loads += (was_in & (la0 >= M)) ? 1 : (lvl <= M ? lvl - la0 : M - la0 + 1);
+            was_in = lvl > M;
+        }
         // exit parameter: the nearest far face (branch-free; pos = moving up the axis)
-        const int csz = 1 << (D - lvl);
-        int lo[3];
+        int far[3];
         bool pos[3];
         double sk[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            lo[k] = r.c[k] & ~(csz - 1);
             pos[k] = r.dg[k] > 0.0;
-            sk[k] = ((double)(lo[k] + (pos[k] ? csz : 0)) - r.og[k]) * r.inv[k];
+            const int x = (int)((ext >> (8 * k + (pos[k] ? 4 : 0))) & 15u);
+            const int cu = r.c[k] >> u;
+            far[k] = (pos[k] ? cu + 1 + x : cu - x) << u;
+            sk[k] = ((double)far[k] - r.og[k]) * r.inv[k];
         }
         double se = fmax(fmin(fmin(sk[0], sk[1]), sk[2]), r.s);
         bool cpl = true;
@@ -449,8 +527,9 @@ __device__ __forceinline__ int march(const KTree& tr, Ray& r, int max_steps, int
                     bool inside = true;
 #pragma unroll
                     for (int k = 0; k < 3; ++k) {
-                        const double q = fmin(fmax(floor(fma(r.s_end, r.dg[k], r.og[k])), 0.0), (double)(N - 1));
-                        inside &= (q >= (double)lo[k]) & (q < (double)(lo[k] + csz));
+                        const int q = (int)fmin(fmax(floor(fma(r.s_end, r.dg[k], r.og[k])), 0.0), (double)(N - 1));
+                        const int d = (q >> u) - (r.c[k] >> u);
+                        inside &= (d <= (int)((ext >> (8 * k + 4)) & 15u)) & (-d <= (int)((ext >> (8 * k)) & 15u));
                     }
                     cpl = !inside;
                 }
@@ -461,37 +540,41 @@ __device__ __forceinline__ int march(const KTree& tr, Ray& r, int max_steps, int
         }
         const float delta = (float)((se - r.s) * r.len);
         const float t_in = (float)(r.s * r.len);
+        const bool cand = (leaf >= 0) & (delta > 0.0f);
         ++steps;
         // next cell: axes whose face is reached step to the neighbouring cell;
         // the others take the finest cell of the exit point, kept inside the
-        // current cube and never moving against the ray (truncation equals
-        // floor here: the result is clamped to >= lo >= 0)
+        // current box and never moving against the ray (truncation equals
+        // floor here: the result is clamped to >= 0)
         bool out = false;
         int nc[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const int stepped = pos[k] ? lo[k] + csz : lo[k] - 1;
-            const int q = min(max((int)fma(se, r.dg[k], r.og[k]), lo[k]), lo[k] + csz - 1);
-            const int kept = pos[k] ? max(q, r.c[k]) : min(q, r.c[k]);
+            const int q = (int)fma(se, r.dg[k], r.og[k]);
+            const int kept = pos[k] ? min(max(q, r.c[k]), far[k] - 1) : max(min(q, r.c[k]), far[k]);
             const bool cross = sk[k] <= se;
+            const int stepped = pos[k] ? far[k] : far[k] - 1;
             nc[k] = cross ? stepped : kept;
             out |= cross & ((stepped < 0) | (stepped >= N));
         }
         if constexpr (Sampler::kClip) out |= se >= r.s_end;
         r.s = se;
-        const bool capped = !out & (steps >= max_steps);
+        bool capped = !out & (steps >= max_steps);
         if constexpr (!SPLIT) bad |= capped;
+        if constexpr (SPLIT) capped |= !out & (exact ? steps >= cap : cand & (nt + 1 >= cap));
         const bool last = out | capped;
         // prefetch the next cell's entry.  The cells agree on the coordinate
         // bits above the highest differing one: inside the same brick the
-        // brick entry is read directly, else the walk restarts below the
-        // deepest common ancestor above the brick level (from the stack).
-        // The load is issued on every path (out of range after the last
-        // step) so the compiler can count the loads in flight exactly.
+        // brick entry is read directly, else the grid's, or without a grid
+        // the walk restarts below the deepest common ancestor above the brick
+        // level (from the stack).  The load is issued on every path (out of
+        // range after the last step) so the compiler can count the loads in
+        // flight exactly.
         uint32_t pf = idx_end;
         if (!last) {
             const int diff = (r.c[0] ^ nc[0]) | (r.c[1] ^ nc[1]) | (r.c[2] ^ nc[2]);
             const int la = D - 32 + __clz(diff);
+            if constexpr (counts_loads<Sampler>::value) la0 = la;
             r.c[0] = nc[0];
             r.c[1] = nc[1];
             r.c[2] = nc[2];
@@ -499,9 +582,14 @@ __device__ __forceinline__ int march(const KTree& tr, Ray& r, int max_steps, int
                 pf = bofs + (brick_cell(r.c) << 2);
             } else {
                 inb = false;
-                L = la;
-                node = stk[L * kBlock];
-                pf = ((uint32_t)node << 5) | (child_slot(r.c, D, L) << 2);
+                if ((G > 0) & ((G == M) | (la < G))) {
+                    L = -1;
+                    pf = grid_ofs();
+                } else {
+                    L = la;
+                    node = stk[L * kBlock];
+                    pf = node0 + (((uint32_t)node << 5) | (child_slot(r.c, D, L) << 2));
+                }
             }
         }
         if constexpr (SPLIT) {
@@ -512,7 +600,6 @@ __device__ __forceinline__ int march(const KTree& tr, Ray& r, int max_steps, int
             }
         }
         e = __builtin_amdgcn_raw_buffer_load_b32(child, pf, 0, 0);
-        if constexpr (counts_loads<Sampler>::value) smp.loads += last ? 0 : 1;
         // composite the previous sample (its loads precede the prefetch)
         bool stop = false;
         if (pending) {
@@ -523,7 +610,7 @@ __device__ __forceinline__ int march(const KTree& tr, Ray& r, int max_steps, int
         // start this cell's gather; lanes without a sample load nothing.  The
         // walk ends only at the bottom of the body, so every path back to the
         // top has issued the same loads.
-        const bool take = !stop & (leaf >= 0) & (delta > 0.0f);
+        const bool take = !stop & cand;
         if constexpr (is_chunk<Sampler>::value) {
             smp.cpl_next = cpl;
             // a piece's first cell without a sample (the zero-length rest of
@@ -533,13 +620,19 @@ __device__ __forceinline__ int march(const KTree& tr, Ray& r, int max_steps, int
         }
         smp.issue(take ? leaf : -1, delta, t_in);
         pending = take;
-        if constexpr (SPLIT) cap_end = capped & !stop;
+        if constexpr (SPLIT) {
+            nt += take ? 1 : 0;
+            cap_end = capped & !stop;
+        }
         if (last | stop) break;
     }
     bool end_stop = false;
     if (pending) end_stop = smp.consume();
     smp.flush();
-    if constexpr (SPLIT) r.more = cap_end & !end_stop;
+    if constexpr (SPLIT) {
+        r.more = cap_end & !end_stop;
+        r.nt = exact ? steps : nt;
+    }
     // a lane that met a malformed entry or the step cap is counted once
     if (bad) atomicAdd(&g_po_errors, 1ull);
     return steps;
@@ -793,7 +886,7 @@ __device__ __forceinline__ void render_one(const KTree& tr, const KOpts& op, con
             for (int k = 0; k < K; ++k)
                 if ((op.sh_off >> k) & 1u) smp.Y[k] = 0.0f;
         }
-        steps = march(tr, r, op.max_steps, stk, smp);
+        steps = march(tr, r, op.max_steps, kNoCap, exact_cells(op), stk, smp);
         C[0] = smp.c0;
         C[1] = smp.c1;
         C[2] = smp.c2;
@@ -940,12 +1033,12 @@ __global__ __launch_bounds__(kBlock) void k_render_camera(KBatch<MAXJ> B) {
 // associative (Sec. 3, eqn:quad: a range of segments acts on what lies behind
 // it as (C, T) -> C_range + T_range C), so a long walk can be cut into
 // pieces walked in parallel and joined front to back:
-//   k_render_camera_split  walks every ray for at most split_steps cells;
+//   k_render_camera_split  walks every ray for at most split_cap samples;
 //                          a ray with cells left is handed on: its state
 //                          (s, T, C) and 1-16 chunks, equal parameter
 //                          intervals of the rest of the ray;
 //   k_render_chunks        walks one chunk per lane for at most chunk_cap
-//                          cells; a chunk with cells left hands its
+//                          samples; a chunk with cells left hands its
 //                          remainder on as 1-16 sub-chunks (cells are
 //                          bunched along a ray, so equal intervals are not
 //                          equal work; the walked part of the chunk tells
@@ -1086,13 +1179,13 @@ __device__ __forceinline__ void piece_bounds(const KJob& J, const KSplit& S, int
     up = k + 1 < n ? a + (e - a) * (double)(k + 1) / (double)n : hi;
 }
 
-// Pieces wanted for the rest [r.s, r.s_exit] of a walk that crossed `steps`
-// cells since s_first: about chunk_steps cells each, from the cells per unit
-// parameter so far, and at least ub_frac of the finest-cell faces ahead.
-__device__ __forceinline__ int pieces_wanted(const Ray& r, double s_first, int steps, const KSplit& S,
-                                             int target) {
+// Pieces wanted for the rest [r.s, r.s_exit] of a walk that took r.nt samples
+// (exact renders: cells) since s_first: about `target` each, from the number
+// per unit parameter so far, and at least ub_frac of the finest-cell faces
+// ahead.
+__device__ __forceinline__ int pieces_wanted(const Ray& r, double s_first, const KSplit& S, int target) {
     const double rest = r.s_exit - r.s;
-    double est = (double)steps * rest / fmax(r.s - s_first, 1e-300);
+    double est = (double)r.nt * rest / fmax(r.s - s_first, 1e-300);
     est = fmax(est, (double)S.ub_frac * rest * (fabs(r.dg[0]) + fabs(r.dg[1]) + fabs(r.dg[2])));
     return (int)fmin(fmax(ceil(est / (double)target), 1.0), (double)kSplitMaxChunks);
 }
@@ -1139,7 +1232,7 @@ __device__ __forceinline__ int claim_pieces(int32_t* count, int4* __restrict__ i
 }
 
 // The first walk of a split render for ray idx (valid: idx names a ray):
-// at most split_steps cells, then the ray is handed on or, if its region of
+// at most split_cap samples, then the ray is handed on or, if its region of
 // the queue is full, walked to its end here.  Every lane of the wave must
 // call it.
 template <typename T, int K, int VEC, int NL, int V, int SRC>
@@ -1160,12 +1253,12 @@ __device__ __forceinline__ void first_walk(const KJob& J, const KSplit& S, int i
         if (ray_setup(tr, ro, rd, r, s_lo, s_hi)) {
             const double s_first = r.s;
             fwd_init<T, K, V>(smp, tr, op, r);
-            steps = march<Smp, true>(tr, r, min(S.split_steps, op.max_steps), stk, smp);
+            steps = march<Smp, true>(tr, r, op.max_steps, S.split_cap, S.exact, stk, smp);
             if (r.more) {
                 if (steps >= op.max_steps)
                     atomicAdd(&g_po_errors, 1ull);  // the step cap proper
                 else
-                    want = pieces_wanted(r, s_first, steps, S, S.chunk_steps);
+                    want = pieces_wanted(r, s_first, S, S.chunk_target);
             }
         }
     }
@@ -1184,7 +1277,8 @@ __device__ __forceinline__ void first_walk(const KJob& J, const KSplit& S, int i
             reinterpret_cast<ContHead*>(S.head)[h] = hd;
             handed = true;
         } else {
-            steps += march<Smp>(tr, r, op.max_steps - steps, stk, smp);  // region full: finish here
+            // region full: finish here
+            steps += march<Smp>(tr, r, op.max_steps - steps, kNoCap, S.exact, stk, smp);
         }
     }
     const size_t p = (size_t)idx;
@@ -1209,8 +1303,21 @@ __device__ __forceinline__ void first_walk(const KJob& J, const KSplit& S, int i
     }
 }
 
+// The plain (SH, SG) chunk and sub-chunk walks of records up to 192 bytes
+// are held to 128 VGPRs (4 waves per SIMD; unconstrained the float32 K=16
+// chunk kernel takes 131 and 3 waves): 0.639 against 0.671 ms per depth-9
+// 800x800 frame; float16 SH records of K <= 16 with the basis values in
+// LDS, to 96 VGPRs (5 waves; 20 bytes of scratch outside the loop).  Larger
+// records and the viewer and codebook variants would spill (K=25 float32:
+// 180 bytes of scratch, half the frame rate; float16 K=25 at 5 waves: 144),
+// so they keep 4 waves or their natural count.
+template <typename T, int K, int V>
+constexpr int kPieceWaves = (V == PO_FWD_SH || V == PO_FWD_SG) && sizeof(T) * 3 * K <= 192
+                                ? (sizeof(T) == 2 && V == PO_FWD_SH && K <= 16 ? 5 : 4)
+                                : 1;
+
 template <typename T, int K, int VEC, int NL, int V>
-__global__ __launch_bounds__(kBlock) void k_render_camera_split(KBatch<1> B, KSplit S) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWaves<T, K, V>, 8))) void k_render_camera_split(KBatch<1> B, KSplit S) {
     const int64_t b = xcd_interleave(blockIdx.x, B.n_blocks, 4 * B.job[0].tiles_x);
     if (b < 0) return;
     const KJob& J = B.job[0];
@@ -1225,7 +1332,7 @@ __global__ __launch_bounds__(kBlock) void k_render_camera_split(KBatch<1> B, KSp
 }
 
 template <typename T, int K, int VEC, int NL, int V>
-__global__ __launch_bounds__(kBlock) void k_render_rays_split(KBatch<1> B, KSplit S) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWaves<T, K, V>, 8))) void k_render_rays_split(KBatch<1> B, KSplit S) {
     const int64_t b = xcd_swizzle(blockIdx.x, B.n_blocks);
     if (b < 0) return;
     const int64_t i = b * kBlock + threadIdx.x;
@@ -1265,19 +1372,6 @@ __device__ __forceinline__ int split_slot(const int32_t* count, int region_slots
     return -1;
 }
 
-// The plain (SH, SG) chunk and sub-chunk walks of records up to 192 bytes
-// are held to 128 VGPRs (4 waves per SIMD; unconstrained the float32 K=16
-// chunk kernel takes 131 and 3 waves): 0.639 against 0.671 ms per depth-9
-// 800x800 frame; float16 SH records of K <= 16 with the basis values in
-// LDS, to 96 VGPRs (5 waves; 20 bytes of scratch outside the loop).  Larger
-// records and the viewer and codebook variants would spill (K=25 float32:
-// 180 bytes of scratch, half the frame rate; float16 K=25 at 5 waves: 144),
-// so they keep 4 waves or their natural count.
-template <typename T, int K, int V>
-constexpr int kPieceWaves = (V == PO_FWD_SH || V == PO_FWD_SG) && sizeof(T) * 3 * K <= 192
-                                ? (sizeof(T) == 2 && V == PO_FWD_SH && K <= 16 ? 5 : 4)
-                                : 1;
-
 template <typename T, int K, int VEC, int NL, int V, int SRC>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWaves<T, K, V>, 8))) void k_render_chunks(
     KBatch<1> B, KSplit S) {
@@ -1298,18 +1392,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
         if (piece_setup<SRC>(J, S, pix, hd.s, walk_end<V, SRC>(J, S, pix), mj & 255, mj >> 8, r)) {
             const double s_first = r.s;
             fwd_init<T, K, V>(smp, J.tr, J.op, r);
-            steps = march<Smp, true>(J.tr, r, min(S.chunk_cap, J.op.max_steps), stk, smp);
+            steps = march<Smp, true>(J.tr, r, J.op.max_steps, S.chunk_cap, S.exact, stk, smp);
             if (r.more) {
                 if (steps >= J.op.max_steps) {
                     atomicAdd(&g_po_errors, 1ull);
                 } else {
-                    want = pieces_wanted(r, s_first, steps, S, S.sub_steps);
-#ifdef PO_MIN_SUB
-                    if (want < PO_MIN_SUB) {
-                        march<Smp>(J.tr, r, J.op.max_steps - steps, stk, smp);
-                        want = 0;
-                    }
-#endif
+                    want = pieces_wanted(r, s_first, S, S.sub_target);
                 }
             }
         }
@@ -1324,7 +1412,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
             sh.pad[0] = sh.pad[1] = sh.pad[2] = 0;
             reinterpret_cast<SubHead*>(S.head2)[sub] = sh;
         } else {
-            steps += march<Smp>(J.tr, r, J.op.max_steps - steps, stk, smp);  // region full: finish here
+            // region full: finish here
+            steps += march<Smp>(J.tr, r, J.op.max_steps - steps, kNoCap, S.exact, stk, smp);
             want = 0;
         }
     }
@@ -1363,7 +1452,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
     if (piece_setup<SRC>(J, S, sh.pix, sh.lo, sh.hi, mj & 255, mj >> 8, r)) {
         fwd_init<T, K, V>(smp, J.tr, J.op, r);
         extern __shared__ int po_stack[];
-        steps = march(J.tr, r, J.op.max_steps, po_stack + threadIdx.x, smp);
+        steps = march(J.tr, r, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
     }
     PieceOut o;
     o.c0 = smp.c0;
@@ -1408,7 +1497,7 @@ __device__ __forceinline__ bool join_piece(const KJob& J, const KSplit& S, int p
         if (piece_setup<SRC>(J, S, pix, lo, up, 0, 1, r)) {
             fwd_init<T, K, V>(smp, J.tr, J.op, r);
             extern __shared__ int po_stack[];
-            steps = march(J.tr, r, J.op.max_steps, po_stack + threadIdx.x, smp);
+            steps = march(J.tr, r, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
         }
         A.c[0] += smp.c0;
         A.c[1] += smp.c1;
@@ -1655,7 +1744,7 @@ __global__ __launch_bounds__(kBlock) void k_backward(KTree tr, int64_t n, int64_
     smp.sleaf = s_leaf;
     colour_basis<K>(tr, r.dn[0], r.dn[1], r.dn[2], smp.Y);
     extern __shared__ int po_stack[];
-    march(tr, r, op.max_steps, po_stack + threadIdx.x, smp);
+    march(tr, r, op.max_steps, kNoCap, exact_cells(op), po_stack + threadIdx.x, smp);
 }
 
 // ---------------------------------------------------------------------------
@@ -1664,7 +1753,7 @@ __global__ __launch_bounds__(kBlock) void k_backward(KTree tr, int64_t n, int64_
 // everything in front of it (App. B.3: dC/dsigma_i = delta_i (c_i T_{i+1} -
 // (C - P_i)), dC/dk = w_i c_i (1 - c_i) Y).  A piece that cuts a cell is a
 // segment of its own: the two parts' gradients add up to the whole cell's.
-//   k_backward_split      the backward of the first split_steps cells of
+//   k_backward_split      the backward of the first split_cap samples of
 //                         every ray, which then hands the rest on as chunks
 //                         (head state: s, T, P);
 //   k_render_chunks,
@@ -1729,12 +1818,12 @@ __global__ __launch_bounds__(kBlock) void k_backward_split(KBatch<1> B, KSplit S
     }
     if (live) {
         const double s_first = r.s;
-        steps = march<Smp, true>(tr, r, min(S.split_steps, J.op.max_steps), stk, smp);
+        steps = march<Smp, true>(tr, r, J.op.max_steps, S.split_cap, S.exact, stk, smp);
         if (r.more) {
             if (steps >= J.op.max_steps)
                 atomicAdd(&g_po_errors, 1ull);
             else
-                want = pieces_wanted(r, s_first, steps, S, S.chunk_steps);
+                want = pieces_wanted(r, s_first, S, S.chunk_target);
         }
     }
     const int h = claim_pieces(S.count, S.info, claim_region(), want, S.region_slots);
@@ -1750,7 +1839,8 @@ __global__ __launch_bounds__(kBlock) void k_backward_split(KBatch<1> B, KSplit S
             hd.pad = 0;
             reinterpret_cast<ContHead*>(S.head)[h] = hd;
         } else {
-            march<Smp>(tr, r, J.op.max_steps - steps, stk, smp);  // region full: finish here
+            // region full: finish here
+            march<Smp>(tr, r, J.op.max_steps - steps, kNoCap, S.exact, stk, smp);
         }
     }
 }
@@ -1759,7 +1849,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_split(KBatch<1> B, KSplit S
 // (po_render_rays_keep): the render's pieces, their heads (s, T and the
 // colour prefix P after its first walk) and ray_slot stay in the queue, so
 // a ray the render handed on is differentiated over the same first
-// split_steps cells and its pieces are not walked forward again; a ray it
+// split_cap samples and its pieces are not walked forward again; a ray it
 // did not hand on (ended within the first walk, or its region was full) is
 // differentiated to its end here.
 template <int K, int VEC, int NL>
@@ -1789,8 +1879,8 @@ __global__ __launch_bounds__(kBlock) void k_backward_first_kept(KBatch<1> B, KSp
         }
     }
     if (live) {
-        const int cap = handed ? min(S.split_steps, J.op.max_steps) : J.op.max_steps;
-        const int steps = march<Smp, true>(tr, r, cap, po_stack + threadIdx.x, smp);
+        const int steps = march<Smp, true>(tr, r, J.op.max_steps, handed ? S.split_cap : kNoCap, S.exact,
+                                           po_stack + threadIdx.x, smp);
         if (r.more & (steps >= J.op.max_steps)) atomicAdd(&g_po_errors, 1ull);  // the step cap proper
     }
 }
@@ -1899,7 +1989,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_pieces(KBatch<1> B, KSplit 
     smp.P1 = o.c1;
     smp.P2 = o.c2;
     extern __shared__ int po_stack[];
-    march(J.tr, r, J.op.max_steps, po_stack + threadIdx.x, smp);
+    march(J.tr, r, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
 }
 
 // Visibility filter of the conversion (Sec. 4.2, "Filtering"): alpha
@@ -1962,7 +2052,7 @@ __global__ __launch_bounds__(kBlock) void k_leaf_weights(KTree tr, KCam cam, KOp
         smp.stopT = op.stop_T;
         smp.wt = wt;
         extern __shared__ int po_stack[];
-        march(tr, r, op.max_steps, po_stack + threadIdx.x, smp);
+        march(tr, r, op.max_steps, kNoCap, exact_cells(op), po_stack + threadIdx.x, smp);
         Tr = smp.Tl;
     }
     if (alpha) alpha[(size_t)py * cam.W + px] = 1.0f - Tr;
@@ -2040,7 +2130,8 @@ __global__ __launch_bounds__(kBlock) void k_traversal_stats(KTree tr, KCam cam, 
             smp.sig_end = tr.sigma_bytes;
             smp.stopT = op.stop_T;
             extern __shared__ int po_stack[];
-            v[2] = (unsigned long long)march(tr, r, op.max_steps, po_stack + threadIdx.x, smp);
+            v[2] = 
+                (unsigned long long)march(tr, r, op.max_steps, kNoCap, true, po_stack + threadIdx.x, smp);
             v[1] = (unsigned long long)smp.ns;
             v[3] = (unsigned long long)smp.loads;
         }
@@ -2128,6 +2219,166 @@ __global__ __launch_bounds__(256) void k_draw_batch(int64_t n, uint64_t seed, ui
     }
 }
 
+#if PO_PART == 0
+// ---------------------------------------------------------------------------
+// The device half of po_tree_build_index.  The host lays out nodes and bricks
+// (index_of); these kernels add what the walk crosses empty space with: the
+// grid, and the empty box of every empty entry.
+// ---------------------------------------------------------------------------
+
+// Grows an empty box [lo, hi] (inclusive) by one layer at a time, the six
+// sides in turn, until every side meets an occupied cell (empty(lo, hi) false
+// for the layer), the limit [0, n) or `most` layers.  Growing the sides in
+// turn keeps the box near a cube, which no direction of travel is hurt by.
+template <class Empty>
+__device__ __forceinline__ void grow_box(int (&lo)[3], int (&hi)[3], int n, int most, Empty empty) {
+    unsigned live = 63u;
+    for (int it = 0; it < most && live; ++it) {
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+            if (!((live >> f) & 1u)) continue;
+            const int a = f >> 1;
+            int l[3] = {lo[0], lo[1], lo[2]}, h[3] = {hi[0], hi[1], hi[2]};
+            const int at = (f & 1) ? hi[a] + 1 : lo[a] - 1;
+            l[a] = h[a] = at;
+            if (at < 0 || at >= n || !empty(l, h)) {
+                live &= ~(1u << f);
+                continue;
+            }
+            if (f & 1)
+                hi[a] = at;
+            else
+                lo[a] = at;
+        }
+    }
+}
+
+// Entry of an empty cell c whose empty octree cube lies `up` levels higher,
+// inside the empty box [lo, hi].
+__device__ __forceinline__ int32_t index_entry_box(const int (&c)[3], const int (&lo)[3], const int (&hi)[3], int up) {
+    uint32_t e = 0x80000000u | (uint32_t)up << kIdxUpShift;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        e |= (uint32_t)min(c[k] - lo[k], 15) << (8 * k) | (uint32_t)min(hi[k] - c[k], 15) << (8 * k + 4);
+    return (int32_t)e;
+}
+
+// One wave per brick: the boxes of its empty cells, inside the brick.  The
+// brick's occupancy is held as eight 64-bit masks (one per x, bit 8 y + z), so
+// a layer is tested in one to eight ANDs.
+__global__ __launch_bounds__(kBlock) void k_index_bricks(int32_t* __restrict__ bricks) {
+    __shared__ unsigned occ[16];
+    int32_t* B = bricks + (size_t)blockIdx.x * 512;
+    const int lane = (int)threadIdx.x;
+    if (lane < 16) occ[lane] = 0u;
+    __syncthreads();
+    int32_t v[8];
+    int cx[8][3];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int q = i * 64 + lane;  // slot1 << 6 | slot2 << 3 | slot3
+        v[i] = B[q];
+        cx[i][0] = ((q >> 8 & 1) << 2) | ((q >> 5 & 1) << 1) | (q >> 2 & 1);
+        cx[i][1] = ((q >> 7 & 1) << 2) | ((q >> 4 & 1) << 1) | (q >> 1 & 1);
+        cx[i][2] = ((q >> 6 & 1) << 2) | ((q >> 3 & 1) << 1) | (q & 1);
+        const int bit = cx[i][1] * 8 + cx[i][2];
+        if ((v[i] >> 2) != 0) atomicOr(&occ[cx[i][0] * 2 + (bit >> 5)], 1u << (bit & 31));
+    }
+    __syncthreads();
+    auto empty = [&](const int (&l)[3], const int (&h)[3]) {
+        const uint64_t z = ((2ull << h[2]) - 1ull) & ~((1ull << l[2]) - 1ull);  // bits l..h of a byte
+        const uint64_t y = (h[1] == 7 ? ~0ull : (1ull << (8 * (h[1] + 1))) - 1ull) & ~((1ull << (8 * l[1])) - 1ull);
+        const uint64_t m = (z * 0x0101010101010101ull) & y;
+        uint64_t any = 0ull;
+        for (int x = l[0]; x <= h[0]; ++x) any |= ((uint64_t)occ[2 * x + 1] << 32 | occ[2 * x]) & m;
+        return any == 0ull;
+    };
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        if ((v[i] >> 2) != 0) continue;
+        const int up = v[i] & 3, w = (1 << up) - 1;
+        int lo[3], hi[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            lo[k] = cx[i][k] & ~w;
+            hi[k] = cx[i][k] | w;
+        }
+        grow_box(lo, hi, 8, 8, empty);
+        B[i * 64 + lane] = index_entry_box(cx[i], lo, hi, up);
+    }
+}
+
+// One thread per grid cell: descends the host's nodes to the cell's leaf,
+// empty cube, brick or level-G node.  A leaf entry of the nodes there is
+// -(number in the coarse table) - 1.  Empty cells get their octree cube only.
+__global__ __launch_bounds__(256) void k_index_grid(const int32_t* __restrict__ nodes, int n_top, int G,
+                                                    int32_t* __restrict__ grid) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i >= (1u << (3 * G))) return;
+    const int c[3] = {(int)(i >> (2 * G)), (int)(i >> G) & ((1 << G) - 1), (int)i & ((1 << G) - 1)};
+    int32_t e = 0;
+    int L = 0;  // e: node of level L holding the cell
+    do {
+        e = nodes[(size_t)e * 8 + child_slot(c, G, L)];
+        ++L;
+    } while (L < G && e > 0 && e < n_top);
+    if (e < 0)
+        e = kIdxCoarse | (-e - 1);
+    else if (e == 0)
+        e = index_entry_box(c, c, c, G - L);
+    else if (e >= n_top)
+        e -= n_top;  // a brick: G == M
+    grid[i] = e;
+}
+
+// Summed-area table of the grid's occupancy, one axis per launch (axis 2
+// reads the grid): one thread per line of n = 2^G cells.
+__global__ __launch_bounds__(256) void k_index_sums(const int32_t* __restrict__ grid, int32_t* __restrict__ sat, int G,
+                                                    int axis) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    const uint32_t n = 1u << G;
+    if (i >= n * n) return;
+    const uint32_t a = i >> G, b = i & (n - 1);
+    const uint32_t base = axis == 2 ? (a << G | b) << G : axis == 1 ? (a << (2 * G) | b) : i;
+    const uint32_t step = axis == 2 ? 1u : axis == 1 ? n : n * n;
+    int32_t sum = 0;
+    for (uint32_t q = 0; q < n; ++q) {
+        const uint32_t at = base + q * step;
+        sum += axis == 2 ? (grid[at] < 0 ? 0 : 1) : sat[at];
+        sat[at] = sum;
+    }
+}
+
+// One thread per grid cell: the empty box of an empty cell, in grid cells.
+__global__ __launch_bounds__(256) void k_index_grid_boxes(const int32_t* __restrict__ sat, int G,
+                                                          int32_t* __restrict__ grid) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i >= (1u << (3 * G))) return;
+    const int32_t e = grid[i];
+    if (e >= 0) return;
+    const int n = 1 << G;
+    const int c[3] = {(int)(i >> (2 * G)), (int)(i >> G) & (n - 1), (int)i & (n - 1)};
+    const int up = (e >> kIdxUpShift) & 15, w = (1 << up) - 1;
+    auto S = [&](int x, int y, int z) {  // cells occupied in [0, x] x [0, y] x [0, z]
+        return x < 0 || y < 0 || z < 0 ? 0 : sat[((((uint32_t)x << G) | (uint32_t)y) << G) | (uint32_t)z];
+    };
+    auto empty = [&](const int (&l)[3], const int (&h)[3]) {
+        const int a = l[0] - 1, b = l[1] - 1, d = l[2] - 1;
+        return S(h[0], h[1], h[2]) - S(a, h[1], h[2]) - S(h[0], b, h[2]) - S(h[0], h[1], d) + S(a, b, h[2]) +
+                   S(a, h[1], d) + S(h[0], b, d) - S(a, b, d) ==
+               0;
+    };
+    int lo[3], hi[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        lo[k] = c[k] & ~w;
+        hi[k] = c[k] | w;
+    }
+    grow_box(lo, hi, n, 15, empty);
+    grid[i] = index_entry_box(c, lo, hi, up);
+}
+#endif
+
 // Plain SGD on the leaf values (Sec. 4.3): p -= lr g, optionally clearing g.
 __global__ __launch_bounds__(256) void k_sgd(int64_t n, float* __restrict__ p, float* __restrict__ g, float lr,
                                              int zero_grad) {
@@ -2142,8 +2393,11 @@ inline int64_t grid_for(int64_t n_blocks) { return 8 * ((n_blocks + 7) / 8); }
 // Grid of xcd_interleave over n_blocks logical workgroups in runs of chunk.
 inline int64_t rows_grid(int64_t n_blocks, int64_t chunk) { return 8 * chunk * (((n_blocks + chunk - 1) / chunk + 7) / 8); }
 
-// Dynamic LDS of the node stack: one int per lane and tree level.
-inline size_t stack_bytes(int depth) { return sizeof(int) * kBlock * (size_t)depth; }
+// Dynamic LDS of the node stack: one int per lane and tree level.  Trees whose
+// grid reaches the brick level keep no node path.
+inline size_t stack_bytes(const KTree& t) {
+    return t.grid_level > 0 && t.grid_level == t.brick_level ? 0 : sizeof(int) * kBlock * (size_t)t.depth;
+}
 
 // Record-load plan: "fast" loads the padded record with the widest vectors,
 // "generic" uses dword loads of exactly the record (rounded to whole dwords).
@@ -2182,7 +2436,7 @@ hipError_t rays_t(const po_tree* t, int64_t n, const float* o, const float* d, c
     using P = Plan<T, K>;
     const int64_t nb = (n + kBlock - 1) / kBlock;
     dim3 grid((unsigned)grid_for(nb)), block(kBlock);
-    const size_t lds = stack_bytes(t->kt.depth);
+    const size_t lds = stack_bytes(t->kt);
     const bool fast = use_fast<T, K>(t);
     const int v = po_fwd_variant(op, aux, t->kt);
     if (v != PO_FWD_VIEW) aux = nullptr;
@@ -2225,11 +2479,10 @@ hipError_t camera_t(const po_tree* t, int n_jobs, KJob* jobs, int n_blocks, int 
     for (int j = n_jobs; j < MAXJ; ++j) B.job[j] = jobs[0];
     B.n_jobs = n_jobs;
     B.n_blocks = n_blocks;
-    int depth = 1;
-    for (int j = 0; j < n_jobs; ++j) depth = max(depth, jobs[j].tr.depth);
+    size_t lds = 0;
+    for (int j = 0; j < n_jobs; ++j) lds = std::max(lds, stack_bytes(jobs[j].tr));
     dim3 grid((unsigned)(MAXJ == 1 ? rows_grid(n_blocks, 4 * (int64_t)jobs[0].tiles_x) : grid_for(n_blocks))),
         block(kBlock);
-    const size_t lds = stack_bytes(depth);
     if constexpr (std::is_same_v<T, __half>) {
         if (variant == PO_FWD_CB) {
             using Q = CbPlan<K>;
@@ -2272,7 +2525,7 @@ hipError_t split_t(const po_tree* t, const KJob& job, int n_blocks, int variant,
     // camera: tile rows dealt over the XCDs (xcd_interleave)
     const int64_t g1n = SRC == 0 ? rows_grid(n_blocks, 4 * (int64_t)job.tiles_x) : grid_for(n_blocks);
     dim3 g1((unsigned)g1n), g2((unsigned)(kSplitRegions * (S.region_slots / kBlock))), blk(kBlock);
-    const size_t lds = stack_bytes(job.tr.depth);
+    const size_t lds = stack_bytes(job.tr);
     const bool fast = use_fast<T, K>(t);
 #define PO_SPLIT(VEC_, NL_, V_)                                                                        \
     do {                                                                                              \
@@ -2331,11 +2584,11 @@ hipError_t backward_split_t(const po_tree* t, int64_t n, const float* o, const f
     S.n_rays = n;
     // the pieces of the render of the same rays (before the grids: they
     // cover the queue regions as this pass lays them out)
-    po_rays_piece_sizes(n, &S);
+    po_rays_piece_sizes(n, t->kt.depth, (op.flags & kOptExact) != 0u, &S);
     hipLaunchKernelGGL(k_zero_i32, dim3(2), dim3(kSplitRegions), 0, s, S.count, 2 * kSplitRegions);
     dim3 g1((unsigned)grid_for(B.n_blocks)), g2((unsigned)(kSplitRegions * (S.region_slots / kBlock))),
         g3(2u * g2.x), blk(kBlock);
-    const size_t lds = stack_bytes(t->kt.depth);
+    const size_t lds = stack_bytes(t->kt);
     const bool sg = t->kt.lobes != nullptr;
 #define PO_BSPLIT(VEC_, NL_)                                                                                    \
     do {                                                                                                       \
@@ -2378,10 +2631,10 @@ hipError_t backward_kept_t(const po_tree* t, int64_t n, const float* o, const fl
     S.ray_o = o;
     S.ray_d = d;
     S.n_rays = n;
-    po_rays_piece_sizes(n, &S);
+    po_rays_piece_sizes(n, t->kt.depth, (op.flags & kOptExact) != 0u, &S);
     dim3 g1((unsigned)grid_for(B.n_blocks)), g3(2u * (unsigned)(kSplitRegions * (S.region_slots / kBlock))),
         blk(kBlock);
-    const size_t lds = stack_bytes(t->kt.depth);
+    const size_t lds = stack_bytes(t->kt);
 #define PO_BKEPT(VEC_, NL_)                                                                                       \
     do {                                                                                                         \
         hipLaunchKernelGGL((k_backward_first_kept<K, VEC_, NL_>), g1, blk, lds, s, B, S, rgb_fwd, grad, gsig,    \
@@ -2403,10 +2656,10 @@ hipError_t backward_t(const po_tree* t, int64_t n, const float* o, const float* 
     const int64_t nb = (n + kBlock - 1) / kBlock;
     dim3 grid((unsigned)grid_for(nb)), block(kBlock);
     if (use_fast<float, K>(t))
-        hipLaunchKernelGGL((k_backward<K, P::FAST_VEC, P::FAST_NL>), grid, block, stack_bytes(t->kt.depth), s,
+        hipLaunchKernelGGL((k_backward<K, P::FAST_VEC, P::FAST_NL>), grid, block, stack_bytes(t->kt), s,
                            t->kt, n, nb, o, d, op, rgb_fwd, grad, gsig, gsh);
     else
-        hipLaunchKernelGGL((k_backward<K, 4, P::GEN_NL>), grid, block, stack_bytes(t->kt.depth), s, t->kt, n, nb,
+        hipLaunchKernelGGL((k_backward<K, 4, P::GEN_NL>), grid, block, stack_bytes(t->kt), s, t->kt, n, nb,
                            o, d, op, rgb_fwd, grad, gsig, gsh);
     return hipGetLastError();
 }
@@ -2566,7 +2819,7 @@ hipError_t po_launch_rays_split(const po_tree* t, int64_t n, const float* o, con
     // first walk and smaller pieces (65536 random rays of the depth-8
     // training tree: 203 us with 8-cell pieces, 325 us with the frame's 32,
     // 300 us in one pass)
-    po_rays_piece_sizes(n, &S);
+    po_rays_piece_sizes(n, t->kt.depth, (op.flags & kOptExact) != 0u, &S);
     const int n_blocks = (int)((n + kBlock - 1) / kBlock);
     const int variant = po_fwd_variant(op, aux, t->kt);
     return t->desc.dtype == PO_F32 ? po_rays_split_f32(t, job, n_blocks, variant, S, s)
@@ -2578,11 +2831,24 @@ hipError_t po_launch_backward(const po_tree* t, int64_t n, const float* o, const
     PO_DISPATCH_K(t->K, (backward_t<KK>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, s)));
 }
 
+hipError_t po_launch_index(const int32_t* nodes, int n_top, int G, int64_t n_bricks, int32_t* grid,
+                           int32_t* bricks, int32_t* sat, hipStream_t s) {
+    if (n_bricks > 0) hipLaunchKernelGGL(k_index_bricks, dim3((unsigned)n_bricks), dim3(kBlock), 0, s, bricks);
+    if (G > 0) {
+        const unsigned cells = ((1u << (3 * G)) + 255u) / 256u, lines = ((1u << (2 * G)) + 255u) / 256u;
+        hipLaunchKernelGGL(k_index_grid, dim3(cells), dim3(256), 0, s, nodes, n_top, G, grid);
+        for (int axis = 2; axis >= 0; --axis)
+            hipLaunchKernelGGL(k_index_sums, dim3(lines), dim3(256), 0, s, grid, sat, G, axis);
+        hipLaunchKernelGGL(k_index_grid_boxes, dim3(cells), dim3(256), 0, s, sat, G, grid);
+    }
+    return hipGetLastError();
+}
+
 hipError_t po_launch_leaf_weights(const po_tree* t, const KCam& cam, const KOpts& op, int mode, float* weight,
                                   float* alpha, hipStream_t s) {
     const int n_blocks = 4 * ((cam.W + 15) / 16) * ((cam.H + 15) / 16);
     dim3 grid((unsigned)rows_grid(n_blocks, 4 * (int64_t)((cam.W + 15) / 16))), block(kBlock);
-    const size_t lds = stack_bytes(t->kt.depth);
+    const size_t lds = stack_bytes(t->kt);
     unsigned* wt = reinterpret_cast<unsigned*>(weight);
     if (t->desc.dtype == PO_F32) {
         if (mode == 0)
@@ -2610,7 +2876,7 @@ hipError_t po_traversal_stats_sync(const po_tree* t, const KCam* cam, int64_t n,
     if (cam) c = *cam;
     const int n_blocks = cam ? 4 * ((c.W + 15) / 16) * ((c.H + 15) / 16) : (int)((n + kBlock - 1) / kBlock);
     dim3 grid((unsigned)grid_for(n_blocks)), block(kBlock);
-    const size_t lds = stack_bytes(t->kt.depth);
+    const size_t lds = stack_bytes(t->kt);
     const bool f32 = t->desc.dtype == PO_F32;
     if (cam && f32)
         hipLaunchKernelGGL((k_traversal_stats<float, 0>), grid, block, lds, s, t->kt, c, o, d, n, op, n_blocks, d_sums);
