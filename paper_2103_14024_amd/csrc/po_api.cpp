@@ -523,12 +523,10 @@ static po_status bind_impl(const po_tree_desc* desc, int64_t n_nodes, const int3
         k.lobes = d_lobes;
     k.cb_entries = cb ? cb_entries : 0;
     k.n_top = (int32_t)n_nodes;
-    k.brick_level = (int8_t)desc->depth;  // no bricks and no grid until po_tree_build_index
-    k.grid_level = 0;
+    k.set_levels(desc->depth, desc->depth, 0, false);  // no bricks and no grid until po_tree_build_index
     k.index_bytes = (uint32_t)(n_nodes * 32);
     k.n_leaves = (int32_t)n_leaves;
     k.stride = t->stride;
-    k.depth = (int8_t)desc->depth;
     k.sigma_bytes = (uint32_t)(n_leaves * es);
     k.sh_bytes = (uint32_t)(n_leaves * (int64_t)t->stride * es);
     for (int a = 0; a < 3; ++a) k.lo[a] = (double)desc->center[a] - (double)desc->half_size;
@@ -727,7 +725,7 @@ po_status po_tree_build_index(po_tree* t, void* stream) {
     put(d + grid_bytes + kept_nodes, index.data() + n_top * 8, brick_bytes);
     put(d + grid_bytes + kept_nodes + brick_bytes, coarse.data(), coarse.size() * 4);
     if (e == hipSuccess)
-        e = po_launch_index(reinterpret_cast<const int32_t*>(tmp), (int)n_top, G, n_bricks,
+        e = po_launch_index(reinterpret_cast<const int32_t*>(tmp), (int)n_top, G, D - G, n_bricks,
                             reinterpret_cast<int32_t*>(d), reinterpret_cast<int32_t*>(d + grid_bytes + kept_nodes),
                             reinterpret_cast<int32_t*>(tmp + node_bytes), s);
     const hipError_t es = hipStreamSynchronize(s);
@@ -742,8 +740,7 @@ po_status po_tree_build_index(po_tree* t, void* stream) {
     t->n_bricks = n_bricks;
     t->kt.child = reinterpret_cast<const int32_t*>(d);
     t->kt.n_top = G == M ? 0 : (int32_t)n_top;
-    t->kt.brick_level = (int8_t)M;
-    t->kt.grid_level = (int8_t)G;
+    t->kt.set_levels(D, M, G, !coarse.empty());
     t->kt.index_bytes = (uint32_t)bytes;
     return ok();
 }

@@ -21,18 +21,18 @@ struct KTree {
     //           renumbered; an entry of a level-brick_level cell >= n_top
     //           names brick (entry - n_top).  n_top is 0 where the grid
     //           reaches brick_level
-    //   bricks  [n_bricks][512], 8x8x8 finest cells per internal node of level
-    //           brick_level, indexed by the child slots of the three levels
-    //           below the brick's cube (slot1 << 6 | slot2 << 3 | slot3)
+    //   bricks  [n_bricks][8][8][8], the finest cells (x, y, z) below each
+    //           internal node of level brick_level
     //   coarse  leaves of level <= grid_level, {leaf, level}, from the end of
     //           the buffer backwards
     // A grid entry is an empty entry (< 0), kIdxCoarse | number of a coarse
     // leaf, or the brick (grid_level == brick_level) or node below the cell.  A
     // brick entry is ((leaf + 1) << 2) | (D - level) of the leaf holding the
-    // cell, or an empty entry.  An empty entry is bit 31, the levels from its
-    // cell up to the octree's empty cube in bits kIdxUpShift.. (4 bits), and
-    // an empty box around the cell: cells to spare below and above it on
-    // axis k, 0..15 each, in bits 8k..8k+3 and 8k+4..8k+7.
+    // cell, or an empty entry.  An empty entry is bit 31, log2 of its own
+    // cell's edge in bits kIdxUnitShift.. (3 bits), the levels from its cell up
+    // to the octree's empty cube in bits kIdxUpShift.. (4 bits), and an empty
+    // box around the cell: cells to spare below and above it on axis k, 0..15
+    // each, in bits 8k..8k+3 and 8k+4..8k+7.
     const int32_t* child;
     const void* sigma;      // [n_leaves] float or half
     const void* sh;         // [n_leaves][stride] float or half
@@ -43,21 +43,37 @@ struct KTree {
     int32_t n_top;          // nodes in `child` (all of the caller's nodes when brick_level == depth)
     int32_t n_leaves;
     int32_t stride;         // elements per SH record
-    int8_t depth;           // D
-    int8_t brick_level;     // M: cells below level M are resolved by bricks; M == D: no bricks
-    int8_t grid_level;      // G: cells of levels <= G are resolved by the grid; 0: no grid
-    int8_t pad_;
+    // depth D, brick_level M (cells below level M are resolved by bricks; M ==
+    // D: no bricks), grid_level G (cells of levels <= G are resolved by the
+    // grid; 0: no grid) and whether the grid names leaves, a byte each (one
+    // word, because scalar loads are of words: as int8_t members a batch's
+    // kernel read them through the vector memory in every step)
+    uint32_t levels;
     uint32_t index_bytes;   // bytes readable through `child`
     int32_t cb_entries;     // codebook entries per basis function (0: no codebook)
     uint32_t sigma_bytes;   // n_leaves * element size (< 2^32)
     uint32_t sh_bytes;      // n_leaves * stride * element size (< 2^32 - 256)
     double lo[3];           // box minimum corner, world units
     double scale;           // grid units (finest cells) per world unit: 2^D / (2 half)
+
+#ifdef __HIPCC__
+#define PO_HD __host__ __device__
+#else
+#define PO_HD
+#endif
+    PO_HD int depth() const { return (int)(levels & 255u); }
+    PO_HD int brick_level() const { return (int)(levels >> 8 & 255u); }
+    PO_HD int grid_level() const { return (int)(levels >> 16 & 255u); }
+    PO_HD bool has_coarse() const { return (levels >> 24) != 0u; }
+    void set_levels(int D, int M, int G, bool coarse) {
+        levels = (uint32_t)D | (uint32_t)M << 8 | (uint32_t)G << 16 | (coarse ? 1u << 24 : 0u);
+    }
 };
 
 // Traversal index encoding (KTree::child).
 constexpr int kIdxCoarse = 1 << 30;
 constexpr int kIdxUpShift = 24;
+constexpr int kIdxUnitShift = 28;
 // Finest grid of an index: 8^8 entries, 64 MB.
 constexpr int kIdxMaxGrid = 8;
 
@@ -278,7 +294,7 @@ hipError_t po_launch_backward_kept(const po_tree* t, int64_t n, const float* o, 
 // Adds to an index the boxes of its n_bricks bricks (bricks of the host's
 // layout, changed in place) and, for G > 0, the grid with its boxes, from the
 // host's nodes (device copy); sat: 8^G words of scratch.
-hipError_t po_launch_index(const int32_t* nodes, int n_top, int G, int64_t n_bricks, int32_t* grid,
+hipError_t po_launch_index(const int32_t* nodes, int n_top, int G, int unit, int64_t n_bricks, int32_t* grid,
                            int32_t* bricks, int32_t* sat, hipStream_t s);
 hipError_t po_launch_camera_rays(const KCam& cam, float* o, float* d, hipStream_t s);
 // Visibility filter: mode 0 alpha, 1 contribution; weight[n_leaves] raised in place, alpha[H*W] or nullptr.

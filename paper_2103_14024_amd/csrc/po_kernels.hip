@@ -136,9 +136,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_rsrc(const void* base, uin
 // ---------------------------------------------------------------------------
 // Leaf record access.  T is float or __half; values are widened to float.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float load_sigma(const float* p, int i) { return p[i]; }
-__device__ __forceinline__ float load_sigma(const __half* p, int i) { return __half2float(p[i]); }
-
 // Number of 32-bit words holding NL elements of type T.
 template <typename T, int NL>
 struct Words {
@@ -146,74 +143,19 @@ struct Words {
     static constexpr int N = (NB + 3) / 4;
 };
 
-// Loads NL elements of one SH record at `base` as raw 32-bit words using
-// VEC-byte loads (16, 8 or 4; `base` is VEC-aligned), then dword loads and,
-// for an odd number of halves, one 2-byte load.  The host guarantees the NL
-// elements lie inside the record (NL <= stride).  The loads are only issued
-// here; the words are consumed later, so their latency can overlap other work.
-template <typename T, int NL, int VEC>
-__device__ __forceinline__ void load_words(const char* __restrict__ base, uint32_t (&w)[Words<T, NL>::N]) {
-    constexpr int NB = Words<T, NL>::NB;
-    constexpr int NV = NB / VEC;
-    constexpr int DONE = NV * VEC / 4;
-    constexpr int FULLW = NB / 4;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        if constexpr (VEC == 16) {
-            const uint4 q = *reinterpret_cast<const uint4*>(base + 16 * v);
-            w[4 * v + 0] = q.x;
-            w[4 * v + 1] = q.y;
-            w[4 * v + 2] = q.z;
-            w[4 * v + 3] = q.w;
-        } else if constexpr (VEC == 8) {
-            const uint2 q = *reinterpret_cast<const uint2*>(base + 8 * v);
-            w[2 * v + 0] = q.x;
-            w[2 * v + 1] = q.y;
-        } else {
-            w[v] = *reinterpret_cast<const uint32_t*>(base + 4 * v);
-        }
-    }
-#pragma unroll
-    for (int i = DONE; i < FULLW; ++i) w[i] = *reinterpret_cast<const uint32_t*>(base + 4 * i);
-    if constexpr (NB % 4 != 0) w[FULLW] = *reinterpret_cast<const uint16_t*>(base + 4 * FULLW);
+// A density as it lies in memory; sigma_of widens it.  (Two steps, so that a
+// float16 density is not waited for where its load is issued.)
+__device__ __forceinline__ uint32_t sigma_buf(__amdgpu_buffer_rsrc_t rs, uint32_t off, float*) {
+    return __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
 }
-
-// Same as load_words, through a raw buffer descriptor at byte offset `off`.
-// An offset at or beyond the end of the buffer returns zeros and touches no
-// memory, which lets lanes without a sample run the same straight-line code.
-template <typename T, int NL, int VEC>
-__device__ __forceinline__ void load_words_buf(__amdgpu_buffer_rsrc_t rs, uint32_t off,
-                                               uint32_t (&w)[Words<T, NL>::N]) {
-    constexpr int NB = Words<T, NL>::NB;
-    constexpr int NV = NB / VEC;
-    constexpr int DONE = NV * VEC / 4;
-    constexpr int FULLW = NB / 4;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        if constexpr (VEC == 16) {
-            const auto q = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * v, 0, 0);
-            w[4 * v + 0] = q[0];
-            w[4 * v + 1] = q[1];
-            w[4 * v + 2] = q[2];
-            w[4 * v + 3] = q[3];
-        } else if constexpr (VEC == 8) {
-            const auto q = __builtin_amdgcn_raw_buffer_load_b64(rs, off + 8 * v, 0, 0);
-            w[2 * v + 0] = q[0];
-            w[2 * v + 1] = q[1];
-        } else {
-            w[v] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * v, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int i = DONE; i < FULLW; ++i) w[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * i, 0, 0);
-    if constexpr (NB % 4 != 0) w[FULLW] = __builtin_amdgcn_raw_buffer_load_b16(rs, off + 4 * FULLW, 0, 0);
+__device__ __forceinline__ uint32_t sigma_buf(__amdgpu_buffer_rsrc_t rs, uint32_t off, __half*) {
+    return __builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0);
 }
-
-__device__ __forceinline__ float sigma_buf(__amdgpu_buffer_rsrc_t rs, uint32_t off, float*) {
-    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
-}
-__device__ __forceinline__ float sigma_buf(__amdgpu_buffer_rsrc_t rs, uint32_t off, __half*) {
-    return __half2float(__ushort_as_half(__builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0)));
+template <typename T>
+__device__ __forceinline__ float sigma_of(uint32_t raw) {
+    if constexpr (sizeof(T) == 4) return __uint_as_float(raw);
+    asm volatile("" : "+v"(raw));  // (the conversion stays here)
+    return __half2float(__ushort_as_half((unsigned short)raw));
 }
 
 // Element i of a record held as raw words, widened to float.
@@ -242,18 +184,30 @@ __device__ __forceinline__ float sigmoid(float z) { return __builtin_amdgcn_rcpf
 // that exceeds 1e-4 in colour.  Leaf values, SH and compositing stay FP32.
 // A segment's length in world units is (s_exit - s_entry) * |d|.
 // ---------------------------------------------------------------------------
+//
+// Cell coordinates are kept mirrored (x -> 2^D - 1 - x) on the axes along which
+// the ray runs downwards, so that every step goes up and needs no case for its
+// sign; positions and parameters are the tree's own.
 struct Ray {
     double og[3];  // origin, grid units
     double dg[3];  // direction (caller's length), grid units per unit of s
     double inv[3]; // 1 / dg
     double len;    // |d| in world units
     float dn[3];   // unit direction, world (SH argument)
-    int c[3];      // finest-level coordinates of the current cell
+    int c[3];      // finest-level coordinates of the current cell, mirrored
     double s;      // current parameter
     double s_end;  // end of the rendered part (slicing plane), else 1e300
     double s_exit; // end of the walk: min(s_end, box exit)
     bool more;     // split walks: the walk stopped at its sample limit with cells left
     int nt;        // split walks: samples taken (exact: cells walked)
+
+    // c ^ flip is the tree's coordinate (recomputed where it is needed: kept,
+    // the three would cost a wave per SIMD)
+    __device__ __forceinline__ int flip(int k, int N) const { return dg[k] > 0.0 ? 0 : N - 1; }
+    // Mirrored coordinate of the cell holding the point at parameter s.
+    __device__ __forceinline__ int cell_at(double s, int k, int N) const {
+        return (int)fmin(fmax(floor(fma(s, dg[k], og[k])), 0.0), (double)(N - 1)) ^ flip(k, N);
+    }
 };
 
 // The walk covers the parameters s in [max(s_lo, 0), s_hi] inside the box.
@@ -265,7 +219,7 @@ __device__ __forceinline__ bool ray_setup(const KTree& tr, const double (&o)[3],
     const double il = 1.0 / r.len;
 #pragma unroll
     for (int k = 0; k < 3; ++k) r.dn[k] = (float)(d[k] * il);
-    const double N = (double)(1 << tr.depth);
+    const int N = 1 << tr.depth();
     double s0 = fmax(s_lo, 0.0), s1 = s_hi;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -279,16 +233,13 @@ __device__ __forceinline__ bool ray_setup(const KTree& tr, const double (&o)[3],
         r.dg[k] = (g == 0.0) ? 1e-300 : g;
         r.inv[k] = 1.0 / r.dg[k];
         const double ta = (0.0 - r.og[k]) * r.inv[k];
-        const double tb = (N - r.og[k]) * r.inv[k];
+        const double tb = ((double)N - r.og[k]) * r.inv[k];
         s0 = fmax(s0, fmin(ta, tb));
         s1 = fmin(s1, fmax(ta, tb));
     }
     if (!(s1 > s0)) return false;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const double p = fma(s0, r.dg[k], r.og[k]);
-        r.c[k] = (int)fmin(fmax(floor(p), 0.0), N - 1.0);
-    }
+    for (int k = 0; k < 3; ++k) r.c[k] = r.cell_at(s0, k, N);
     r.s = s0;
     r.s_end = s_hi;
     r.s_exit = s1;
@@ -309,7 +260,8 @@ __device__ __forceinline__ void clip_range(const KOpts& op, const double (&o)[3]
     s_hi = pd < 0.0 ? t : 1e300;
 }
 
-// Child slot of cell c below a node of level L (bits D-1-L of the coordinates).
+// Child slot of cell c (the tree's coordinates) below a node of level L (bits
+// D-1-L of the coordinates).
 __device__ __forceinline__ uint32_t child_slot(const int (&c)[3], int D, int L) {
     const int sft = D - 1 - L;
     return (uint32_t)((((c[0] >> sft) & 1) << 2) | (((c[1] >> sft) & 1) << 1) | ((c[2] >> sft) & 1));
@@ -321,23 +273,13 @@ constexpr int kNoCap = 0x7fffffff;
 // report or cap their number (see kOptExact).
 __device__ __forceinline__ bool exact_cells(const KOpts& op) { return (op.flags & kOptExact) != 0u; }
 
-// Walks the segments of a ray.  Data leaves crossed over a positive length
-// go through a two-stage sampler: smp.issue(leaf, delta, t) starts the loads
-// of the leaf's density and SH record (leaf -1: a lane without a sample,
-// which loads nothing; t is the segment's start distance from the origin),
-// and smp.consume() shades and composites the sample one step later and
-// returns true to stop the walk; smp.flush() then runs with every lane still
-// walking.  A sampler with kClip set also ends the walk at r.s_end.  The samples, their order and the
-// stop point are those of the plain front-to-back walk.  Returns the number
-// of cells visited.
+// The walk of one ray through the cells of the tree.
 //
-// Per step: resolve the entry of cell c (a leaf, or empty space); compute the
-// exit parameter and the next cell; prefetch the next cell's entry; composite
-// the previous sample; start this cell's gather.  Loads complete in issue
-// order, so the next step waits only for its own entry and not for the
-// gather, and compositing runs while that entry is in flight.
+// A step resolves the entry of cell c (a leaf, or empty space), computes the
+// parameter at which the ray leaves the cell, moves the coordinates across the
+// exit face and starts the read of the next cell's entry.
 //
-// Entries.  With a grid (tr.grid_level G > 0) the level-G cell holding c is
+// Entries.  With a grid (tr.grid_level() G > 0) the level-G cell holding c is
 // one read, and the 8x8x8 brick below it another, whatever the cell crossed
 // before: no node path is kept.  An empty entry names the box of empty space
 // around its cell, so that one step crosses it whole (see index_entry_box);
@@ -357,167 +299,229 @@ __device__ __forceinline__ bool exact_cells(const KOpts& op) { return (op.flags 
 // a buffer descriptor: an entry beyond it reads as 0 (empty), and an internal
 // entry below depth D or past the node count is counted as malformed and
 // taken as empty.
-//
-// SPLIT: reaching `cap` data samples (exact: cells) with cells left stops the
-// walk; it leaves r.s and r.c at the start of the next cell and sets r.more
-// (unless the last sample ended it by early stopping), so that it can be
-// resumed or handed on.  (Samples, so that the hand-off does not depend on how
-// empty space is crossed.)  So does reaching max_steps, which without SPLIT is
-// an error.  A chunk sampler (kChunk) learns for every sample
-// whether its cell ends inside the walked range (cpl_next) or is cut by
-// r.s_end.
-template <class S, class = void>
-struct is_chunk : std::false_type {};
-template <class S>
-struct is_chunk<S, std::void_t<decltype(S::kChunk)>> : std::bool_constant<S::kChunk> {};
-// A sampler with kCountLoads set (po_traversal_stats) walks the octree's own
-// cells and counts the child and brick entries that a descent from the
-// deepest common ancestor reads for each of them (member `loads`).
-template <class S, class = void>
-struct counts_loads : std::false_type {};
-template <class S>
-struct counts_loads<S, std::void_t<decltype(S::kCountLoads)>> : std::bool_constant<S::kCountLoads> {};
 
-// Spreads the three low bits of b to bits 0, 3 and 6.
-__device__ __forceinline__ uint32_t spread3(uint32_t b) { return (b | (b << 2) | (b << 4)) & 0x49u; }
+// What one step crossed.
+struct Cell {
+    int leaf;     // data leaf, or -1: empty space
+    float delta;  // length of the segment, world units
+    float t_in;   // distance of its start from the ray origin
+    bool cpl;     // the cell ends inside the walked range (kClip)
+    bool last;    // the walk ends with this cell
+    int u;        // log2 of the edge of the cell's cube (without its empty box)
+};
 
-// Index of a finest cell in its 8x8x8 brick: the child slots of the three
-// levels below the brick's cube, slot1 << 6 | slot2 << 3 | slot3 (slot =
-// 4 x + 2 y + z of that level's coordinate bits).
-__device__ __forceinline__ uint32_t brick_cell(const int (&c)[3]) {
-    return (spread3((uint32_t)c[0] & 7u) << 2) | (spread3((uint32_t)c[1] & 7u) << 1) | spread3((uint32_t)c[2] & 7u);
+// What the walk needs of a tree, held in scalar registers while it runs (read
+// through the kernel arguments, the compiler fetched them anew in every step).
+__device__ __forceinline__ uint32_t held(uint32_t v) {
+    asm volatile("" : "+v"(v));
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
+__device__ __forceinline__ int held(int v) { return (int)held((uint32_t)v); }
+__device__ __forceinline__ const void* held(const void* p) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    return reinterpret_cast<const void*>((uint64_t)held((uint32_t)(a >> 32)) << 32 | held((uint32_t)a));
+}
+struct Index {
+    __amdgpu_buffer_rsrc_t rs;
+    uint32_t bytes, node0, brick0;  // end of the index; byte offsets of node 0 and brick 0
+    int D, M, G, q;                 // q = D - G
+    int top;                        // 2^D - 1
+    int n_top, n_leaves;
+    int direct, coarse;             // the grid reaches the bricks; it names leaves
 
-template <class Sampler, bool SPLIT = false>
-__device__ __forceinline__ int march(const KTree& tr, Ray& r, int max_steps, int cap, bool exact,
-                                     int* __restrict__ stk, Sampler& smp) {
-    const int D = tr.depth;
-    const int M = tr.brick_level;
-    const int G = tr.grid_level;
-    const int N = 1 << D;
-    const uint32_t idx_end = tr.index_bytes;
-    const __amdgpu_buffer_rsrc_t child = raw_rsrc(tr.child, idx_end);
-    const uint32_t node0 = G > 0 ? 4u << (3 * G) : 0u;          // byte offset of node 0
-    const uint32_t brick0 = node0 + (uint32_t)tr.n_top * 32u;   // and of brick 0
-    if constexpr (counts_loads<Sampler>::value) exact = true;
-    int steps = 0, nt = 0;
-    bool pending = false, bad = false, cap_end = false;
-    // L: level of the node whose entry e is (e describes a level-(L+1) cell);
-    // L < 0: e is the grid entry of c; inb: e is the brick entry of c
-    int L = 0, node = 0;
-    bool inb = false;
-    uint32_t bofs = 0;  // byte offset of the brick holding c (valid while inb)
-    auto grid_ofs = [&]() {
-        return (uint32_t)((((r.c[0] >> (D - G)) << G | (r.c[1] >> (D - G))) << G) | (r.c[2] >> (D - G))) << 2;
-    };
-    int e;
-    if (G > 0) {
-        L = -1;
-        e = __builtin_amdgcn_raw_buffer_load_b32(child, grid_ofs(), 0, 0);
-    } else {
-        stk[0] = 0;
-        e = __builtin_amdgcn_raw_buffer_load_b32(child, child_slot(r.c, D, 0) << 2, 0, 0);
+    __device__ __forceinline__ explicit Index(const KTree& tr) {
+        bytes = held(tr.index_bytes);
+        rs = raw_rsrc(held(static_cast<const void*>(tr.child)), bytes);
+        const uint32_t levels = held(tr.levels);
+        D = (int)(levels & 255u);
+        M = (int)(levels >> 8 & 255u);
+        G = held((int)(levels >> 16 & 255u));
+        q = held(D - G);
+        top = held((1 << D) - 1);
+        coarse = held((int)(levels >> 24));
+        direct = held((int)((G > 0) & (G == M)));
+        n_top = tr.n_top;
+        n_leaves = tr.n_leaves;
+        node0 = G > 0 ? 4u << (3 * G) : 0u;
+        brick0 = held(node0 + (uint32_t)n_top * 32u);
     }
-    [[maybe_unused]] int la0 = 0;        // counted descents: level they start from,
-    [[maybe_unused]] bool was_in = false;  // and whether the cell before lay in a brick
-    // an empty gather, so that every path into the loop has the same loads in
-    // flight behind the entry (the compiler then waits for the entry alone)
-    smp.issue(-1, 0.0f, 0.0f);
-    while (true) {
-        // resolve e: the leaf holding c (-1: empty), log2 of the edge of its
-        // cube, and for empty space how far the empty box reaches beyond it
-        int leaf = -1, u = 0;
-        uint32_t ext = 0;
+    __device__ __forceinline__ int entry(uint32_t at) const {
+        return __builtin_amdgcn_raw_buffer_load_b32(rs, at, 0, 0);
+    }
+    // The same, waited for at once: a load that only some lanes make is waited
+    // for where they make it.  (Left to its first use, the wait would stand in
+    // every lane's path and, loads returning in order, wait for the gather.)
+    __device__ __forceinline__ int entry_now(uint32_t at) const {
+        int e = entry(at);
+        asm volatile("" : "+v"(e));
+        return e;
+    }
+    // Byte offsets of the entries of cell c (the tree's coordinates): the grid's,
+    // a brick's ([x][y][z] of the low three bits), a node's.
+    __device__ __forceinline__ uint32_t grid_at(const int (&c)[3]) const {
+        return (uint32_t)((((c[0] >> q) << G | (c[1] >> q)) << G) | (c[2] >> q)) << 2;
+    }
+    static __device__ __forceinline__ uint32_t brick_at(uint32_t brick, const int (&c)[3]) {
+        return brick + ((uint32_t)(((c[0] & 7) << 6) | ((c[1] & 7) << 3) | (c[2] & 7)) << 2);
+    }
+    __device__ __forceinline__ uint32_t slot_at(const int (&c)[3], int node, int L) const {
+        return node0 + (((uint32_t)node << 5) | (child_slot(c, D, L) << 2));
+    }
+};
+
+// CLIP: the walk also ends at r.s_end.  CHUNK: r.s_end is a piece's end, and
+// cpl says whether the next piece starts outside this cell.
+//
+// A wave's time is the chain of its longest ray: about 350 instructions a step
+// (223 vector, 127 scalar) and one or two index reads kept the SIMDs' waves
+// issuing 25 % and waiting 75 % of their cycles, with 1.8 waves of 4 resident
+// on average.  So the step is kept short: mirrored axes, entries that carry
+// their own box, and a branch-free path for trees whose grid reaches the
+// bricks.
+template <bool CLIP, bool CHUNK>
+struct Walker {
+    int e;
+    int bad;        // met a malformed entry
+    bool inb;       // e is the brick entry of c
+    // inb: byte offset of the brick; else (as int) the level of the node whose
+    // entry e is, e describing a cell one level below, or -1: e is a grid entry
+    uint32_t bofs;
+
+    __device__ __forceinline__ void start(const Index& ix, const Ray& r, int* __restrict__ stk) {
+        inb = false;
+        bad = 0;
+        const int N = ix.top + 1;
+        const int c[3] = {r.c[0] ^ r.flip(0, N), r.c[1] ^ r.flip(1, N), r.c[2] ^ r.flip(2, N)};
+        if (ix.G > 0) {
+            bofs = 0xffffffffu;
+            e = ix.entry(ix.grid_at(c));
+        } else {
+            bofs = 0;
+            stk[0] = 0;
+            e = ix.entry(ix.slot_at(c, 0, 0));
+        }
+    }
+
+    // Resolves e, the entry of cell c: its leaf (-1: empty space), log2 of the
+    // edge u of its cube, and for empty space how far the box reaches beyond.
+    __device__ __forceinline__ void resolve(const Index& ix, const int (&c)[3], int* __restrict__ stk, bool exact,
+                                            int& leaf, int& u, uint32_t& ext) {
+        const int D = ix.D, M = ix.M, G = ix.G;
+        leaf = -1;
+        u = 0;
+        ext = 0;
+        bool boxed = inb;  // e is a brick or grid entry
         if (!inb) {
             bool descend = true;
+            int L = (int)bofs, node;
             if (L < 0) {
                 descend = false;
-                if (e < 0) {
-                    u = D - G;
-                    if (exact)
-                        u += (e >> kIdxUpShift) & 15;
-                    else
-                        ext = (uint32_t)e;
-                } else if (e & kIdxCoarse) {
-                    // a leaf of level <= G: its number and level in a side table
-                    const uint32_t at = idx_end - 8u - ((uint32_t)(e & (kIdxCoarse - 1)) << 3);
-                    const auto q = __builtin_amdgcn_raw_buffer_load_b64(child, at, 0, 0);
-                    leaf = (int)q[0];
-                    u = D - (int)q[1];
-                } else if (G == M) {
-                    bofs = brick0 + (uint32_t)e * 2048u;
-                    e = __builtin_amdgcn_raw_buffer_load_b32(child, bofs + (brick_cell(r.c) << 2), 0, 0);
-                    inb = true;
-                } else {
+                if ((uint32_t)e < (uint32_t)kIdxCoarse) {
                     L = G;
                     node = e;
                     stk[L * kBlock] = node;
-                    e = __builtin_amdgcn_raw_buffer_load_b32(
-                        child, node0 + (((uint32_t)node << 5) | (child_slot(r.c, D, L) << 2)), 0, 0);
+                    e = ix.entry_now(ix.slot_at(c, node, L));
                     descend = true;
+                } else {
+                    boxed = true;
                 }
             }
             if (descend) {
                 ++L;  // e is the entry of the level-L cell holding c
-                // further levels (each waits for its own load, and for any older one)
-                while ((e > 0) & (e < tr.n_top) & (L < M)) {
+                while ((e > 0) & (e < ix.n_top) & (L < M)) {
                     node = e;
                     stk[L * kBlock] = node;
-                    e = __builtin_amdgcn_raw_buffer_load_b32(
-                        child, node0 + (((uint32_t)node << 5) | (child_slot(r.c, D, L) << 2)), 0, 0);
+                    e = ix.entry_now(ix.slot_at(c, node, L));
                     ++L;
                 }
-                if ((e > 0) & (L == M) & (M < D) & (e >= tr.n_top)) {
+                if ((e > 0) & (L == M) & (M < D) & (e >= ix.n_top)) {
                     // the level-M cube holding c is a brick: one load gives the leaf
-                    bofs = brick0 + (uint32_t)(e - tr.n_top) * 2048u;
-                    e = __builtin_amdgcn_raw_buffer_load_b32(child, bofs + (brick_cell(r.c) << 2), 0, 0);
-                    inb = true;
+                    bofs = ix.brick0 + (uint32_t)(e - ix.n_top) * 2048u;
+                    e = ix.entry_now(ix.brick_at(bofs, c));
+                    inb = boxed = true;
                 } else {
                     // a leaf or empty cube of level L; any other positive entry
                     // (past the nodes, or internal at the deepest level) is malformed
-                    const bool malformed = e > 0;
-                    bad |= malformed;
-                    leaf = malformed ? -1 : -1 - e;
+                    if (e > 0) bad = 1;
+                    leaf = e > 0 ? -1 : -1 - e;
                     u = D - L;
                 }
             }
         }
-        if (inb) {
-            if (e < 0) {
-                if (exact)
-                    u = (e >> kIdxUpShift) & 15;
-                else
-                    ext = (uint32_t)e;
-            } else {
-                u = e & 3;
-                leaf = (int)((uint32_t)e >> 2) - 1;
-            }
-        }
-        if (leaf >= tr.n_leaves) {
-            bad = true;
+        if (boxed) decode(ix, exact, leaf, u, ext);
+        if (leaf >= ix.n_leaves) {
+            bad = 1;
             leaf = -1;
         }
-        if constexpr (counts_loads<Sampler>::value) {
-            const int lvl = D - u;
-            smp.loads += (was_in & (la0 >= M)) ? 1 : (lvl <= M ? lvl - la0 : M - la0 + 1);
-            was_in = lvl > M;
+    }
+    // A brick or grid entry.
+    __device__ __forceinline__ void decode(const Index& ix, bool exact, int& leaf, int& u, uint32_t& ext) const {
+        leaf = e < 0 ? -1 : (e >> 2) - 1;
+        u = e < 0 ? (int)(((uint32_t)e >> kIdxUnitShift) & 7u) : e & 3;
+        ext = e < 0 ? (uint32_t)e : 0u;
+        if (exact) {
+            u += e < 0 ? (e >> kIdxUpShift) & 15 : 0;
+            ext = 0;
         }
-        // exit parameter: the nearest far face (branch-free; pos = moving up the axis)
-        int far[3];
-        bool pos[3];
-        double sk[3];
+        if (ix.coarse) {
+            if (!inb & (e >= 0)) {
+                // a leaf of level <= G: its number and level in a side table
+                const uint32_t at = ix.bytes - 8u - ((uint32_t)(e & (kIdxCoarse - 1)) << 3);
+                const auto q = __builtin_amdgcn_raw_buffer_load_b64(ix.rs, at, 0, 0);
+                int l = (int)q[0], level = (int)q[1];
+                asm volatile("" : "+v"(l), "+v"(level));
+                leaf = l;
+                u = ix.D - level;
+            }
+        }
+    }
+
+    // One cell.  cell_cap: the walk ends with it whatever it is; smp_cap: it
+    // ends with it if it holds a sample.  At the end of the walk r.s and r.c
+    // are at the start of the next cell.
+    __device__ __forceinline__ Cell step(const Index& ix, Ray& r, bool exact, bool cell_cap, bool smp_cap,
+                                         int* __restrict__ stk) {
+        const int N = ix.top + 1;
+        Cell o;
+        // sign of the direction (0, or -1 on mirrored axes) and what follows
+        // from it are made anew in every step: kept, they would take registers
+        // that the records in flight need
+        int sg[3], flip[3], c[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            pos[k] = r.dg[k] > 0.0;
-            const int x = (int)((ext >> (8 * k + (pos[k] ? 4 : 0))) & 15u);
-            const int cu = r.c[k] >> u;
-            far[k] = (pos[k] ? cu + 1 + x : cu - x) << u;
-            sk[k] = ((double)far[k] - r.og[k]) * r.inv[k];
+            int hi = __double2hiint(r.dg[k]);
+            asm volatile("" : "+v"(hi));
+            sg[k] = hi >> 31;
+            flip[k] = sg[k] & ix.top;
+            c[k] = r.c[k] ^ flip[k];
+        }
+        int leaf, u;
+        uint32_t ext;
+        if (ix.direct) {
+            if (!inb & ((uint32_t)e < (uint32_t)kIdxCoarse)) {
+                bofs = ix.brick0 + (uint32_t)e * 2048u;
+                e = ix.entry_now(ix.brick_at(bofs, c));
+                inb = true;
+            }
+            decode(ix, exact, leaf, u, ext);
+        } else {
+            resolve(ix, c, stk, exact, leaf, u, ext);
+        }
+        // exit parameter: the nearest far face
+        int end[3];  // last cell of the box ahead
+        double sk[3];
+        const int w = (1 << u) - 1;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            end[k] = (((r.c[k] >> u) + (int)((ext >> (8 * k + 4 + (sg[k] & -4))) & 15u)) << u) | w;
+            // the face behind it: end + 1, or in the tree's coordinates on a
+            // mirrored axis 2^D - 1 - end
+            sk[k] = ((double)((end[k] ^ flip[k]) + 1 + sg[k]) - r.og[k]) * r.inv[k];
         }
         double se = fmax(fmin(fmin(sk[0], sk[1]), sk[2]), r.s);
-        bool cpl = true;
-        if constexpr (Sampler::kClip) {
-            if constexpr (is_chunk<Sampler>::value) {
+        o.cpl = true;
+        if constexpr (CLIP) {
+            if constexpr (CHUNK) {
                 // a piece's cell is cut when the next piece starts inside it;
                 // that piece finds its first cell from the point at s_end as
                 // ray_setup does, so the two agree on every cell (a cell
@@ -527,115 +531,328 @@ __device__ __forceinline__ int march(const KTree& tr, Ray& r, int max_steps, int
                     bool inside = true;
 #pragma unroll
                     for (int k = 0; k < 3; ++k) {
-                        const int q = (int)fmin(fmax(floor(fma(r.s_end, r.dg[k], r.og[k])), 0.0), (double)(N - 1));
-                        const int d = (q >> u) - (r.c[k] >> u);
+                        const int d = ((r.cell_at(r.s_end, k, N) ^ flip[k]) >> u) - (c[k] >> u);
                         inside &= (d <= (int)((ext >> (8 * k + 4)) & 15u)) & (-d <= (int)((ext >> (8 * k)) & 15u));
                     }
-                    cpl = !inside;
+                    o.cpl = !inside;
                 }
             } else {
-                cpl = se <= r.s_end;
+                o.cpl = se <= r.s_end;
             }
             se = fmin(se, r.s_end);
         }
-        const float delta = (float)((se - r.s) * r.len);
-        const float t_in = (float)(r.s * r.len);
-        const bool cand = (leaf >= 0) & (delta > 0.0f);
-        ++steps;
+        o.leaf = leaf;
+        o.u = u;
+        o.delta = (float)((se - r.s) * r.len);
+        o.t_in = (float)(r.s * r.len);
         // next cell: axes whose face is reached step to the neighbouring cell;
         // the others take the finest cell of the exit point, kept inside the
         // current box and never moving against the ray (truncation equals
-        // floor here: the result is clamped to >= 0)
-        bool out = false;
+        // floor here: the result is clamped)
         int nc[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const int q = (int)fma(se, r.dg[k], r.og[k]);
-            const int kept = pos[k] ? min(max(q, r.c[k]), far[k] - 1) : max(min(q, r.c[k]), far[k]);
-            const bool cross = sk[k] <= se;
-            const int stepped = pos[k] ? far[k] : far[k] - 1;
-            nc[k] = cross ? stepped : kept;
-            out |= cross & ((stepped < 0) | (stepped >= N));
+            int q = max((int)fma(se, r.dg[k], r.og[k]), 0) ^ flip[k];
+            asm volatile("" : "+v"(q));  // (or the compiler branches around it)
+            nc[k] = sk[k] <= se ? end[k] + 1 : max(min(q, end[k]), r.c[k]);
         }
-        if constexpr (Sampler::kClip) out |= se >= r.s_end;
+        bool out = ((nc[0] | nc[1] | nc[2]) & N) != 0;  // a coordinate of N: past the box
+        if constexpr (CLIP) out |= se >= r.s_end;
         r.s = se;
-        bool capped = !out & (steps >= max_steps);
-        if constexpr (!SPLIT) bad |= capped;
-        if constexpr (SPLIT) capped |= !out & (exact ? steps >= cap : cand & (nt + 1 >= cap));
-        const bool last = out | capped;
-        // prefetch the next cell's entry.  The cells agree on the coordinate
-        // bits above the highest differing one: inside the same brick the
-        // brick entry is read directly, else the grid's, or without a grid
-        // the walk restarts below the deepest common ancestor above the brick
-        // level (from the stack).  The load is issued on every path (out of
-        // range after the last step) so the compiler can count the loads in
-        // flight exactly.
-        uint32_t pf = idx_end;
-        if (!last) {
-            const int diff = (r.c[0] ^ nc[0]) | (r.c[1] ^ nc[1]) | (r.c[2] ^ nc[2]);
-            const int la = D - 32 + __clz(diff);
-            if constexpr (counts_loads<Sampler>::value) la0 = la;
-            r.c[0] = nc[0];
-            r.c[1] = nc[1];
-            r.c[2] = nc[2];
-            if (inb & (la >= M)) {
-                pf = bofs + (brick_cell(r.c) << 2);
-            } else {
-                inb = false;
-                if ((G > 0) & ((G == M) | (la < G))) {
-                    L = -1;
-                    pf = grid_ofs();
+        const bool capped = !out & (cell_cap | (smp_cap & (leaf >= 0) & (o.delta > 0.0f)));
+        r.more = capped;
+        o.last = out | capped;
+        const uint32_t diff = (uint32_t)((r.c[0] ^ nc[0]) | (r.c[1] ^ nc[1]) | (r.c[2] ^ nc[2]));
+        if (!out) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) r.c[k] = nc[k];
+        }
+        // read the next cell's entry (nothing after the last step: an offset
+        // past the index): inside the same brick the brick's, else the grid's
+        uint32_t at;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) c[k] = nc[k] ^ flip[k];
+        if (ix.direct) {
+            inb = inb & (diff < 8u);
+            at = inb ? ix.brick_at(bofs, c) : ix.grid_at(c);
+        } else {
+            // the cells agree on the coordinate bits above the highest
+            // differing one: without a grid the walk restarts below the deepest
+            // common ancestor above the brick level (from the stack)
+            const int D = ix.D, M = ix.M, G = ix.G;
+            const int la = D - 32 + __clz((int)diff);
+            at = 0;
+            if (!o.last) {
+                if (inb & (la >= M)) {
+                    at = ix.brick_at(bofs, c);
                 } else {
-                    L = la;
-                    node = stk[L * kBlock];
-                    pf = node0 + (((uint32_t)node << 5) | (child_slot(r.c, D, L) << 2));
+                    inb = false;
+                    if ((G > 0) & (la < G)) {
+                        bofs = 0xffffffffu;
+                        at = ix.grid_at(c);
+                    } else {
+                        bofs = (uint32_t)la;
+                        at = ix.slot_at(c, stk[la * kBlock], la);
+                    }
                 }
             }
         }
-        if constexpr (SPLIT) {
-            if (capped) {
-                r.c[0] = nc[0];
-                r.c[1] = nc[1];
-                r.c[2] = nc[2];
+        e = ix.entry(o.last ? ix.bytes : at);
+        return o;
+    }
+};
+
+// ---------------------------------------------------------------------------
+// Samples of a wave.  The data segments that its rays cross are collected in a
+// queue in LDS, in the order of the steps, and shaded 64 at a time, one per
+// lane whatever ray it belongs to; then every ray composites its own, front to
+// back.
+//
+// Why a queue.  What a sample's colour and opacity need (leaf, segment length,
+// the ray's basis values) does not depend on the samples in front of it.  Shaded
+// by its own ray's lane, at the step that met it, a gather ran with the 20-30
+// lanes of 64 that had a sample at that step, held the registers of all 64, and
+// delayed the walk: loads return in order, so the read of a cell's entry waited
+// for the gather before it.  Through the queue every gather and contraction
+// runs with all lanes, and the steps between two of them wait for nothing but
+// the index.
+// ---------------------------------------------------------------------------
+constexpr int kQueue = 2 * kBlock;  // up to 63 samples left over and 64 new ones
+struct Sample {
+    uint32_t leaf;
+    float delta;     // segment length, world units
+    uint32_t info;   // ray's lane | its cell is cut by the end of the walk << 6 | number of the step << 7
+    uint32_t next;   // slot of the same ray's next sample
+};
+__device__ __forceinline__ Sample* sample_queue() {
+    __shared__ __align__(16) Sample s_queue[kQueue];
+    return s_queue;
+}
+// Start distances of the queue's segments (viewer).
+__device__ __forceinline__ float* sample_starts() {
+    __shared__ float s_t[kQueue];
+    return s_t;
+}
+// Results of the 64 samples being shaded: {e^-(sigma delta), colour}, -1 for a
+// leaf without density; the viewer's depth terms.
+__device__ __forceinline__ float4* shaded() {
+    __shared__ __align__(16) float4 s_shaded[kBlock];
+    return s_shaded;
+}
+__device__ __forceinline__ float* shaded_depth() {
+    __shared__ float s_depth[kBlock];
+    return s_depth;
+}
+// Basis values of the wave's rays, [k / 4][lane][k % 4]: a lane reads its own in
+// (K + 3) / 4 wide loads without bank conflicts.  In LDS they cost no registers
+// while a walk steps (float32 K = 16: kept in registers, the walk's loop would
+// spill at 4 waves per SIMD).
+template <int K>
+__device__ __forceinline__ float4* basis_values() {
+    __shared__ __align__(16) float4 s_Y[(K + 3) / 4 * kBlock];
+    return s_Y;
+}
+template <int K>
+__device__ __forceinline__ void read_basis(uint32_t lane, float (&Y)[K]) {
+    const float4* p = basis_values<K>() + lane;
+#pragma unroll
+    for (int q = 0; q < (K + 3) / 4; ++q) {
+        const float4 v = p[q * kBlock];
+        Y[4 * q] = v.x;
+        if (4 * q + 1 < K) Y[4 * q + 1] = v.y;
+        if (4 * q + 2 < K) Y[4 * q + 2] = v.z;
+        if (4 * q + 3 < K) Y[4 * q + 3] = v.w;
+    }
+}
+__device__ __forceinline__ int rank_in(uint64_t m) {  // lanes of m below this one
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+template <class S, class = void>
+struct is_chunk : std::false_type {};
+template <class S>
+struct is_chunk<S, std::void_t<decltype(S::kChunk)>> : std::bool_constant<S::kChunk> {};
+
+// Walks the segments of the wave's rays; every lane of the wave calls it, and
+// those with `walk` set have a ray.  smp.shade(head, n) shades the n samples
+// from slot `head` of the queue on, smp.composite(...) adds one of them to its
+// ray and returns true to stop it, and smp.finish(head, n) then runs with every
+// lane.
+// Returns the number of cells visited, up to the one after the stop.
+//
+// A ray that has stopped early has walked up to a queue's length past the
+// stop, which changes nothing but the time (malformed entries there are not
+// counted).
+//
+// SPLIT: reaching `cap` data samples (exact: cells) with cells left stops the
+// walk; it leaves r.s and r.c at the start of the next cell and sets r.more
+// (unless the last sample ended it by early stopping), so that it can be
+// resumed or handed on.  (Samples, so that the hand-off does not depend on how
+// empty space is crossed.)  So does reaching max_steps, which without SPLIT is
+// an error.
+template <class Sampler, bool SPLIT>
+__device__ __forceinline__ int march_queued(const KTree& tr, Ray& r, bool walk, int max_steps, int cap, bool exact,
+                                            int* __restrict__ stk, Sampler& smp) {
+    constexpr bool CHUNK = is_chunk<Sampler>::value;
+    constexpr bool VIEW = Sampler::kView;
+    Walker<Sampler::kClip, CHUNK> w;
+    Sample* Q = sample_queue();
+    int steps = 0, nt = 0, bad_step = kNoCap;
+    // this ray's samples in the queue: how many, the first and the last
+    int mine = 0;
+    uint32_t first = 0, last = 0;
+    // the wave's queue: first slot and length
+    uint32_t head = 0, count = 0;
+    r.more = false;
+    const Index ix(tr);
+    if (walk) w.start(ix, r, stk);
+    while (true) {
+        bool take = false;
+        Cell c;
+        if (walk) {
+            ++steps;
+            const bool cell_cap = (steps >= max_steps) | (SPLIT && exact && steps >= cap);
+            c = w.step(ix, r, exact, cell_cap, SPLIT && !exact && nt + 1 >= cap, stk);
+            if (w.bad & (bad_step == kNoCap)) bad_step = steps;
+            walk = !c.last;
+            take = (c.leaf >= 0) & (c.delta > 0.0f);
+            if constexpr (CHUNK) {
+                smp.cpl = c.cpl;
+                if (steps == 1) {
+                    if (smp.skip0 < 0) smp.skip0 = c.delta > 0.0f ? 0 : 1;
+                    // a piece's first cell without a sample (the zero-length
+                    // rest of a cell the previous piece cut, or a start on a
+                    // face) still carries the stop test at its end
+                    if (!take && smp.test_first(c.cpl)) {
+                        walk = false;
+                        r.more = false;
+                    }
+                }
             }
         }
-        e = __builtin_amdgcn_raw_buffer_load_b32(child, pf, 0, 0);
-        // composite the previous sample (its loads precede the prefetch)
-        bool stop = false;
-        if (pending) {
-            pending = false;
-            stop = smp.consume();
+        const uint64_t m = __ballot(take);
+        if (m != 0ull) {
+            if (take) {
+                const uint32_t slot = (head + count + (uint32_t)rank_in(m)) % kQueue;
+                Sample q;
+                q.leaf = (uint32_t)c.leaf;
+                q.delta = c.delta;
+                q.info = threadIdx.x | (c.cpl ? 0u : 64u) | (uint32_t)steps << 7;
+                q.next = 0;
+                Q[slot] = q;
+                if constexpr (VIEW) sample_starts()[slot] = c.t_in;
+                if (mine == 0)
+                    first = slot;
+                else
+                    Q[last].next = slot;
+                last = slot;
+                ++mine;
+                ++nt;
+            }
+            count += (uint32_t)__popcll(m);
         }
-        smp.flush();
-        // start this cell's gather; lanes without a sample load nothing.  The
-        // walk ends only at the bottom of the body, so every path back to the
-        // top has issued the same loads.
-        const bool take = !stop & cand;
-        if constexpr (is_chunk<Sampler>::value) {
-            smp.cpl_next = cpl;
-            // a piece's first cell without a sample (the zero-length rest of
-            // a cell the previous piece cut, or a start on a face) still
-            // carries the stop test at its end
-            if ((steps == 1) & !take & !stop) stop = smp.test_first(cpl);
+        const bool walking = __ballot(walk) != 0ull;
+        if (count >= (uint32_t)kBlock || (!walking && count > 0)) {
+            const uint32_t n = min(count, (uint32_t)kBlock);
+            __builtin_amdgcn_wave_barrier();
+            smp.shade(head, n);
+            __builtin_amdgcn_wave_barrier();
+            while (mine > 0) {
+                const uint32_t at = (first - head) % kQueue;
+                if (at >= n) break;
+                const Sample q = Q[first];
+                --mine;
+                const bool stop = smp.composite(q, first, at);
+                first = q.next;
+                if (stop) {
+                    // the stop counts the cell behind it, where there is one
+                    const int seen = (int)(q.info >> 7) + 1;
+                    steps = walk ? seen : min(steps, seen);
+                    walk = false;
+                    r.more = false;
+                    mine = 0;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            smp.finish(head, n);
+            head = (head + n) % kQueue;
+            count -= n;
+        } else if (!walking) {
+            break;
         }
-        smp.issue(take ? leaf : -1, delta, t_in);
-        pending = take;
-        if constexpr (SPLIT) {
-            nt += take ? 1 : 0;
-            cap_end = capped & !stop;
-        }
-        if (last | stop) break;
     }
-    bool end_stop = false;
-    if (pending) end_stop = smp.consume();
-    smp.flush();
-    if constexpr (SPLIT) {
-        r.more = cap_end & !end_stop;
-        r.nt = exact ? steps : nt;
-    }
+    r.nt = exact ? steps : nt;
     // a lane that met a malformed entry or the step cap is counted once
-    if (bad) atomicAdd(&g_po_errors, 1ull);
+    if ((bad_step <= steps) | (!SPLIT & r.more)) atomicAdd(&g_po_errors, 1ull);
     return steps;
+}
+
+// The same walk with every sample shaded by its own ray's lane, one step after
+// the step that met it: smp.issue(leaf, delta, t, cut) starts the loads of the
+// leaf (leaf -1: a lane without a sample, which loads nothing), and
+// smp.consume() shades and composites them and returns true to stop the walk.
+// The read of the next cell's entry is started before, so that compositing
+// runs while it is in flight.
+template <class Sampler, bool SPLIT>
+__device__ __forceinline__ int march_inline(const KTree& tr, Ray& r, int max_steps, int cap, bool exact,
+                                            int* __restrict__ stk, Sampler& smp) {
+    constexpr bool CHUNK = is_chunk<Sampler>::value;
+    Walker<Sampler::kClip, CHUNK> w;
+    int steps = 0, nt = 0;
+    bool pending = false, stop = false;
+    const Index ix(tr);
+    w.start(ix, r, stk);
+    __builtin_amdgcn_sched_barrier(0);  // (the entry's load first)
+    // an empty gather, so that every path into the loop has the same loads in
+    // flight behind the entry (the compiler then waits for the entry alone)
+    smp.issue(-1, 0.0f, 0.0f, false);
+    while (true) {
+        ++steps;
+        const bool cell_cap = (steps >= max_steps) | (SPLIT && exact && steps >= cap);
+        const Cell c = w.step(ix, r, exact, cell_cap, SPLIT && !exact && nt + 1 >= cap, stk);
+        __builtin_amdgcn_sched_barrier(0);
+        if (pending) stop = smp.consume();
+        pending = !stop & (c.leaf >= 0) & (c.delta > 0.0f);
+        if constexpr (CHUNK) {
+            smp.cpl = c.cpl;
+            if (steps == 1) {
+                if (smp.skip0 < 0) smp.skip0 = c.delta > 0.0f ? 0 : 1;
+                // a piece's first cell without a sample (the zero-length rest of
+                // a cell the previous piece cut, or a start on a face) still
+                // carries the stop test at its end
+                if (!pending) stop = smp.test_first(c.cpl);
+            }
+        }
+        smp.issue(pending ? c.leaf : -1, c.delta, c.t_in, !c.cpl);
+        nt += pending ? 1 : 0;
+        if (c.last | stop) break;
+    }
+    const bool capped = r.more;
+    if (pending) stop = smp.consume();
+    r.more &= !stop;
+    r.nt = exact ? steps : nt;
+    // a lane that met a malformed entry or the step cap is counted once
+    if (w.bad | (!SPLIT & capped)) atomicAdd(&g_po_errors, 1ull);
+    return steps;
+}
+
+// Which of the two a sampler takes (kQueued): the queue costs about 45
+// instructions a step, and saves the waits on gathers and the lanes without a
+// sample.  It pays where a sample is expensive: records over 192 bytes (SG-25
+// 400x400, float32: 0.219 against 0.259 ms), codebooks (640x480: 0.306 against
+// 0.377) and gradients (8191 rays forward and backward: 0.291 against 0.486),
+// not for smaller records (800x800 float32 K = 16: 0.497 against 0.451) or the
+// densities alone (filter 800x800: 0.379 against 0.330).
+template <class Sampler, bool SPLIT = false>
+__device__ __forceinline__ int march(const KTree& tr, Ray& r, bool walk, int max_steps, int cap, bool exact,
+                                     int* __restrict__ stk, Sampler& smp) {
+    if constexpr (Sampler::kQueued) {
+        return march_queued<Sampler, SPLIT>(tr, r, walk, max_steps, cap, exact, stk, smp);
+    } else {
+        r.more = false;
+        r.nt = 0;
+        return walk ? march_inline<Sampler, SPLIT>(tr, r, max_steps, cap, exact, stk, smp) : 0;
+    }
 }
 
 template <typename T, int K, int NW>
@@ -646,130 +863,87 @@ __device__ __forceinline__ float dot_channel(const uint32_t (&w)[NW], int base, 
     return z;
 }
 
-// Forward shading and compositing of the samples of one ray (Sec. 3
-// eqn:quad, Sec. 4.1 colour, App. B.3 clamp of the raw density).  VIEW adds
-// the viewer outputs of Sec. 5.5: the expected termination distance and the
-// end of the walk at a slicing plane.
-template <typename T, int K, int VEC, int NL, bool VIEW>
-struct FwdSampler {
-    static constexpr int NW = Words<T, NL>::N;
-    static constexpr bool kClip = VIEW;
-    // float16 records: the basis values live in LDS ([k][lane], written by
-    // init_basis) instead of K registers, which takes the float16 chunk and
-    // sub-chunk walks to 5 waves per SIMD (depth-9 800x800 frame 0.461 ->
-    // 0.451 ms, 1920x1080 1.13 -> 1.06 ms)
-    static constexpr bool kLdsY = std::is_same<T, __half>::value && !VIEW;
-    __amdgpu_buffer_rsrc_t sig, shb;
-    uint32_t sig_end, sh_end, rec_bytes;
-    float stopT;
-    float Y[kLdsY ? 1 : K];
-    float* Yl;  // kLdsY: this lane's column of the LDS basis values
-    float c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, Tl = 1.0f;
-    float dep = 0.0f;
-    int ns = 0;
-    // in flight
-    float raw, delta, ta;
-    uint32_t w[NW];
-
-    // leaf < 0: no sample; the out-of-range offsets load zeros without memory traffic
-    __device__ __forceinline__ void issue(int leaf, float d, float t_in) {
-        raw = sigma_buf(sig, leaf < 0 ? sig_end : (uint32_t)leaf * (uint32_t)sizeof(T), (T*)nullptr);
-        load_words_buf<T, NL, VEC>(shb, leaf < 0 ? sh_end : (uint32_t)leaf * rec_bytes, w);
-        delta = d;
-        if constexpr (VIEW) ta = t_in;
-    }
-    __device__ __forceinline__ void flush() {}
-    __device__ __forceinline__ bool consume() {
-        ++ns;
-        const float s = fmaxf(raw, 0.0f);
-        if (!(s > 0.0f)) return false;
-        const float ex = __expf(-(s * delta));
-        const float wgt = Tl * (1.0f - ex);
-        if constexpr (kLdsY) {
-            float Yv[K];
+// Loads one record (NL elements, a whole number of VEC-byte vectors) at byte
+// offset `off` of a raw buffer.  An offset at or beyond the end of the buffer
+// returns zeros and touches no memory, which lets lanes without a sample run
+// the same straight-line code.
+template <typename T, int NL, int VEC>
+__device__ __forceinline__ void load_record(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t (&w)[Words<T, NL>::N]) {
+    static_assert(Words<T, NL>::NB % VEC == 0, "a record is loaded in whole vectors");
 #pragma unroll
-            for (int k = 0; k < K; ++k) Yv[k] = Yl[k * kBlock];
-            c0 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, 0, Yv)), c0);
-            c1 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, K, Yv)), c1);
-            c2 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, 2 * K, Yv)), c2);
+    for (int v = 0; v < Words<T, NL>::NB / VEC; ++v) {
+        if constexpr (VEC == 16) {
+            const auto q = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * v, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[4 * v + i] = q[i];
+        } else if constexpr (VEC == 8) {
+            const auto q = __builtin_amdgcn_raw_buffer_load_b64(rs, off + 8 * v, 0, 0);
+            w[2 * v] = q[0];
+            w[2 * v + 1] = q[1];
         } else {
-            c0 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, 0, Y)), c0);
-            c1 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, K, Y)), c1);
-            c2 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, 2 * K, Y)), c2);
+            w[v] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * v, 0, 0);
         }
-        if constexpr (VIEW) {
-            // integral of t sigma T(t) over the segment [ta, ta + delta]:
-            // Tl (ta alpha + delta f), f = alpha / tau - e^-tau, from its
-            // series below tau = 0.05 (alpha / tau cancels there)
-            const float tau = s * delta;
-            const float al = 1.0f - ex;
-            const float f = tau < 0.05f
-                                ? tau * (0.5f - tau * (1.0f / 3.0f - tau * (0.125f - tau * (1.0f / 30.0f - tau * (1.0f / 144.0f)))))
-                                : al / tau - ex;
-            dep = fmaf(Tl, fmaf(ta, al, delta * f), dep);
-        }
-        Tl = Tl * ex;
-        return Tl < stopT;
-    }
-};
-
-// The SH or SG basis at the ray direction (once per ray) for a plain
-// forward sampler: into its registers, or for float16 records into this
-// lane's column of an LDS array (one per kernel, K x kBlock floats).
-template <typename T, int K, int V, class Smp>
-__device__ __forceinline__ void init_basis(Smp& smp, const KTree& tr, const Ray& r) {
-    if constexpr (Smp::kLdsY) {
-        __shared__ float s_Y[K * kBlock];
-        float Yt[K];
-        if constexpr (V == PO_FWD_SG)
-            sg_basis<K>(tr.lobes, r.dn[0], r.dn[1], r.dn[2], Yt);
-        else
-            sh_basis<K>(r.dn[0], r.dn[1], r.dn[2], Yt);
-        smp.Yl = s_Y + threadIdx.x;
-#pragma unroll
-        for (int k = 0; k < K; ++k) smp.Yl[k * kBlock] = Yt[k];
-    } else if constexpr (V == PO_FWD_SG) {
-        sg_basis<K>(tr.lobes, r.dn[0], r.dn[1], r.dn[2], smp.Y);
-    } else {
-        sh_basis<K>(r.dn[0], r.dn[1], r.dn[2], smp.Y);
     }
 }
 
+// Leaf arrays of a tree with float32 or float16 records, bound to buffers.
+template <typename T, int K, int VEC, int NL>
+struct Records {
+    __amdgpu_buffer_rsrc_t sig, shb;
+    uint32_t sig_end, sh_end, rec_bytes;
+
+    __device__ __forceinline__ void bind(const KTree& tr) {
+        sig_end = held(tr.sigma_bytes);
+        sh_end = held(tr.sh_bytes);
+        sig = raw_rsrc(held(tr.sigma), sig_end);
+        shb = raw_rsrc(held(tr.sh), sh_end);
+        rec_bytes = held((uint32_t)tr.stride * (uint32_t)sizeof(T));
+    }
+    // Density (clamped) and colour of the leaf of this lane's sample, for the
+    // ray of lane src; on false: no sample.
+    __device__ __forceinline__ float eval(bool on, uint32_t leaf, uint32_t src, float (&col)[3]) const {
+        uint32_t w[Words<T, NL>::N];
+        const uint32_t raw = sigma_buf(sig, on ? leaf * (uint32_t)sizeof(T) : sig_end, (T*)nullptr);
+        load_record<T, NL, VEC>(shb, on ? leaf * rec_bytes : sh_end, w);
+        float Y[K];
+        read_basis<K>(src, Y);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) col[c] = sigmoid(dot_channel<T, K>(w, c * K, Y));
+        return fmaxf(sigma_of<T>(raw), 0.0f);
+    }
+};
+
 // Codebook leaves (App. B.2): the record holds one 16-bit codebook position
-// per basis function; consume() gathers the K float16 colours (8 bytes each,
-// from the per-basis codebooks) and shades as an SH leaf.  The gathers are in
-// flight together with the next cell's entry prefetch, which the walk waits
-// for next anyway.
+// per basis function; a sample gathers the K float16 colours (8 bytes each,
+// from the per-basis codebooks) and shades as an SH leaf.
 template <int K, int VEC, int NL>
-struct CbSampler {
-    static constexpr int NW = Words<__half, NL>::N;
-    static constexpr bool kClip = false;
+struct CbRecords {
     __amdgpu_buffer_rsrc_t sig, shb, cb;
     uint32_t sig_end, sh_end, rec_bytes, cb_basis_bytes;
-    float stopT;
-    float Y[K];
-    float c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, Tl = 1.0f;
-    float dep = 0.0f;
-    int ns = 0;
-    // in flight
-    float raw, delta;
-    uint32_t w[NW];
 
-    __device__ __forceinline__ void issue(int leaf, float d, float) {
-        raw = sigma_buf(sig, leaf < 0 ? sig_end : (uint32_t)leaf * 2u, (__half*)nullptr);
-        load_words_buf<__half, NL, VEC>(shb, leaf < 0 ? sh_end : (uint32_t)leaf * rec_bytes, w);
-        delta = d;
+    __device__ __forceinline__ void bind(const KTree& tr) {
+        sig = raw_rsrc(tr.sigma, tr.sigma_bytes);
+        shb = raw_rsrc(tr.sh, tr.sh_bytes);
+        sig_end = tr.sigma_bytes;
+        sh_end = tr.sh_bytes;
+        rec_bytes = (uint32_t)tr.stride * 2u;
+        cb_basis_bytes = (uint32_t)tr.cb_entries * 8u;
+        cb = raw_rsrc(tr.codebook, (uint32_t)K * cb_basis_bytes);
     }
-    __device__ __forceinline__ void flush() {}
-    __device__ __forceinline__ bool consume() {
-        ++ns;
-        const float s = fmaxf(raw, 0.0f);
-        if (!(s > 0.0f)) return false;
+    __device__ __forceinline__ float eval(bool on, uint32_t leaf, uint32_t src, float (&col)[3]) const {
+        uint32_t w[Words<__half, NL>::N];
+        const uint32_t raw = sigma_buf(sig, on ? leaf * 2u : sig_end, (__half*)nullptr);
+        load_record<__half, NL, VEC>(shb, on ? leaf * rec_bytes : sh_end, w);
+        const float s = fmaxf(sigma_of<__half>(raw), 0.0f);
+        float Y[K];
+        read_basis<K>(src, Y);
         uint32_t e0[K], e1[K];
+        const uint32_t none = (uint32_t)K * cb_basis_bytes;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const uint32_t pos = (w[k >> 1] >> (16 * (k & 1))) & 0xffffu;
-            const auto q = __builtin_amdgcn_raw_buffer_load_b64(cb, (uint32_t)k * cb_basis_bytes + pos * 8u, 0, 0);
+            const auto q = __builtin_amdgcn_raw_buffer_load_b64(
+                cb, s > 0.0f ? (uint32_t)k * cb_basis_bytes + pos * 8u : none, 0, 0);
             e0[k] = q[0];
             e1[k] = q[1];
         }
@@ -780,15 +954,129 @@ struct CbSampler {
             z1 = fmaf(__half2float(__ushort_as_half((unsigned short)(e0[k] >> 16))), Y[k], z1);
             z2 = fmaf(__half2float(__ushort_as_half((unsigned short)(e1[k] & 0xffffu))), Y[k], z2);
         }
-        const float ex = __expf(-(s * delta));
+        col[0] = sigmoid(z0);
+        col[1] = sigmoid(z1);
+        col[2] = sigmoid(z2);
+        return s;
+    }
+};
+
+// The integral of t sigma T(t) over a segment [ta, ta + delta] of optical
+// depth tau, from T = 1 (ex = e^-tau): ta alpha + delta f, f = alpha / tau -
+// e^-tau, from its series below tau = 0.05 (alpha / tau cancels there).
+__device__ __forceinline__ float depth_term(float tau, float ex, float delta, float ta) {
+    const float al = 1.0f - ex;
+    const float f = tau < 0.05f
+                        ? tau * (0.5f - tau * (1.0f / 3.0f - tau * (0.125f - tau * (1.0f / 30.0f - tau * (1.0f / 144.0f)))))
+                        : al / tau - ex;
+    return fmaf(ta, al, delta * f);
+}
+
+// Forward shading and compositing of the samples of a wave's rays (Sec. 3
+// eqn:quad, Sec. 4.1 colour, App. B.3 clamp of the raw density).  VIEW adds
+// the viewer outputs of Sec. 5.5: the expected termination distance and the
+// end of the walk at a slicing plane.
+template <class Rec, bool VIEW>
+struct FwdQueued : Rec {
+    static constexpr bool kClip = VIEW;
+    static constexpr bool kView = VIEW;
+    static constexpr bool kQueued = true;
+    float stopT;
+    float c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, Tl = 1.0f;
+    float dep = 0.0f;
+    int ns = 0;
+
+    __device__ __forceinline__ void shade(uint32_t head, uint32_t n) {
+        const uint32_t slot = (head + threadIdx.x) % kQueue;
+        const Sample q = sample_queue()[slot];
+        const bool on = threadIdx.x < n;
+        float col[3];
+        const float s = Rec::eval(on, q.leaf, q.info & 63u, col);
+        const float tau = s * q.delta;
+        const float ex = __expf(-tau);
+        shaded()[threadIdx.x] = make_float4(s > 0.0f ? ex : -1.0f, col[0], col[1], col[2]);
+        if constexpr (VIEW) shaded_depth()[threadIdx.x] = depth_term(tau, ex, q.delta, sample_starts()[slot]);
+    }
+    // Composites one sample of this lane's ray (slot of the queue, number `at`
+    // of the shaded ones); true when early stopping ends the ray.
+    __device__ __forceinline__ bool composite(const Sample&, uint32_t, uint32_t at) {
+        ++ns;
+        const float4 v = shaded()[at];
+        if (v.x < 0.0f) return false;
+        const float wgt = Tl * (1.0f - v.x);
+        c0 = fmaf(wgt, v.y, c0);
+        c1 = fmaf(wgt, v.z, c1);
+        c2 = fmaf(wgt, v.w, c2);
+        if constexpr (VIEW) dep = fmaf(Tl, shaded_depth()[at], dep);
+        Tl = Tl * v.x;
+        return Tl < stopT;
+    }
+    __device__ __forceinline__ void finish(uint32_t, uint32_t) {}
+};
+
+// The same for samples shaded by their own ray's lane (march_inline).
+template <typename T, int K, int VEC, int NL, bool VIEW>
+struct FwdInline : Records<T, K, VEC, NL> {
+    static constexpr bool kClip = VIEW;
+    static constexpr bool kView = VIEW;
+    static constexpr bool kQueued = false;
+    float stopT;
+    float c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, Tl = 1.0f;
+    float dep = 0.0f;
+    int ns = 0;
+    // in flight
+    uint32_t raw;
+    float delta, ta;
+    bool cut;
+    uint32_t w[Words<T, NL>::N];
+
+    __device__ __forceinline__ void issue(int leaf, float d, float t_in, bool is_cut) {
+        raw = sigma_buf(this->sig, leaf < 0 ? this->sig_end : (uint32_t)leaf * (uint32_t)sizeof(T), (T*)nullptr);
+        load_record<T, NL, VEC>(this->shb, leaf < 0 ? this->sh_end : (uint32_t)leaf * this->rec_bytes, w);
+        delta = d;
+        cut = is_cut;
+        if constexpr (VIEW) ta = t_in;
+    }
+    __device__ __forceinline__ bool consume() {
+        ++ns;
+        const float s = fmaxf(sigma_of<T>(raw), 0.0f);
+        if (!(s > 0.0f)) return false;
+        const float tau = s * delta;
+        const float ex = __expf(-tau);
         const float wgt = Tl * (1.0f - ex);
-        c0 = fmaf(wgt, sigmoid(z0), c0);
-        c1 = fmaf(wgt, sigmoid(z1), c1);
-        c2 = fmaf(wgt, sigmoid(z2), c2);
+        float Y[K];
+        read_basis<K>(threadIdx.x, Y);
+        c0 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, 0, Y)), c0);
+        c1 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, K, Y)), c1);
+        c2 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, 2 * K, Y)), c2);
+        if constexpr (VIEW) dep = fmaf(Tl, depth_term(tau, ex, delta, ta), dep);
         Tl = Tl * ex;
         return Tl < stopT;
     }
 };
+
+// The SH or SG basis of a variant at this lane's ray direction, into the
+// wave's LDS array.
+template <int K, int V>
+__device__ __forceinline__ void init_basis(const KTree& tr, const KOpts& op, const Ray& r) {
+    float Y[K];
+    if constexpr (V == PO_FWD_SG)
+        sg_basis<K>(tr.lobes, r.dn[0], r.dn[1], r.dn[2], Y);
+    else if constexpr (V == PO_FWD_VIEW)
+        colour_basis<K>(tr, r.dn[0], r.dn[1], r.dn[2], Y);
+    else
+        sh_basis<K>(r.dn[0], r.dn[1], r.dn[2], Y);
+    if constexpr (V == PO_FWD_VIEW) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if ((op.sh_off >> k) & 1u) Y[k] = 0.0f;
+    }
+    float4* p = basis_values<K>() + threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < (K + 3) / 4; ++q)
+        p[q * kBlock] = make_float4(Y[4 * q], 4 * q + 1 < K ? Y[4 * q + 1] : 0.0f, 4 * q + 2 < K ? Y[4 * q + 2] : 0.0f,
+                                    4 * q + 3 < K ? Y[4 * q + 3] : 0.0f);
+}
 
 // One chunk [s_lo, s_hi] of a split ray.  The chunk composites from T = 1
 // (or from a known transmittance when it is walked again); because
@@ -801,29 +1089,26 @@ struct CbSampler {
 // tested sample (-1: none); the chunk stops itself once T < stopT there,
 // since its walk cannot matter past that point for any transmittance in
 // front of it.
-template <class Base, bool COUNT = false>
+template <class Base>
 struct ChunkOf : Base {
     static constexpr bool kClip = true;
     static constexpr bool kChunk = true;
-    bool cpl_next = true, cpl = true;
+    bool cpl = true;        // the last cell walked ends inside the piece
     bool hit = false;       // stopped by stopT
     bool smp_cut = false;   // the last composited sample was cut by the walk's end
-    int issued = 0;         // issue() calls: the walk's first is its placeholder gather
-    int skip0 = 0;          // 1: the first cell had zero length (the walk began on its far face)
+    int skip0 = -1;         // 1: the first cell had zero length (the walk began on its far face)
     float Tlast = -1.0f;
 
-    __device__ __forceinline__ void issue(int leaf, float d, float t_in) {
-        Base::issue(leaf, d, t_in);
-        cpl = cpl_next;
-        if constexpr (COUNT) {
-            if (issued == 1) skip0 = d > 0.0f ? 0 : 1;
-            ++issued;
-        }
+    __device__ __forceinline__ bool composite(const Sample& q, uint32_t slot, uint32_t at) {
+        return tested(Base::composite(q, slot, at), (q.info & 64u) != 0u);
     }
     __device__ __forceinline__ bool consume() {
         const bool st = Base::consume();
-        if constexpr (COUNT) smp_cut = !cpl;
-        if (!cpl) return false;
+        return tested(st, this->cut);
+    }
+    __device__ __forceinline__ bool tested(bool st, bool is_cut) {
+        smp_cut = is_cut;
+        if (is_cut) return false;
         Tlast = this->Tl;
         hit |= st;
         return st;
@@ -841,62 +1126,42 @@ struct ChunkOf : Base {
 
 // Samplers of the split render: the first walk's, and a piece's.
 template <typename T, int K, int VEC, int NL, int V>
-using FirstSampler = std::conditional_t<V == PO_FWD_CB, CbSampler<K, VEC, NL>,
-                                        FwdSampler<T, K, VEC, NL, V == PO_FWD_VIEW>>;
+using FirstSampler = std::conditional_t<
+    V == PO_FWD_CB, FwdQueued<CbRecords<K, VEC, NL>, false>,
+    std::conditional_t<(sizeof(T) * 3 * K > 192), FwdQueued<Records<T, K, VEC, NL>, V == PO_FWD_VIEW>,
+                       FwdInline<T, K, VEC, NL, V == PO_FWD_VIEW>>>;
 template <typename T, int K, int VEC, int NL, int V>
-using ChunkSampler = ChunkOf<FirstSampler<T, K, VEC, NL, V>, V == PO_FWD_VIEW>;
+using ChunkSampler = ChunkOf<FirstSampler<T, K, VEC, NL, V>>;
 
-// Renders one ray: colour (background included), final T, samples, steps
-// and, in the viewer variant, the expected termination distance, SH subsets
-// and the slicing plane.  V is a PO_FWD_* variant.
+// Binds a forward sampler to a tree (every lane), and a ray's basis.
+template <int K, int V, class Smp>
+__device__ __forceinline__ void fwd_init(Smp& smp, const KTree& tr, const KOpts& op, bool ray, const Ray& r) {
+    smp.bind(tr);
+    smp.stopT = op.stop_T;
+    if (ray) init_basis<K, V>(tr, op, r);
+}
+
+// Renders the wave's rays (valid: this lane has one): colour (background
+// included), final T, samples, steps and, in the viewer variant, the expected
+// termination distance, SH subsets and the slicing plane.  V is a PO_FWD_*
+// variant.
 template <typename T, int K, int VEC, int NL, int V>
-__device__ __forceinline__ void render_one(const KTree& tr, const KOpts& op, const double (&o)[3],
+__device__ __forceinline__ void render_one(const KTree& tr, const KOpts& op, bool valid, const double (&o)[3],
                                            const double (&d)[3], int* __restrict__ stk, float (&C)[3], float& Tr,
                                            int& ns, int& steps, float& dep) {
-    C[0] = C[1] = C[2] = 0.0f;
-    Tr = 1.0f;
-    ns = 0;
-    steps = 0;
-    dep = 0.0f;
-    constexpr bool VIEW = V == PO_FWD_VIEW;
     Ray r;
     double s_lo = 0.0, s_hi = 1e300;
-    if constexpr (VIEW) clip_range(op, o, d, s_lo, s_hi);
-    if (ray_setup(tr, o, d, r, s_lo, s_hi)) {
-        using Smp = std::conditional_t<V == PO_FWD_CB, CbSampler<K, VEC, NL>, FwdSampler<T, K, VEC, NL, VIEW>>;
-        Smp smp;
-        smp.sig = raw_rsrc(tr.sigma, tr.sigma_bytes);
-        smp.shb = raw_rsrc(tr.sh, tr.sh_bytes);
-        smp.sig_end = tr.sigma_bytes;
-        smp.sh_end = tr.sh_bytes;
-        smp.rec_bytes = (uint32_t)tr.stride * (uint32_t)sizeof(T);
-        smp.stopT = op.stop_T;
-        if constexpr (V == PO_FWD_CB) {
-            smp.cb_basis_bytes = (uint32_t)tr.cb_entries * 8u;
-            smp.cb = raw_rsrc(tr.codebook, (uint32_t)K * smp.cb_basis_bytes);
-        }
-        if constexpr (V == PO_FWD_SH || V == PO_FWD_SG)
-            init_basis<T, K, V>(smp, tr, r);
-        else if constexpr (V == PO_FWD_CB)
-            sh_basis<K>(r.dn[0], r.dn[1], r.dn[2], smp.Y);
-        else
-            colour_basis<K>(tr, r.dn[0], r.dn[1], r.dn[2], smp.Y);
-        if constexpr (VIEW) {
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                if ((op.sh_off >> k) & 1u) smp.Y[k] = 0.0f;
-        }
-        steps = march(tr, r, op.max_steps, kNoCap, exact_cells(op), stk, smp);
-        C[0] = smp.c0;
-        C[1] = smp.c1;
-        C[2] = smp.c2;
-        Tr = smp.Tl;
-        ns = smp.ns;
-        dep = smp.dep;
-    }
-    C[0] = fmaf(Tr, op.bg[0], C[0]);
-    C[1] = fmaf(Tr, op.bg[1], C[1]);
-    C[2] = fmaf(Tr, op.bg[2], C[2]);
+    if constexpr (V == PO_FWD_VIEW) clip_range(op, o, d, s_lo, s_hi);
+    const bool walk = valid && ray_setup(tr, o, d, r, s_lo, s_hi);
+    FirstSampler<T, K, VEC, NL, V> smp;
+    fwd_init<K, V>(smp, tr, op, walk, r);
+    steps = march(tr, r, walk, op.max_steps, kNoCap, exact_cells(op), stk, smp);
+    Tr = smp.Tl;
+    ns = smp.ns;
+    dep = smp.dep;
+    C[0] = fmaf(Tr, op.bg[0], smp.c0);
+    C[1] = fmaf(Tr, op.bg[1], smp.c1);
+    C[2] = fmaf(Tr, op.bg[2], smp.c2);
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs (workgroup b runs on
@@ -929,13 +1194,20 @@ __global__ __launch_bounds__(kBlock) void k_render_rays(KTree tr, int64_t n, int
     const int64_t blk = xcd_swizzle(blockIdx.x, n_blocks);
     if (blk < 0) return;
     const int64_t i = blk * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const double ro[3] = {(double)o[3 * i], (double)o[3 * i + 1], (double)o[3 * i + 2]};
-    const double rd[3] = {(double)d[3 * i], (double)d[3 * i + 1], (double)d[3 * i + 2]};
+    const bool valid = i < n;
+    double ro[3] = {0.0, 0.0, 0.0}, rd[3] = {0.0, 0.0, 0.0};
+    if (valid) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            ro[k] = (double)o[3 * i + k];
+            rd[k] = (double)d[3 * i + k];
+        }
+    }
     float C[3], Tr, dep;
     int ns, steps;
     extern __shared__ int po_stack[];
-    render_one<T, K, VEC, NL, V>(tr, op, ro, rd, po_stack + threadIdx.x, C, Tr, ns, steps, dep);
+    render_one<T, K, VEC, NL, V>(tr, op, valid, ro, rd, po_stack + threadIdx.x, C, Tr, ns, steps, dep);
+    if (!valid) return;
     rgb[3 * i + 0] = C[0];
     rgb[3 * i + 1] = C[1];
     rgb[3 * i + 2] = C[2];
@@ -1005,13 +1277,14 @@ __global__ __launch_bounds__(kBlock) void k_render_camera(KBatch<MAXJ> B) {
     const int lane = threadIdx.x;
     const int px = tx * 16 + (quad & 1) * 8 + (lane & 7);
     const int py = ty * 16 + (quad >> 1) * 8 + (lane >> 3);
-    if (px >= J.cam.W || py >= J.cam.H) return;
+    const bool valid = (px < J.cam.W) & (py < J.cam.H);
     double ro[3], rd[3];
     pixel_ray(J.cam, px, py, ro, rd);
     float C[3], Tr, dep;
     int ns, steps;
     extern __shared__ int po_stack[];
-    render_one<T, K, VEC, NL, V>(J.tr, J.op, ro, rd, po_stack + threadIdx.x, C, Tr, ns, steps, dep);
+    render_one<T, K, VEC, NL, V>(J.tr, J.op, valid, ro, rd, po_stack + threadIdx.x, C, Tr, ns, steps, dep);
+    if (!valid) return;
     const size_t p = (size_t)py * J.cam.W + px;
     J.rgb[3 * p + 0] = C[0];
     J.rgb[3 * p + 1] = C[1];
@@ -1097,31 +1370,6 @@ struct PieceOut {
 };
 static_assert(sizeof(PieceOut) == 32, "queue record layout");
 
-template <typename T, int K, int V, class Smp>
-__device__ __forceinline__ void fwd_init(Smp& smp, const KTree& tr, const KOpts& op, const Ray& r) {
-    smp.sig = raw_rsrc(tr.sigma, tr.sigma_bytes);
-    smp.shb = raw_rsrc(tr.sh, tr.sh_bytes);
-    smp.sig_end = tr.sigma_bytes;
-    smp.sh_end = tr.sh_bytes;
-    smp.rec_bytes = (uint32_t)tr.stride * (uint32_t)sizeof(T);
-    smp.stopT = op.stop_T;
-    if constexpr (V == PO_FWD_CB) {
-        smp.cb_basis_bytes = (uint32_t)tr.cb_entries * 8u;
-        smp.cb = raw_rsrc(tr.codebook, (uint32_t)K * smp.cb_basis_bytes);
-    }
-    if constexpr (V == PO_FWD_SH || V == PO_FWD_SG) {
-        init_basis<T, K, V>(smp, tr, r);
-    } else if constexpr (V == PO_FWD_VIEW) {
-        colour_basis<K>(tr, r.dn[0], r.dn[1], r.dn[2], smp.Y);
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if ((op.sh_off >> k) & 1u) smp.Y[k] = 0.0f;
-    } else {
-        sh_basis<K>(r.dn[0], r.dn[1], r.dn[2], smp.Y);
-    }
-}
-
-
 // Ray idx of a split render: pixel idx = py * W + px of the job's camera
 // (SRC 0) or entry idx of the caller's ray arrays (SRC 1).
 template <int SRC>
@@ -1179,13 +1427,21 @@ __device__ __forceinline__ void piece_bounds(const KJob& J, const KSplit& S, int
     up = k + 1 < n ? a + (e - a) * (double)(k + 1) / (double)n : hi;
 }
 
-// Pieces wanted for the rest [r.s, r.s_exit] of a walk that took r.nt samples
-// (exact renders: cells) since s_first: about `target` each, from the number
-// per unit parameter so far, and at least ub_frac of the finest-cell faces
-// ahead.
-__device__ __forceinline__ int pieces_wanted(const Ray& r, double s_first, const KSplit& S, int target) {
-    const double rest = r.s_exit - r.s;
-    double est = (double)r.nt * rest / fmax(r.s - s_first, 1e-300);
+// Start of this lane's walk and end of its ray, kept in LDS (not in registers)
+// while the walk runs.
+__device__ __forceinline__ double2* walk_range() {
+    __shared__ double2 s_range[kBlock];
+    return s_range + threadIdx.x;
+}
+
+// Pieces wanted for the rest of a walk from r.s on that took r.nt samples
+// (exact renders: cells) over its walk_range: about `target` each, from the
+// number per unit parameter so far, and at least ub_frac of the finest-cell
+// faces ahead.
+__device__ __forceinline__ int pieces_wanted(const Ray& r, const KSplit& S, int target) {
+    const double2 range = *walk_range();
+    const double rest = range.y - r.s;
+    double est = (double)r.nt * rest / fmax(r.s - range.x, 1e-300);
     est = fmax(est, (double)S.ub_frac * rest * (fabs(r.dg[0]) + fabs(r.dg[1]) + fabs(r.dg[2])));
     return (int)fmin(fmax(ceil(est / (double)target), 1.0), (double)kSplitMaxChunks);
 }
@@ -1244,42 +1500,42 @@ __device__ __forceinline__ void first_walk(const KJob& J, const KSplit& S, int i
     using Smp = FirstSampler<T, K, VEC, NL, V>;
     Smp smp;
     Ray r;
-    int want = 0, steps = 0;
+    int want = 0, steps = 0, h = -1;
+    bool walk = false, handed = false;
     if (valid) {
         double ro[3], rd[3];
         ray_of<SRC>(J, S, idx, ro, rd);
         double s_lo = 0.0, s_hi = 1e300;
         if constexpr (V == PO_FWD_VIEW) clip_range(op, ro, rd, s_lo, s_hi);
-        if (ray_setup(tr, ro, rd, r, s_lo, s_hi)) {
-            const double s_first = r.s;
-            fwd_init<T, K, V>(smp, tr, op, r);
-            steps = march<Smp, true>(tr, r, op.max_steps, S.split_cap, S.exact, stk, smp);
-            if (r.more) {
-                if (steps >= op.max_steps)
-                    atomicAdd(&g_po_errors, 1ull);  // the step cap proper
-                else
-                    want = pieces_wanted(r, s_first, S, S.chunk_target);
-            }
-        }
+        walk = ray_setup(tr, ro, rd, r, s_lo, s_hi);
+        if (walk) *walk_range() = make_double2(r.s, r.s_exit);
     }
-    const int h = claim_pieces(S.count, S.info, claim_region(), want, S.region_slots);
-    bool handed = false;
-    if (want > 0) {
-        if (h >= 0) {
-            ContHead hd;
-            hd.s = r.s;
-            hd.T = smp.Tl;
-            hd.c0 = smp.c0;
-            hd.c1 = smp.c1;
-            hd.c2 = smp.c2;
-            hd.pix = idx;
-            hd.pad = 0;
-            reinterpret_cast<ContHead*>(S.head)[h] = hd;
-            handed = true;
-        } else {
-            // region full: finish here
-            steps += march<Smp>(tr, r, op.max_steps - steps, kNoCap, S.exact, stk, smp);
+    fwd_init<K, V>(smp, tr, op, walk, r);
+    // the second pass finishes the walks whose region is full
+    for (int pass = 0; pass < 2; ++pass) {
+        steps += march<Smp, true>(tr, r, walk, op.max_steps - steps, pass ? kNoCap : S.split_cap, S.exact, stk, smp);
+        if (walk & r.more) {
+            if (steps >= op.max_steps)
+                atomicAdd(&g_po_errors, 1ull);  // the step cap proper
+            else
+                want = pieces_wanted(r, S, S.chunk_target);
         }
+        if (pass) break;
+        h = claim_pieces(S.count, S.info, claim_region(), want, S.region_slots);
+        handed = (want > 0) & (h >= 0);
+        walk = (want > 0) & (h < 0);
+        if (__ballot(walk) == 0ull) break;
+    }
+    if (handed) {
+        ContHead hd;
+        hd.s = r.s;
+        hd.T = smp.Tl;
+        hd.c0 = smp.c0;
+        hd.c1 = smp.c1;
+        hd.c2 = smp.c2;
+        hd.pix = idx;
+        hd.pad = 0;
+        reinterpret_cast<ContHead*>(S.head)[h] = hd;
     }
     const size_t p = (size_t)idx;
     if constexpr (SRC == 1) {
@@ -1313,7 +1569,7 @@ __device__ __forceinline__ void first_walk(const KJob& J, const KSplit& S, int i
 // so they keep 4 waves or their natural count.
 template <typename T, int K, int V>
 constexpr int kPieceWaves = (V == PO_FWD_SH || V == PO_FWD_SG) && sizeof(T) * 3 * K <= 192
-                                ? (sizeof(T) == 2 && V == PO_FWD_SH && K <= 16 ? 5 : 4)
+                                ? 4
                                 : 1;
 
 template <typename T, int K, int VEC, int NL, int V>
@@ -1382,40 +1638,44 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
     using Smp = ChunkSampler<T, K, VEC, NL, V>;
     Smp smp;
     Ray r;
-    int want = 0, steps = 0, pix = 0;
+    int want = 0, steps = 0, pix = 0, sub = -1;
     extern __shared__ int po_stack[];
     int* stk = po_stack + threadIdx.x;
+    bool walk = false;
     if (h >= 0) {
         const int mj = in.y;
         const ContHead hd = reinterpret_cast<const ContHead*>(S.head)[h];
         pix = hd.pix;
-        if (piece_setup<SRC>(J, S, pix, hd.s, walk_end<V, SRC>(J, S, pix), mj & 255, mj >> 8, r)) {
-            const double s_first = r.s;
-            fwd_init<T, K, V>(smp, J.tr, J.op, r);
-            steps = march<Smp, true>(J.tr, r, J.op.max_steps, S.chunk_cap, S.exact, stk, smp);
-            if (r.more) {
-                if (steps >= J.op.max_steps) {
-                    atomicAdd(&g_po_errors, 1ull);
-                } else {
-                    want = pieces_wanted(r, s_first, S, S.sub_target);
-                }
+        walk = piece_setup<SRC>(J, S, pix, hd.s, walk_end<V, SRC>(J, S, pix), mj & 255, mj >> 8, r);
+        if (walk) *walk_range() = make_double2(r.s, r.s_exit);
+    }
+    if (__ballot(h >= 0) == 0ull) return;
+    fwd_init<K, V>(smp, J.tr, J.op, walk, r);
+    // the second pass finishes the walks whose region is full
+    for (int pass = 0; pass < 2; ++pass) {
+        steps += march<Smp, true>(J.tr, r, walk, J.op.max_steps - steps, pass ? kNoCap : S.chunk_cap, S.exact, stk, smp);
+        if (walk & r.more) {
+            if (steps >= J.op.max_steps)
+                atomicAdd(&g_po_errors, 1ull);
+            else
+                want = pieces_wanted(r, S, S.sub_target);
+        }
+        if (pass) break;
+        sub = claim_pieces(S.count2, S.info2, claim_region(), want, S.region_slots);
+        walk = (want > 0) & (sub < 0);
+        if (want > 0) {
+            if (sub >= 0) {
+                SubHead sh;
+                sh.lo = r.s;
+                sh.hi = r.s_end;
+                sh.pix = pix;
+                sh.pad[0] = sh.pad[1] = sh.pad[2] = 0;
+                reinterpret_cast<SubHead*>(S.head2)[sub] = sh;
+            } else {
+                want = 0;
             }
         }
-    }
-    int sub = claim_pieces(S.count2, S.info2, claim_region(), want, S.region_slots);
-    if (want > 0) {
-        if (sub >= 0) {
-            SubHead sh;
-            sh.lo = r.s;
-            sh.hi = r.s_end;
-            sh.pix = pix;
-            sh.pad[0] = sh.pad[1] = sh.pad[2] = 0;
-            reinterpret_cast<SubHead*>(S.head2)[sub] = sh;
-        } else {
-            // region full: finish here
-            steps += march<Smp>(J.tr, r, J.op.max_steps - steps, kNoCap, S.exact, stk, smp);
-            want = 0;
-        }
+        if (__ballot(walk) == 0ull) break;
     }
     if (h >= 0) {
         PieceOut o;
@@ -1429,7 +1689,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
         o.dep = smp.dep;
         reinterpret_cast<PieceOut*>(S.part)[q] = o;
         if constexpr (V == PO_FWD_VIEW)
-            S.view_part[q] = make_int4(smp.ns, steps - smp.skip0, smp.smp_cut ? 1 : 0,
+            S.view_part[q] = make_int4(smp.ns, steps - max(smp.skip0, 0), smp.smp_cut ? 1 : 0,
                                        (want == 0 && !smp.cpl) ? 1 : 0);
     }
 }
@@ -1438,22 +1698,23 @@ template <typename T, int K, int VEC, int NL, int V, int SRC>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWaves<T, K, V>, 8))) void k_render_subchunks(
     KBatch<1> B, KSplit S) {
     const int q = split_slot(S.count2, S.region_slots);
-    if (q < 0) return;
-    const int4 in = S.info2[q];
+    const int4 in = q < 0 ? make_int4(-1, 0, -1, 0) : S.info2[q];
     const int h = in.x;
-    if (h < 0) return;
-    const int mj = in.y;
-    const SubHead sh = reinterpret_cast<const SubHead*>(S.head2)[h];
+    if (__ballot(h >= 0) == 0ull) return;
     const KJob& J = B.job[0];
     using Smp = ChunkSampler<T, K, VEC, NL, V>;
     Smp smp;
     Ray r;
-    int steps = 0;
-    if (piece_setup<SRC>(J, S, sh.pix, sh.lo, sh.hi, mj & 255, mj >> 8, r)) {
-        fwd_init<T, K, V>(smp, J.tr, J.op, r);
-        extern __shared__ int po_stack[];
-        steps = march(J.tr, r, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
+    bool walk = false;
+    if (h >= 0) {
+        const int mj = in.y;
+        const SubHead sh = reinterpret_cast<const SubHead*>(S.head2)[h];
+        walk = piece_setup<SRC>(J, S, sh.pix, sh.lo, sh.hi, mj & 255, mj >> 8, r);
     }
+    fwd_init<K, V>(smp, J.tr, J.op, walk, r);
+    extern __shared__ int po_stack[];
+    const int steps = march(J.tr, r, walk, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
+    if (h < 0) return;
     PieceOut o;
     o.c0 = smp.c0;
     o.c1 = smp.c1;
@@ -1465,12 +1726,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
     o.dep = smp.dep;
     reinterpret_cast<PieceOut*>(S.part2)[q] = o;
     if constexpr (V == PO_FWD_VIEW)
-        S.view_part2[q] = make_int4(smp.ns, steps - smp.skip0, smp.smp_cut ? 1 : 0, smp.cpl ? 0 : 1);
+        S.view_part2[q] = make_int4(smp.ns, steps - max(smp.skip0, 0), smp.smp_cut ? 1 : 0, smp.cpl ? 0 : 1);
 }
 
-// Running state of a join: transmittance and colour in front, and for the
-// viewer variant the depth integral, sample and cell counts, and whether the
-// last piece joined ended in a cut cell (counted again by the next piece).
+// Front-to-back join of the pieces of the ray whose first slot is q (ray: this
+// lane has one; every lane of the wave calls it).  Running state: transmittance
+// and colour in front, and for the viewer variant the depth integral, sample
+// and cell counts, and whether the last piece joined ended in a cut cell
+// (counted again by the next piece).
 struct JoinAcc {
     float Tp;
     float c[3];
@@ -1478,84 +1741,127 @@ struct JoinAcc {
     int ns, steps, cut_smp, cut;
 };
 
-// Front-to-back join of one piece with result o: piece k of n of [a, hi]; a
-// chunk whose remainder was handed on (o.n_sub > 0) ends where its remainder
-// begins.  Returns true when early stopping ends the ray in this piece.
+// Where early stopping ends a ray inside a piece (T below stop_T after a
+// tested sample), the piece is walked again from the known transmittance; the
+// rays of the wave that have reached such a piece are walked together.
+// keep: over each piece's result the transmittance and colour prefix in front
+// of it is written, and whether it lies before the early stop (Tlast 1) or not
+// (-1): the prefixes a backward over these pieces differentiates from.
 template <typename T, int K, int VEC, int NL, int V, int SRC>
-__device__ __forceinline__ bool join_piece(const KJob& J, const KSplit& S, int pix, double a, double hi, int k,
-                                           int n, const PieceOut& o, const int4* vp, JoinAcc& A) {
-    if (o.Tlast >= 0.0f && A.Tp * o.Tlast < J.op.stop_T) {
-        // the walk stops inside this piece: walk it again from Tp
-        double lo, up;
-        piece_bounds<SRC>(J, S, pix, a, hi, k, n, lo, up);
-        if (o.n_sub > 0) up = reinterpret_cast<const SubHead*>(S.head2)[o.sub].lo;
-        using Smp = ChunkSampler<T, K, VEC, NL, V>;
+__device__ __forceinline__ void join_ray(const KJob& J, const KSplit& S, int q, bool ray, int m, const ContHead& hd,
+                                         bool keep, JoinAcc& A) {
+    PieceOut* part = reinterpret_cast<PieceOut*>(S.part);
+    PieceOut* part2 = reinterpret_cast<PieceOut*>(S.part2);
+    const SubHead* head2 = reinterpret_cast<const SubHead*>(S.head2);
+    using Smp = ChunkSampler<T, K, VEC, NL, V>;
+    // next chunk j in slot qj; sub-chunk k of n_sub of the chunk before it, in slot qk
+    int j = 0, qj = q, k = 0, n_sub = 0, sub = -1, qk = -1;
+    bool more = ray, done = false;
+    while (true) {
+        bool again = false, is_sub = false;
+        PieceOut o;
+        while (more & !again) {
+            PieceOut* rec;
+            const int4* vp;
+            is_sub = k < n_sub;
+            if (is_sub) {
+                rec = part2 + qk;
+                vp = S.view_part2 + qk;
+                qk = S.info2[qk].z;
+                ++k;
+            } else if (j < m) {
+                rec = part + qj;
+                vp = S.view_part + qj;
+                qj = S.info[qj].z;
+                ++j;
+            } else {
+                more = false;
+                break;
+            }
+            o = *rec;
+            if (!is_sub) {
+                n_sub = o.n_sub;
+                sub = qk = o.sub;
+                k = 0;
+            }
+            if (keep) {
+                PieceOut p = o;
+                p.c0 = A.c[0];
+                p.c1 = A.c[1];
+                p.c2 = A.c[2];
+                p.T = A.Tp;
+                p.Tlast = done ? -1.0f : 1.0f;
+                *rec = p;
+            }
+            if (done) continue;
+            again = (o.Tlast >= 0.0f) & (A.Tp * o.Tlast < J.op.stop_T);
+            if (again) break;
+            A.c[0] = fmaf(A.Tp, o.c0, A.c[0]);
+            A.c[1] = fmaf(A.Tp, o.c1, A.c[1]);
+            A.c[2] = fmaf(A.Tp, o.c2, A.c[2]);
+            if constexpr (V == PO_FWD_VIEW) {
+                const int4 c = *vp;  // ns, steps, cut_smp, cut
+                A.dep = fmaf(A.Tp, o.dep, A.dep);
+                A.ns += c.x - c.z;
+                A.steps += c.y - c.w;
+                A.cut_smp = c.z;
+                A.cut = c.w;
+            }
+            A.Tp = A.Tp * o.T;
+        }
+        if (__ballot(again) == 0ull) break;
+        // the walk stops inside this piece: walk it again from Tp (a chunk
+        // whose remainder was handed on ends where its remainder begins)
         Smp smp;
-        smp.Tl = A.Tp;
         Ray r;
-        int steps = 0;
-        if (piece_setup<SRC>(J, S, pix, lo, up, 0, 1, r)) {
-            fwd_init<T, K, V>(smp, J.tr, J.op, r);
-            extern __shared__ int po_stack[];
-            steps = march(J.tr, r, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
+        bool walk = false;
+        if (again) {
+            smp.Tl = A.Tp;
+            double lo, up;
+            if (is_sub) {
+                const SubHead sh = head2[sub];
+                piece_bounds<SRC>(J, S, hd.pix, sh.lo, sh.hi, k - 1, n_sub, lo, up);
+            } else {
+                piece_bounds<SRC>(J, S, hd.pix, hd.s, walk_end<V, SRC>(J, S, hd.pix), j - 1, m, lo, up);
+                if (n_sub > 0) up = head2[sub].lo;
+            }
+            walk = piece_setup<SRC>(J, S, hd.pix, lo, up, 0, 1, r);
         }
-        A.c[0] += smp.c0;
-        A.c[1] += smp.c1;
-        A.c[2] += smp.c2;
-        A.Tp = smp.Tl;
-        if constexpr (V == PO_FWD_VIEW) {
-            A.dep += smp.dep;
-            A.cut_smp = smp.hit ? 0 : (smp.smp_cut ? 1 : 0);
-            A.cut = (smp.hit || o.n_sub > 0 || smp.cpl) ? 0 : 1;
-            A.ns += smp.ns - A.cut_smp;
-            A.steps += steps - smp.skip0 - A.cut;
+        fwd_init<K, V>(smp, J.tr, J.op, walk, r);
+        extern __shared__ int po_stack[];
+        const int steps = march(J.tr, r, walk, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
+        if (again) {
+            A.c[0] += smp.c0;
+            A.c[1] += smp.c1;
+            A.c[2] += smp.c2;
+            A.Tp = smp.Tl;
+            if constexpr (V == PO_FWD_VIEW) {
+                A.dep += smp.dep;
+                A.cut_smp = smp.hit ? 0 : (smp.smp_cut ? 1 : 0);
+                A.cut = (smp.hit || (!is_sub && n_sub > 0) || smp.cpl) ? 0 : 1;
+                A.ns += smp.ns - A.cut_smp;
+                A.steps += steps - max(smp.skip0, 0) - A.cut;
+            }
+            // (rounding can leave T just above stop_T; then the later pieces still count)
+            done = smp.hit;
+            if (done & !keep) more = false;
         }
-        // (rounding can leave T just above stop_T; then the later pieces still count)
-        return smp.hit;
     }
-    A.c[0] = fmaf(A.Tp, o.c0, A.c[0]);
-    A.c[1] = fmaf(A.Tp, o.c1, A.c[1]);
-    A.c[2] = fmaf(A.Tp, o.c2, A.c[2]);
-    if constexpr (V == PO_FWD_VIEW) {
-        const int4 c = *vp;  // ns, steps, cut_smp, cut
-        A.dep = fmaf(A.Tp, o.dep, A.dep);
-        A.ns += c.x - c.z;
-        A.steps += c.y - c.w;
-        A.cut_smp = c.z;
-        A.cut = c.w;
-    }
-    A.Tp = A.Tp * o.T;
-    return false;
 }
 
 template <typename T, int K, int VEC, int NL, int V, int SRC>
 __global__ __launch_bounds__(kBlock) void k_render_join(KBatch<1> B, KSplit S) {
     const int q = split_slot(S.count, S.region_slots);
-    if (q < 0) return;
-    const int4 in = S.info[q];
-    if (in.x != q) return;  // not the first slot of a ray
-    const int m = in.y >> 8;
-    const ContHead hd = reinterpret_cast<const ContHead*>(S.head)[q];
+    const int4 in = q < 0 ? make_int4(-1, 0, -1, 0) : S.info[q];
+    const bool ray = (q >= 0) & (in.x == q);  // the first slot of a ray
+    if (__ballot(ray) == 0ull) return;
     const KJob& J = B.job[0];
-    PieceOut* part = reinterpret_cast<PieceOut*>(S.part);
-    PieceOut* part2 = reinterpret_cast<PieceOut*>(S.part2);
-    const SubHead* head2 = reinterpret_cast<const SubHead*>(S.head2);
-    const size_t p = (size_t)hd.pix;
-    // the join of a kept ray-list render also writes, over each piece's
-    // result, the transmittance and colour prefix in front of it and whether
-    // it lies before the early stop (Tlast 1) or not (-1): the prefixes its
-    // backward differentiates from (what k_piece_prefix computes otherwise)
-    bool keep = false;
+    ContHead hd;
+    if (ray) hd = reinterpret_cast<const ContHead*>(S.head)[q];
+    const size_t p = ray ? (size_t)hd.pix : 0;
+    bool keep = false;  // a kept ray-list render
     if constexpr (SRC == 1 && V != PO_FWD_VIEW) keep = S.ray_slot != nullptr;
     JoinAcc A;
-    auto prefix = [&](PieceOut* rec, PieceOut o, bool past) {
-        o.c0 = A.c[0];
-        o.c1 = A.c[1];
-        o.c2 = A.c[2];
-        o.T = A.Tp;
-        o.Tlast = past ? -1.0f : 1.0f;
-        *rec = o;
-    };
     A.Tp = hd.T;
     A.c[0] = hd.c0;
     A.c[1] = hd.c1;
@@ -1563,41 +1869,14 @@ __global__ __launch_bounds__(kBlock) void k_render_join(KBatch<1> B, KSplit S) {
     A.dep = 0.0f;
     A.ns = A.steps = A.cut_smp = A.cut = 0;
     if constexpr (V == PO_FWD_VIEW) {
-        if (J.aux) {
+        if (ray && J.aux) {
             A.ns = (int)J.aux[4 * p + 1];
             A.steps = (int)J.aux[4 * p + 2];
             A.dep = J.aux[4 * p + 3];
         }
     }
-    const double end = walk_end<V, SRC>(J, S, hd.pix);
-    bool done = false;
-    int qj = q;
-    for (int j = 0; j < m && (keep || !done); ++j) {
-        const PieceOut o = part[qj];
-        const int qo = qj;
-        qj = S.info[qj].z;
-        if (keep) prefix(part + qo, o, done);
-        if (!done) done = join_piece<T, K, VEC, NL, V, SRC>(J, S, hd.pix, hd.s, end, j, m, o, S.view_part + qo, A);
-        if (o.n_sub > 0 && (keep || !done)) {
-            // the remainder's sub-chunks (bounds read only to walk one again)
-            double slo = 0.0, shi = 0.0;
-            int qk = o.sub;
-            for (int k = 0; k < o.n_sub && (keep || !done); ++k) {
-                const PieceOut o2 = part2[qk];
-                const int qo2 = qk;
-                qk = S.info2[qk].z;
-                if (keep) prefix(part2 + qo2, o2, done);
-                if (done) continue;
-                if (o2.Tlast >= 0.0f && A.Tp * o2.Tlast < J.op.stop_T && shi == 0.0) {
-                    const SubHead sh = head2[o.sub];
-                    slo = sh.lo;
-                    shi = sh.hi;
-                }
-                done = join_piece<T, K, VEC, NL, V, SRC>(J, S, hd.pix, slo, shi, k, o.n_sub, o2, S.view_part2 + qo2,
-                                                         A);
-            }
-        }
-    }
+    join_ray<T, K, VEC, NL, V, SRC>(J, S, q, ray, in.y >> 8, hd, keep, A);
+    if (!ray) return;
     J.rgb[3 * p + 0] = fmaf(A.Tp, J.op.bg[0], A.c[0]);
     J.rgb[3 * p + 1] = fmaf(A.Tp, J.op.bg[1], A.c[1]);
     J.rgb[3 * p + 2] = fmaf(A.Tp, J.op.bg[2], A.c[2]);
@@ -1616,94 +1895,109 @@ __global__ __launch_bounds__(kBlock) void k_render_join(KBatch<1> B, KSplit S) {
 // first pass; this second pass keeps the prefix P_i of w_k c_k, so that
 // dC/dsigma_i = delta_i (c_i T_{i+1} - (C - P_i)) (zero where the raw density
 // is <= 0) and dC/dk = w_i c_i (1 - c_i) Y, contracted with dL/dC and added
-// to the leaf gradients with float atomics.  The density gradient is added
-// by its own lane; the 3K coefficient gradients of the wave's samples are
-// staged in LDS and added cooperatively (flush), so that one atomic
-// instruction covers one or two records instead of 64 scattered ones.
+// to the leaf gradients with float atomics, once for every 64 samples of the
+// wave: the density gradients by the samples' lanes, the 3K coefficient
+// gradients z_c Y_k by all lanes together, consecutive lanes taking consecutive
+// coefficients, so that one atomic instruction covers whole records.  Atomics
+// complete in order with the loads behind them, so adding each step's samples
+// at once held up the next step by an L2 round trip.
 template <int K, int VEC, int NL>
-struct BwdSampler {
-    static constexpr int NW = Words<float, NL>::N;
+struct BwdSampler : Records<float, K, VEC, NL> {
     static constexpr bool kClip = false;
+    static constexpr bool kView = false;
+    static constexpr bool kQueued = true;
     static constexpr int NE = 3 * K;
-    static constexpr int SW = (NE + 3) / 4 * 4;  // LDS slot: one sample's products
-    __amdgpu_buffer_rsrc_t sig, shb;
-    uint32_t sig_end, sh_end, rec_bytes;
+    static constexpr uint32_t kNone = 0xffffffffu;  // Sample::info: no gradient
     int stride;
     float stopT;
-    float Y[K];
     float g0, g1, g2, C0, C1, C2;
     float* gsig;
     float* gsh;
-    float* sprod;
-    int* sleaf;
     float Tl = 1.0f, P0 = 0.0f, P1 = 0.0f, P2 = 0.0f;
-    bool has = false;
-    float z0, z1, z2;
-    // in flight
-    int leaf;
-    float raw, delta;
-    uint32_t w[NW];
 
-    __device__ __forceinline__ void issue(int l, float d, float) {
-        leaf = l;
-        raw = sigma_buf(sig, l < 0 ? sig_end : (uint32_t)l * 4u, (float*)nullptr);
-        load_words_buf<float, NL, VEC>(shb, l < 0 ? sh_end : (uint32_t)l * rec_bytes, w);
-        delta = d;
+    __device__ __forceinline__ void shade(uint32_t head, uint32_t n) {
+        Sample* q = sample_queue() + (head + threadIdx.x) % kQueue;
+        const bool on = threadIdx.x < n;
+        float col[3];
+        const float s = this->eval(on, q->leaf, q->info & 63u, col);
+        shaded()[threadIdx.x] = make_float4(s > 0.0f ? __expf(-(s * q->delta)) : -1.0f, col[0], col[1], col[2]);
     }
-    __device__ __forceinline__ bool consume() {
-        const float s = fmaxf(raw, 0.0f);
-        if (!(s > 0.0f)) return false;  // no density: zero weight, and dC/dsigma is masked
-        const float ex = __expf(-(s * delta));
+    // Leaves {density gradient, z_0, z_1, z_2} in the place of the sample's
+    // result (opacity -1: no density, zero weight, and dC/dsigma is masked).
+    __device__ __forceinline__ bool composite(const Sample& q, uint32_t, uint32_t at) {
+        const float4 v = shaded()[at];
+        if (v.x < 0.0f) return false;
+        const float ex = v.x, c0 = v.y, c1 = v.z, c2 = v.w;
         const float wgt = Tl * (1.0f - ex);
         const float Tn = Tl * ex;
-        const float c0 = sigmoid(dot_channel<float, K>(w, 0, Y));
-        const float c1 = sigmoid(dot_channel<float, K>(w, K, Y));
-        const float c2 = sigmoid(dot_channel<float, K>(w, 2 * K, Y));
         P0 = fmaf(wgt, c0, P0);
         P1 = fmaf(wgt, c1, P1);
         P2 = fmaf(wgt, c2, P2);
         float gs = g0 * (c0 * Tn - (C0 - P0));
         gs = fmaf(g1, c1 * Tn - (C1 - P1), gs);
         gs = fmaf(g2, c2 * Tn - (C2 - P2), gs);
-        atomicAdd(gsig + leaf, gs * delta);
-        z0 = g0 * wgt * c0 * (1.0f - c0);
-        z1 = g1 * wgt * c1 * (1.0f - c1);
-        z2 = g2 * wgt * c2 * (1.0f - c2);
-        has = true;
+        shaded()[at] = make_float4(gs * q.delta, g0 * wgt * c0 * (1.0f - c0), g1 * wgt * c1 * (1.0f - c1),
+                                   g2 * wgt * c2 * (1.0f - c2));
+        staged()[at] = q.info & 63u;
         Tl = Tn;
         return Tl < stopT;
     }
-    // Runs with every lane still walking: the lanes that composited a sample
-    // write its 3K coefficient gradients to consecutive LDS slots, then all
-    // active lanes add them to the leaves, consecutive lanes taking
-    // consecutive coefficients of a record.
-    __device__ __forceinline__ void flush() {
-        const uint64_t m = __ballot(has);
-        if (m == 0) return;
-        if (has) {
-            const int slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            float* dst = sprod + slot * SW;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                dst[k] = z0 * Y[k];
-                dst[K + k] = z1 * Y[k];
-                dst[2 * K + k] = z2 * Y[k];
-            }
-            sleaf[slot] = leaf;
-            has = false;
+    // The ray's lane of every shaded sample with a gradient, else kNone.
+    static __device__ __forceinline__ uint32_t* staged() {
+        __shared__ uint32_t s_staged[kBlock];
+        return s_staged;
+    }
+    __device__ __forceinline__ void finish(uint32_t head, uint32_t n) {
+        const uint32_t lane = threadIdx.x;
+        const uint32_t src = lane < n ? staged()[lane] : kNone;
+        const uint32_t leaf = sample_queue()[(head + lane) % kQueue].leaf;
+        const uint64_t m = __ballot(src != kNone);
+        // compacted: {leaf, lane of the ray, number of the sample} of the samples with a gradient
+        __shared__ uint32_t s_leaf[kBlock], s_at[kBlock];
+        if (src != kNone) {
+            atomicAdd(gsig + leaf, shaded()[lane].x);
+            const int i = rank_in(m);
+            s_leaf[i] = leaf;
+            s_at[i] = src | lane << 8;
         }
         __builtin_amdgcn_wave_barrier();
-        const uint64_t act = __ballot(1);
-        const int na = __popcll(act);
-        const int r = __builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
-        const int total = __popcll(m) * SW;
-        for (int it = r; it < total; it += na) {
-            const int j = it / SW, e = it - j * SW;
-            if (e < NE) atomicAdd(gsh + (size_t)sleaf[j] * stride + e, sprod[it]);
+        const float* Z = reinterpret_cast<const float*>(shaded());
+        const float* Y = reinterpret_cast<const float*>(basis_values<K>());
+        const uint32_t total = (uint32_t)__popcll(m) * NE;
+        for (uint32_t it = lane; it < total; it += kBlock) {
+            const uint32_t i = it / NE, e = it - i * NE, c = e / K, k = e - c * K;
+            const uint32_t a = s_at[i];
+            atomicAdd(gsh + (size_t)s_leaf[i] * stride + e, Z[4 * (a >> 8) + 1 + c] * Y[4 * ((k >> 2) * kBlock + (a & 255u)) + (k & 3)]);
         }
         __builtin_amdgcn_wave_barrier();
+        staged()[lane] = kNone;
     }
 };
+
+// Binds a backward sampler to a tree (every lane), and to ray i: its incoming
+// gradient and colour, and the basis of its direction.  Returns whether the
+// ray has a gradient.
+template <int K, class Smp>
+__device__ __forceinline__ bool bwd_init(Smp& smp, const KTree& tr, const KOpts& op, bool ray, const Ray& r, size_t i,
+                                         const float* __restrict__ rgb_fwd, const float* __restrict__ grad,
+                                         float* gsig, float* gsh) {
+    smp.bind(tr);
+    smp.stride = tr.stride;
+    smp.stopT = op.stop_T;
+    smp.gsig = gsig;
+    smp.gsh = gsh;
+    Smp::staged()[threadIdx.x] = Smp::kNone;
+    if (!ray) return false;
+    smp.g0 = grad[3 * i];
+    smp.g1 = grad[3 * i + 1];
+    smp.g2 = grad[3 * i + 2];
+    if (smp.g0 == 0.0f && smp.g1 == 0.0f && smp.g2 == 0.0f) return false;
+    smp.C0 = rgb_fwd[3 * i];
+    smp.C1 = rgb_fwd[3 * i + 1];
+    smp.C2 = rgb_fwd[3 * i + 2];
+    init_basis<K, PO_FWD_VIEW>(tr, op, r);
+    return true;
+}
 
 // Backward kernel: replays the forward walk of each ray.
 template <int K, int VEC, int NL>
@@ -1716,35 +2010,17 @@ __global__ __launch_bounds__(kBlock) void k_backward(KTree tr, int64_t n, int64_
     const int64_t blk = xcd_swizzle(blockIdx.x, n_blocks);
     if (blk < 0) return;
     const int64_t i = blk * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const double ro[3] = {(double)o[3 * i], (double)o[3 * i + 1], (double)o[3 * i + 2]};
-    const double rd[3] = {(double)d[3 * i], (double)d[3 * i + 1], (double)d[3 * i + 2]};
     Ray r;
-    if (!ray_setup(tr, ro, rd, r)) return;
+    bool ray = i < n;
+    if (ray) {
+        const double ro[3] = {(double)o[3 * i], (double)o[3 * i + 1], (double)o[3 * i + 2]};
+        const double rd[3] = {(double)d[3 * i], (double)d[3 * i + 1], (double)d[3 * i + 2]};
+        ray = ray_setup(tr, ro, rd, r);
+    }
     BwdSampler<K, VEC, NL> smp;
-    smp.g0 = grad[3 * i];
-    smp.g1 = grad[3 * i + 1];
-    smp.g2 = grad[3 * i + 2];
-    if (smp.g0 == 0.0f && smp.g1 == 0.0f && smp.g2 == 0.0f) return;
-    smp.C0 = rgb_fwd[3 * i];
-    smp.C1 = rgb_fwd[3 * i + 1];
-    smp.C2 = rgb_fwd[3 * i + 2];
-    smp.sig = raw_rsrc(tr.sigma, tr.sigma_bytes);
-    smp.shb = raw_rsrc(tr.sh, tr.sh_bytes);
-    smp.sig_end = tr.sigma_bytes;
-    smp.sh_end = tr.sh_bytes;
-    smp.rec_bytes = (uint32_t)tr.stride * 4u;
-    smp.stride = tr.stride;
-    smp.stopT = op.stop_T;
-    smp.gsig = gsig;
-    smp.gsh = gsh;
-    __shared__ float s_prod[kBlock * BwdSampler<K, VEC, NL>::SW];
-    __shared__ int s_leaf[kBlock];
-    smp.sprod = s_prod;
-    smp.sleaf = s_leaf;
-    colour_basis<K>(tr, r.dn[0], r.dn[1], r.dn[2], smp.Y);
+    ray = bwd_init<K>(smp, tr, op, ray, r, (size_t)i, rgb_fwd, grad, gsig, gsh);
     extern __shared__ int po_stack[];
-    march(tr, r, op.max_steps, kNoCap, exact_cells(op), po_stack + threadIdx.x, smp);
+    march(tr, r, ray, op.max_steps, kNoCap, exact_cells(op), po_stack + threadIdx.x, smp);
 }
 
 // ---------------------------------------------------------------------------
@@ -1766,30 +2042,6 @@ __global__ __launch_bounds__(kBlock) void k_backward(KTree tr, int64_t n, int64_
 //   k_backward_pieces     the backward of every piece before the stop, from
 //                         its T and P (chunks, then sub-chunks).
 // ---------------------------------------------------------------------------
-template <int K, class Smp>
-__device__ __forceinline__ void bwd_init(Smp& smp, const KTree& tr, const KOpts& op, const Ray& r, size_t i,
-                                         const float* __restrict__ rgb_fwd, const float* __restrict__ grad,
-                                         float* gsig, float* gsh, float* sprod, int* sleaf) {
-    smp.g0 = grad[3 * i];
-    smp.g1 = grad[3 * i + 1];
-    smp.g2 = grad[3 * i + 2];
-    smp.C0 = rgb_fwd[3 * i];
-    smp.C1 = rgb_fwd[3 * i + 1];
-    smp.C2 = rgb_fwd[3 * i + 2];
-    smp.sig = raw_rsrc(tr.sigma, tr.sigma_bytes);
-    smp.shb = raw_rsrc(tr.sh, tr.sh_bytes);
-    smp.sig_end = tr.sigma_bytes;
-    smp.sh_end = tr.sh_bytes;
-    smp.rec_bytes = (uint32_t)tr.stride * 4u;
-    smp.stride = tr.stride;
-    smp.stopT = op.stop_T;
-    smp.gsig = gsig;
-    smp.gsh = gsh;
-    smp.sprod = sprod;
-    smp.sleaf = sleaf;
-    colour_basis<K>(tr, r.dn[0], r.dn[1], r.dn[2], smp.Y);
-}
-
 template <int K, int VEC, int NL>
 __global__ __launch_bounds__(kBlock) void k_backward_split(KBatch<1> B, KSplit S, const float* __restrict__ rgb_fwd,
                                                            const float* __restrict__ grad, float* __restrict__ gsig,
@@ -1801,34 +2053,30 @@ __global__ __launch_bounds__(kBlock) void k_backward_split(KBatch<1> B, KSplit S
     const KTree& tr = J.tr;
     using Smp = BwdSampler<K, VEC, NL>;
     Smp smp;
-    __shared__ float s_prod[kBlock * Smp::SW];
-    __shared__ int s_leaf[kBlock];
     extern __shared__ int po_stack[];
     int* stk = po_stack + threadIdx.x;
     Ray r;
     int want = 0, steps = 0;
-    bool live = false;
-    if (i < S.n_rays) {
+    bool live = i < S.n_rays;
+    if (live) {
         double ro[3], rd[3];
         ray_of<1>(J, S, (int)i, ro, rd);
-        if (ray_setup(tr, ro, rd, r)) {
-            bwd_init<K>(smp, tr, J.op, r, (size_t)i, rgb_fwd, grad, gsig, gsh, s_prod, s_leaf);
-            live = !(smp.g0 == 0.0f && smp.g1 == 0.0f && smp.g2 == 0.0f);
-        }
+        live = ray_setup(tr, ro, rd, r);
     }
-    if (live) {
-        const double s_first = r.s;
-        steps = march<Smp, true>(tr, r, J.op.max_steps, S.split_cap, S.exact, stk, smp);
-        if (r.more) {
+    live = bwd_init<K>(smp, tr, J.op, live, r, (size_t)i, rgb_fwd, grad, gsig, gsh);
+    if (live) *walk_range() = make_double2(r.s, r.s_exit);
+    // the second pass finishes the walks whose region is full
+    for (int pass = 0; pass < 2; ++pass) {
+        steps += march<Smp, true>(tr, r, live, J.op.max_steps - steps, pass ? kNoCap : S.split_cap, S.exact, stk, smp);
+        if (live & r.more) {
             if (steps >= J.op.max_steps)
                 atomicAdd(&g_po_errors, 1ull);
             else
-                want = pieces_wanted(r, s_first, S, S.chunk_target);
+                want = pieces_wanted(r, S, S.chunk_target);
         }
-    }
-    const int h = claim_pieces(S.count, S.info, claim_region(), want, S.region_slots);
-    if (want > 0) {
-        if (h >= 0) {
+        if (pass) break;
+        const int h = claim_pieces(S.count, S.info, claim_region(), want, S.region_slots);
+        if ((want > 0) & (h >= 0)) {
             ContHead hd;
             hd.s = r.s;
             hd.T = smp.Tl;
@@ -1838,10 +2086,9 @@ __global__ __launch_bounds__(kBlock) void k_backward_split(KBatch<1> B, KSplit S
             hd.pix = (int)i;
             hd.pad = 0;
             reinterpret_cast<ContHead*>(S.head)[h] = hd;
-        } else {
-            // region full: finish here
-            march<Smp>(tr, r, J.op.max_steps - steps, kNoCap, S.exact, stk, smp);
         }
+        live = (want > 0) & (h < 0);
+        if (__ballot(live) == 0ull) break;
     }
 }
 
@@ -1864,85 +2111,38 @@ __global__ __launch_bounds__(kBlock) void k_backward_first_kept(KBatch<1> B, KSp
     const KTree& tr = J.tr;
     using Smp = BwdSampler<K, VEC, NL>;
     Smp smp;
-    __shared__ float s_prod[kBlock * Smp::SW];
-    __shared__ int s_leaf[kBlock];
     extern __shared__ int po_stack[];
     Ray r;
-    bool live = false, handed = false;
-    if (i < S.n_rays) {
+    bool live = i < S.n_rays, handed = false;
+    if (live) {
         double ro[3], rd[3];
         ray_of<1>(J, S, (int)i, ro, rd);
-        if (ray_setup(tr, ro, rd, r)) {
-            bwd_init<K>(smp, tr, J.op, r, (size_t)i, rgb_fwd, grad, gsig, gsh, s_prod, s_leaf);
-            live = !(smp.g0 == 0.0f && smp.g1 == 0.0f && smp.g2 == 0.0f);
-            handed = S.ray_slot[i] >= 0;
-        }
+        handed = S.ray_slot[i] >= 0;
+        live = ray_setup(tr, ro, rd, r);
     }
-    if (live) {
-        const int steps = march<Smp, true>(tr, r, J.op.max_steps, handed ? S.split_cap : kNoCap, S.exact,
-                                           po_stack + threadIdx.x, smp);
-        if (r.more & (steps >= J.op.max_steps)) atomicAdd(&g_po_errors, 1ull);  // the step cap proper
-    }
+    live = bwd_init<K>(smp, tr, J.op, live, r, (size_t)i, rgb_fwd, grad, gsig, gsh);
+    const int steps = march<Smp, true>(tr, r, live, J.op.max_steps, handed ? S.split_cap : kNoCap, S.exact,
+                                       po_stack + threadIdx.x, smp);
+    if (live & r.more & (steps >= J.op.max_steps)) atomicAdd(&g_po_errors, 1ull);  // the step cap proper
 }
 
-// Prefix of one piece: its forward result o is replaced by (P, T) in front
-// of it and whether it lies before the early stop (Tlast 1) or not (-1).
-template <int K, int VEC, int NL, int V>
-__device__ __forceinline__ void prefix_piece(const KJob& J, const KSplit& S, int pix, double a, double hi, int k,
-                                             int n, PieceOut* rec, float& Tp, float (&P)[3], bool& done) {
-    const PieceOut o = *rec;
-    PieceOut w = o;
-    w.c0 = P[0];
-    w.c1 = P[1];
-    w.c2 = P[2];
-    w.T = Tp;
-    w.Tlast = done ? -1.0f : 1.0f;
-    *rec = w;
-    if (!done) {
-        JoinAcc A;
-        A.Tp = Tp;
-        A.c[0] = P[0];
-        A.c[1] = P[1];
-        A.c[2] = P[2];
-        A.dep = 0.0f;
-        A.ns = A.steps = A.cut_smp = A.cut = 0;
-        done = join_piece<float, K, VEC, NL, V, 1>(J, S, pix, a, hi, k, n, o, nullptr, A);
-        Tp = A.Tp;
-        P[0] = A.c[0];
-        P[1] = A.c[1];
-        P[2] = A.c[2];
-    }
-}
-
+// The prefixes of a ray's pieces, as the join of a kept render writes them.
 template <int K, int VEC, int NL, int V>
 __global__ __launch_bounds__(kBlock) void k_piece_prefix(KBatch<1> B, KSplit S) {
     const int q = split_slot(S.count, S.region_slots);
-    if (q < 0) return;
-    const int4 in = S.info[q];
-    if (in.x != q) return;
-    const int m = in.y >> 8;
-    const ContHead hd = reinterpret_cast<const ContHead*>(S.head)[q];
-    const KJob& J = B.job[0];
-    PieceOut* part = reinterpret_cast<PieceOut*>(S.part);
-    PieceOut* part2 = reinterpret_cast<PieceOut*>(S.part2);
-    const SubHead* head2 = reinterpret_cast<const SubHead*>(S.head2);
-    float Tp = hd.T;
-    float P[3] = {hd.c0, hd.c1, hd.c2};
-    bool done = false;
-    int qj = q;
-    for (int j = 0; j < m; ++j) {
-        const int n_sub = part[qj].n_sub, sub = part[qj].sub;
-        prefix_piece<K, VEC, NL, V>(J, S, hd.pix, hd.s, 1e300, j, m, part + qj, Tp, P, done);
-        if (n_sub > 0) {
-            const SubHead sh = head2[sub];
-            int qk = sub;
-            for (int k = 0; k < n_sub; ++k) {
-                prefix_piece<K, VEC, NL, V>(J, S, hd.pix, sh.lo, sh.hi, k, n_sub, part2 + qk, Tp, P, done);
-                qk = S.info2[qk].z;
-            }
-        }
-        qj = S.info[qj].z;
-    }
+    const int4 in = q < 0 ? make_int4(-1, 0, -1, 0) : S.info[q];
+    const bool ray = (q >= 0) & (in.x == q);
+    if (__ballot(ray) == 0ull) return;
+    ContHead hd;
+    if (ray) hd = reinterpret_cast<const ContHead*>(S.head)[q];
+    JoinAcc A;
+    A.Tp = hd.T;
+    A.c[0] = hd.c0;
+    A.c[1] = hd.c1;
+    A.c[2] = hd.c2;
+    A.dep = 0.0f;
+    A.ns = A.steps = A.cut_smp = A.cut = 0;
+    join_ray<float, K, VEC, NL, V, 1>(B.job[0], S, q, ray, in.y >> 8, hd, true, A);
 }
 
 // The first kSplitRegions * region_slots / kBlock workgroups take the walked parts of the
@@ -1955,41 +2155,41 @@ __global__ __launch_bounds__(kBlock) void k_backward_pieces(KBatch<1> B, KSplit 
     const int half = kSplitRegions * (S.region_slots / kBlock);
     const bool sub = blockIdx.x >= (unsigned)half;
     const int q = split_slot(sub ? S.count2 : S.count, S.region_slots, sub ? half : 0);
-    if (q < 0) return;
-    const int4 in = (sub ? S.info2 : S.info)[q];
-    if (in.x < 0) return;
-    const PieceOut o = reinterpret_cast<const PieceOut*>(sub ? S.part2 : S.part)[q];
-    if (o.Tlast < 0.0f) return;  // behind the early stop
-    const KJob& J = B.job[0];
-    const int k = in.y & 255, n = in.y >> 8;
-    int idx;
-    Ray r;
-    bool ok;
-    if (sub) {
-        const SubHead sh = reinterpret_cast<const SubHead*>(S.head2)[in.x];
-        idx = sh.pix;
-        ok = piece_setup<1>(J, S, idx, sh.lo, sh.hi, k, n, r);
-    } else {
-        const ContHead hd = reinterpret_cast<const ContHead*>(S.head)[in.x];
-        idx = hd.pix;
-        double lo, up;
-        piece_bounds<1>(J, S, idx, hd.s, 1e300, k, n, lo, up);
-        if (o.n_sub > 0) up = reinterpret_cast<const SubHead*>(S.head2)[o.sub].lo;
-        ok = piece_setup<1>(J, S, idx, lo, up, 0, 1, r);
+    const int4 in = q < 0 ? make_int4(-1, 0, -1, 0) : (sub ? S.info2 : S.info)[q];
+    PieceOut o;
+    bool live = in.x >= 0;
+    if (live) {
+        o = reinterpret_cast<const PieceOut*>(sub ? S.part2 : S.part)[q];
+        live = !(o.Tlast < 0.0f);  // not behind the early stop
     }
-    if (!ok) return;
+    if (__ballot(live) == 0ull) return;
+    const KJob& J = B.job[0];
+    int idx = 0;
+    Ray r;
+    if (live) {
+        const int k = in.y & 255, n = in.y >> 8;
+        if (sub) {
+            const SubHead sh = reinterpret_cast<const SubHead*>(S.head2)[in.x];
+            idx = sh.pix;
+            live = piece_setup<1>(J, S, idx, sh.lo, sh.hi, k, n, r);
+        } else {
+            const ContHead hd = reinterpret_cast<const ContHead*>(S.head)[in.x];
+            idx = hd.pix;
+            double lo, up;
+            piece_bounds<1>(J, S, idx, hd.s, 1e300, k, n, lo, up);
+            if (o.n_sub > 0) up = reinterpret_cast<const SubHead*>(S.head2)[o.sub].lo;
+            live = piece_setup<1>(J, S, idx, lo, up, 0, 1, r);
+        }
+    }
     using Smp = ChunkOf<BwdSampler<K, VEC, NL>>;
     Smp smp;
-    __shared__ float s_prod[kBlock * BwdSampler<K, VEC, NL>::SW];
-    __shared__ int s_leaf[kBlock];
-    bwd_init<K>(smp, J.tr, J.op, r, (size_t)idx, rgb_fwd, grad, gsig, gsh, s_prod, s_leaf);
-    if (smp.g0 == 0.0f && smp.g1 == 0.0f && smp.g2 == 0.0f) return;  // (a kept render's rays without gradient)
+    live = bwd_init<K>(smp, J.tr, J.op, live, r, (size_t)idx, rgb_fwd, grad, gsig, gsh);
     smp.Tl = o.T;
     smp.P0 = o.c0;
     smp.P1 = o.c1;
     smp.P2 = o.c2;
     extern __shared__ int po_stack[];
-    march(J.tr, r, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
+    march(J.tr, r, live, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
 }
 
 // Visibility filter of the conversion (Sec. 4.2, "Filtering"): alpha
@@ -2001,6 +2201,8 @@ __global__ __launch_bounds__(kBlock) void k_backward_pieces(KBatch<1> B, KSplit 
 template <typename T, int MODE>
 struct WeightSampler {
     static constexpr bool kClip = false;
+    static constexpr bool kView = false;
+    static constexpr bool kQueued = false;
     __amdgpu_buffer_rsrc_t sig;
     uint32_t sig_end;
     float stopT;
@@ -2008,16 +2210,16 @@ struct WeightSampler {
     float Tl = 1.0f;
     // in flight
     int leaf;
-    float raw, delta;
+    uint32_t raw;
+    float delta;
 
-    __device__ __forceinline__ void issue(int l, float d, float) {
+    __device__ __forceinline__ void issue(int l, float d, float, bool) {
         leaf = l;
         raw = sigma_buf(sig, l < 0 ? sig_end : (uint32_t)l * (uint32_t)sizeof(T), (T*)nullptr);
         delta = d;
     }
-    __device__ __forceinline__ void flush() {}
     __device__ __forceinline__ bool consume() {
-        const float s = fmaxf(raw, 0.0f);
+        const float s = fmaxf(sigma_of<T>(raw), 0.0f);
         if (!(s > 0.0f)) return false;
         const float ex = __expf(-(s * delta));
         const float al = 1.0f - ex;
@@ -2040,58 +2242,29 @@ __global__ __launch_bounds__(kBlock) void k_leaf_weights(KTree tr, KCam cam, KOp
     const int lane = threadIdx.x;
     const int px = (tile % tiles_x) * 16 + (quad & 1) * 8 + (lane & 7);
     const int py = (tile / tiles_x) * 16 + (quad >> 1) * 8 + (lane >> 3);
-    if (px >= cam.W || py >= cam.H) return;
+    const bool valid = (px < cam.W) & (py < cam.H);
     double ro[3], rd[3];
     pixel_ray(cam, px, py, ro, rd);
-    float Tr = 1.0f;
     Ray r;
-    if (ray_setup(tr, ro, rd, r)) {
-        WeightSampler<T, MODE> smp;
-        smp.sig = raw_rsrc(tr.sigma, tr.sigma_bytes);
-        smp.sig_end = tr.sigma_bytes;
-        smp.stopT = op.stop_T;
-        smp.wt = wt;
-        extern __shared__ int po_stack[];
-        march(tr, r, op.max_steps, kNoCap, exact_cells(op), po_stack + threadIdx.x, smp);
-        Tr = smp.Tl;
-    }
-    if (alpha) alpha[(size_t)py * cam.W + px] = 1.0f - Tr;
+    const bool walk = valid && ray_setup(tr, ro, rd, r);
+    WeightSampler<T, MODE> smp;
+    smp.sig_end = held(tr.sigma_bytes);
+    smp.sig = raw_rsrc(held(tr.sigma), smp.sig_end);
+    smp.stopT = op.stop_T;
+    smp.wt = wt;
+    extern __shared__ int po_stack[];
+    march(tr, r, walk, op.max_steps, kNoCap, exact_cells(op), po_stack + threadIdx.x, smp);
+    if (valid && alpha) alpha[(size_t)py * cam.W + px] = 1.0f - smp.Tl;
 }
 
-// Traversal statistics of a camera render: the plain walk with a sampler
+// Traversal statistics of a camera render: the walk of the octree's own cells
 // that gathers only the densities (the early stop depends on nothing else;
 // its transmittance arithmetic is the render's, so it stops at the same
 // sample) and counts, per ray, the data samples (segments of positive length
 // in data leaves, as the aux output counts them), the cells visited and the
-// child entries read from memory.  Sums over the image go to sums[4] =
+// child entries that a descent from the deepest ancestor shared with the cell
+// before reads.  Sums over the image go to sums[4] =
 // {rays, samples, cells, child-entry loads}, one atomic per wave and counter.
-template <typename T>
-struct StatSampler {
-    static constexpr bool kClip = false;
-    static constexpr bool kCountLoads = true;
-    __amdgpu_buffer_rsrc_t sig;
-    uint32_t sig_end;
-    float stopT;
-    float Tl = 1.0f;
-    int ns = 0;
-    int loads = 0;
-    // in flight
-    float raw, delta;
-
-    __device__ __forceinline__ void issue(int l, float d, float) {
-        raw = sigma_buf(sig, l < 0 ? sig_end : (uint32_t)l * (uint32_t)sizeof(T), (T*)nullptr);
-        delta = d;
-    }
-    __device__ __forceinline__ void flush() {}
-    __device__ __forceinline__ bool consume() {
-        ++ns;
-        const float s = fmaxf(raw, 0.0f);
-        if (!(s > 0.0f)) return false;
-        Tl = Tl * __expf(-(s * delta));
-        return Tl < stopT;
-    }
-};
-
 // SRC 0: the pixel rays of cam (16x16 tiles of four 8x8 waves); SRC 1: the
 // n rays (o, d), 64 per wave.
 template <typename T, int SRC>
@@ -2125,15 +2298,51 @@ __global__ __launch_bounds__(kBlock) void k_traversal_stats(KTree tr, KCam cam, 
     if (valid) {
         Ray r;
         if (ray_setup(tr, ro, rd, r)) {
-            StatSampler<T> smp;
-            smp.sig = raw_rsrc(tr.sigma, tr.sigma_bytes);
-            smp.sig_end = tr.sigma_bytes;
-            smp.stopT = op.stop_T;
+            const __amdgpu_buffer_rsrc_t sig = raw_rsrc(tr.sigma, tr.sigma_bytes);
             extern __shared__ int po_stack[];
-            v[2] = 
-                (unsigned long long)march(tr, r, op.max_steps, kNoCap, true, po_stack + threadIdx.x, smp);
-            v[1] = (unsigned long long)smp.ns;
-            v[3] = (unsigned long long)smp.loads;
+            int* stk = po_stack + threadIdx.x;
+            Walker<false, false> w;
+            const Index ix(tr);
+            w.start(ix, r, stk);
+            const int D = tr.depth(), M = tr.brick_level();
+            // la: level the descent to the cell starts from; was_in: the cell
+            // before lay in a brick
+            int steps = 0, ns = 0, loads = 0, la = 0;
+            bool was_in = false, pending = false, bad = false;
+            uint32_t raw = 0;
+            float Tl = 1.0f, delta = 0.0f;
+            while (true) {
+                ++steps;
+                const int from[3] = {r.c[0], r.c[1], r.c[2]};
+                const Cell c = w.step(ix, r, true, steps >= op.max_steps, false, stk);
+                const int lvl = D - c.u;
+                loads += (was_in & (la >= M)) ? 1 : (lvl <= M ? lvl - la : M - la + 1);
+                was_in = lvl > M;
+                la = D - 32 + __clz((from[0] ^ r.c[0]) | (from[1] ^ r.c[1]) | (from[2] ^ r.c[2]));
+                bad |= r.more;
+                // the previous sample is composited one cell later, as the
+                // render counts it
+                bool stop = false;
+                if (pending) {
+                    ++ns;
+                    const float s = fmaxf(sigma_of<T>(raw), 0.0f);
+                    if (s > 0.0f) {
+                        Tl = Tl * __expf(-(s * delta));
+                        stop = Tl < op.stop_T;
+                    }
+                }
+                pending = !stop & (c.leaf >= 0) & (c.delta > 0.0f);
+                if (pending) {
+                    raw = sigma_buf(sig, (uint32_t)c.leaf * (uint32_t)sizeof(T), (T*)nullptr);
+                    delta = c.delta;
+                }
+                if (c.last | stop) break;
+            }
+            if (pending) ++ns;
+            if (bad | (w.bad != 0)) atomicAdd(&g_po_errors, 1ull);
+            v[2] = (unsigned long long)steps;
+            v[1] = (unsigned long long)ns;
+            v[3] = (unsigned long long)loads;
         }
     }
 #pragma unroll
@@ -2253,17 +2462,19 @@ __device__ __forceinline__ void grow_box(int (&lo)[3], int (&hi)[3], int n, int 
     }
 }
 
-// Entry of an empty cell c whose empty octree cube lies `up` levels higher,
-// inside the empty box [lo, hi].
-__device__ __forceinline__ int32_t index_entry_box(const int (&c)[3], const int (&lo)[3], const int (&hi)[3], int up) {
-    uint32_t e = 0x80000000u | (uint32_t)up << kIdxUpShift;
+// Entry of an empty cell c (of edge 2^unit) whose empty octree cube lies `up`
+// levels higher, inside the empty box [lo, hi].
+__device__ __forceinline__ int32_t index_entry_box(const int (&c)[3], const int (&lo)[3], const int (&hi)[3], int up,
+                                                   int unit) {
+    uint32_t e = 0x80000000u | (uint32_t)unit << kIdxUnitShift | (uint32_t)up << kIdxUpShift;
 #pragma unroll
     for (int k = 0; k < 3; ++k)
         e |= (uint32_t)min(c[k] - lo[k], 15) << (8 * k) | (uint32_t)min(hi[k] - c[k], 15) << (8 * k + 4);
     return (int32_t)e;
 }
 
-// One wave per brick: the boxes of its empty cells, inside the brick.  The
+// One wave per brick: the boxes of its empty cells, inside the brick, and its
+// entries from the order of the host's child slots to x, y, z.  The
 // brick's occupancy is held as eight 64-bit masks (one per x, bit 8 y + z), so
 // a layer is tested in one to eight ANDs.
 __global__ __launch_bounds__(kBlock) void k_index_bricks(int32_t* __restrict__ bricks) {
@@ -2295,7 +2506,11 @@ __global__ __launch_bounds__(kBlock) void k_index_bricks(int32_t* __restrict__ b
     };
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        if ((v[i] >> 2) != 0) continue;
+        int32_t* out = B + (cx[i][0] << 6 | cx[i][1] << 3 | cx[i][2]);
+        if ((v[i] >> 2) != 0) {
+            *out = v[i];
+            continue;
+        }
         const int up = v[i] & 3, w = (1 << up) - 1;
         int lo[3], hi[3];
 #pragma unroll
@@ -2304,14 +2519,14 @@ __global__ __launch_bounds__(kBlock) void k_index_bricks(int32_t* __restrict__ b
             hi[k] = cx[i][k] | w;
         }
         grow_box(lo, hi, 8, 8, empty);
-        B[i * 64 + lane] = index_entry_box(cx[i], lo, hi, up);
+        *out = index_entry_box(cx[i], lo, hi, up, 0);
     }
 }
 
 // One thread per grid cell: descends the host's nodes to the cell's leaf,
 // empty cube, brick or level-G node.  A leaf entry of the nodes there is
 // -(number in the coarse table) - 1.  Empty cells get their octree cube only.
-__global__ __launch_bounds__(256) void k_index_grid(const int32_t* __restrict__ nodes, int n_top, int G,
+__global__ __launch_bounds__(256) void k_index_grid(const int32_t* __restrict__ nodes, int n_top, int G, int unit,
                                                     int32_t* __restrict__ grid) {
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     if (i >= (1u << (3 * G))) return;
@@ -2325,7 +2540,7 @@ __global__ __launch_bounds__(256) void k_index_grid(const int32_t* __restrict__ 
     if (e < 0)
         e = kIdxCoarse | (-e - 1);
     else if (e == 0)
-        e = index_entry_box(c, c, c, G - L);
+        e = index_entry_box(c, c, c, G - L, unit);
     else if (e >= n_top)
         e -= n_top;  // a brick: G == M
     grid[i] = e;
@@ -2350,7 +2565,7 @@ __global__ __launch_bounds__(256) void k_index_sums(const int32_t* __restrict__ 
 }
 
 // One thread per grid cell: the empty box of an empty cell, in grid cells.
-__global__ __launch_bounds__(256) void k_index_grid_boxes(const int32_t* __restrict__ sat, int G,
+__global__ __launch_bounds__(256) void k_index_grid_boxes(const int32_t* __restrict__ sat, int G, int unit,
                                                           int32_t* __restrict__ grid) {
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     if (i >= (1u << (3 * G))) return;
@@ -2360,7 +2575,7 @@ __global__ __launch_bounds__(256) void k_index_grid_boxes(const int32_t* __restr
     const int c[3] = {(int)(i >> (2 * G)), (int)(i >> G) & (n - 1), (int)i & (n - 1)};
     const int up = (e >> kIdxUpShift) & 15, w = (1 << up) - 1;
     auto S = [&](int x, int y, int z) {  // cells occupied in [0, x] x [0, y] x [0, z]
-        return x < 0 || y < 0 || z < 0 ? 0 : sat[((((uint32_t)x << G) | (uint32_t)y) << G) | (uint32_t)z];
+        return (x < 0 || y < 0 || z < 0) ? 0 : sat[((((uint32_t)x << G) | (uint32_t)y) << G) | (uint32_t)z];
     };
     auto empty = [&](const int (&l)[3], const int (&h)[3]) {
         const int a = l[0] - 1, b = l[1] - 1, d = l[2] - 1;
@@ -2375,7 +2590,7 @@ __global__ __launch_bounds__(256) void k_index_grid_boxes(const int32_t* __restr
         hi[k] = c[k] | w;
     }
     grow_box(lo, hi, n, 15, empty);
-    grid[i] = index_entry_box(c, lo, hi, up);
+    grid[i] = index_entry_box(c, lo, hi, up, unit);
 }
 #endif
 
@@ -2396,7 +2611,7 @@ inline int64_t rows_grid(int64_t n_blocks, int64_t chunk) { return 8 * chunk * (
 // Dynamic LDS of the node stack: one int per lane and tree level.  Trees whose
 // grid reaches the brick level keep no node path.
 inline size_t stack_bytes(const KTree& t) {
-    return t.grid_level > 0 && t.grid_level == t.brick_level ? 0 : sizeof(int) * kBlock * (size_t)t.depth;
+    return t.grid_level() > 0 && t.grid_level() == t.brick_level() ? 0 : sizeof(int) * kBlock * (size_t)t.depth();
 }
 
 // Record-load plan: "fast" loads the padded record with the widest vectors,
@@ -2584,7 +2799,7 @@ hipError_t backward_split_t(const po_tree* t, int64_t n, const float* o, const f
     S.n_rays = n;
     // the pieces of the render of the same rays (before the grids: they
     // cover the queue regions as this pass lays them out)
-    po_rays_piece_sizes(n, t->kt.depth, (op.flags & kOptExact) != 0u, &S);
+    po_rays_piece_sizes(n, t->kt.depth(), (op.flags & kOptExact) != 0u, &S);
     hipLaunchKernelGGL(k_zero_i32, dim3(2), dim3(kSplitRegions), 0, s, S.count, 2 * kSplitRegions);
     dim3 g1((unsigned)grid_for(B.n_blocks)), g2((unsigned)(kSplitRegions * (S.region_slots / kBlock))),
         g3(2u * g2.x), blk(kBlock);
@@ -2631,7 +2846,7 @@ hipError_t backward_kept_t(const po_tree* t, int64_t n, const float* o, const fl
     S.ray_o = o;
     S.ray_d = d;
     S.n_rays = n;
-    po_rays_piece_sizes(n, t->kt.depth, (op.flags & kOptExact) != 0u, &S);
+    po_rays_piece_sizes(n, t->kt.depth(), (op.flags & kOptExact) != 0u, &S);
     dim3 g1((unsigned)grid_for(B.n_blocks)), g3(2u * (unsigned)(kSplitRegions * (S.region_slots / kBlock))),
         blk(kBlock);
     const size_t lds = stack_bytes(t->kt);
@@ -2819,7 +3034,7 @@ hipError_t po_launch_rays_split(const po_tree* t, int64_t n, const float* o, con
     // first walk and smaller pieces (65536 random rays of the depth-8
     // training tree: 203 us with 8-cell pieces, 325 us with the frame's 32,
     // 300 us in one pass)
-    po_rays_piece_sizes(n, t->kt.depth, (op.flags & kOptExact) != 0u, &S);
+    po_rays_piece_sizes(n, t->kt.depth(), (op.flags & kOptExact) != 0u, &S);
     const int n_blocks = (int)((n + kBlock - 1) / kBlock);
     const int variant = po_fwd_variant(op, aux, t->kt);
     return t->desc.dtype == PO_F32 ? po_rays_split_f32(t, job, n_blocks, variant, S, s)
@@ -2831,15 +3046,15 @@ hipError_t po_launch_backward(const po_tree* t, int64_t n, const float* o, const
     PO_DISPATCH_K(t->K, (backward_t<KK>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, s)));
 }
 
-hipError_t po_launch_index(const int32_t* nodes, int n_top, int G, int64_t n_bricks, int32_t* grid,
+hipError_t po_launch_index(const int32_t* nodes, int n_top, int G, int unit, int64_t n_bricks, int32_t* grid,
                            int32_t* bricks, int32_t* sat, hipStream_t s) {
     if (n_bricks > 0) hipLaunchKernelGGL(k_index_bricks, dim3((unsigned)n_bricks), dim3(kBlock), 0, s, bricks);
     if (G > 0) {
         const unsigned cells = ((1u << (3 * G)) + 255u) / 256u, lines = ((1u << (2 * G)) + 255u) / 256u;
-        hipLaunchKernelGGL(k_index_grid, dim3(cells), dim3(256), 0, s, nodes, n_top, G, grid);
+        hipLaunchKernelGGL(k_index_grid, dim3(cells), dim3(256), 0, s, nodes, n_top, G, unit, grid);
         for (int axis = 2; axis >= 0; --axis)
             hipLaunchKernelGGL(k_index_sums, dim3(lines), dim3(256), 0, s, grid, sat, G, axis);
-        hipLaunchKernelGGL(k_index_grid_boxes, dim3(cells), dim3(256), 0, s, sat, G, grid);
+        hipLaunchKernelGGL(k_index_grid_boxes, dim3(cells), dim3(256), 0, s, sat, G, unit, grid);
     }
     return hipGetLastError();
 }
