@@ -208,19 +208,21 @@ inline void po_frame_piece_sizes(int64_t waves, bool exact, KSplit* S) {
 // walk of a few cells and small pieces (training step of 65,536 rays, depth 8:
 // 0.558 ms with the frame's sizes, 0.460 with these).  Its first walk counts
 // cells: counted in samples it would cross the empty space in front of the
-// first leaf at one wave's speed (52 against 18 us).  As many pieces as the
-// queue's 2^20 slots hold: past that the walks that find their region full
-// finish in their lanes (200,001 rays, depth 8: 0.535 ms at ub_frac 0.2, 0.333
-// at 0.1; 65,536 rays 0.358 at 0.2, 0.383 at 0.1).
+// first leaf at one wave's speed (52 against 18 us).  Chunks of 8 cells, handed
+// on past 16: 0.304 ms for the training step (6 and 12: 0.311), 0.455 and 0.483
+// with 131,072 rays, and the render of 200,001 0.265 and 0.287.  As many pieces
+// as the queue's 2^20 slots hold: past that the walks that find their region
+// full finish in their lanes (200,001 rays, depth 8, chunks of 6: 0.535 ms at
+// ub_frac 0.2, 0.333 at 0.1; 65,536 rays 0.358 at 0.2, 0.383 at 0.1).
 inline void po_rays_piece_sizes(int64_t n, int depth, bool exact, KSplit* S) {
     if (n >= (1 << 18)) {
         po_frame_piece_sizes(0, exact, S);
     } else {
         S->exact = true;
         S->split_cap = 4;
-        S->chunk_target = 6;
-        S->sub_target = 6;
-        S->chunk_cap = 12;
+        S->chunk_target = 8;
+        S->sub_target = 8;
+        S->chunk_cap = 16;
         S->ub_frac = (float)std::min(0.2, 5.6e6 / (double)(n << depth));
     }
 }
