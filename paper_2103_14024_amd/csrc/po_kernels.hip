@@ -478,9 +478,10 @@ struct Walker {
 
     // One cell.  cell_cap: the walk ends with it whatever it is; smp_cap: it
     // ends with it if it holds a sample.  At the end of the walk r.s and r.c
-    // are at the start of the next cell.
+    // are at the start of the next cell.  A lane whose walk has ended (live
+    // unset; cell_cap and inb set) keeps them.
     __device__ __forceinline__ Cell step(const Index& ix, Ray& r, bool exact, bool cell_cap, bool smp_cap,
-                                         int* __restrict__ stk) {
+                                         int* __restrict__ stk, bool live = true) {
         const int N = ix.top + 1;
         Cell o;
         // sign of the direction (0, or -1 on mirrored axes) and what follows
@@ -558,12 +559,12 @@ struct Walker {
         }
         bool out = ((nc[0] | nc[1] | nc[2]) & N) != 0;  // a coordinate of N: past the box
         if constexpr (CLIP) out |= se >= r.s_end;
-        r.s = se;
+        r.s = live ? se : r.s;
         const bool capped = !out & (cell_cap | (smp_cap & (leaf >= 0) & (o.delta > 0.0f)));
-        r.more = capped;
+        r.more = live ? capped : r.more;
         o.last = out | capped;
         const uint32_t diff = (uint32_t)((r.c[0] ^ nc[0]) | (r.c[1] ^ nc[1]) | (r.c[2] ^ nc[2]));
-        if (!out) {
+        if (!out & live) {
 #pragma unroll
             for (int k = 0; k < 3; ++k) r.c[k] = nc[k];
         }
@@ -836,6 +837,74 @@ __device__ __forceinline__ int march_inline(const KTree& tr, Ray& r, int max_ste
     return steps;
 }
 
+// march_inline for records that the four lanes of a quad load together: every
+// lane of the wave takes every step, a ray that has ended standing still, and
+// smp.consume(pending) runs in all of them.
+//
+// Why.  A float32 record of 16 coefficients is 192 bytes, 12 loads a lane, and
+// every load that sends 64 lanes to 64 lines holds the address unit four times
+// as long as one that sends each quad to one line (12 loads of the record's
+// first 64 bytes took nearly as long as the whole record, 4 of them 28 % less
+// of an 800x800 frame and 38 % less of 1920x1080).  By quads one load reads a
+// channel of one of the quad's four records, 64 bytes side by side; each lane
+// contracts its quarter with the basis of the ray it belongs to, and the four
+// parts meet in three exchanges inside the quad.  800x800 float32 K = 16: 427
+// to 403 us, 1920x1080 881 to 771.  Not for float16 (8 bytes a lane and so
+// twice the loads: 605 to 723 us at 1920x1080), nor for K = 9, whose channels
+// are no whole lines.
+template <class Sampler, bool SPLIT>
+__device__ __forceinline__ int march_quads(const KTree& tr, Ray& r, bool walk, int max_steps, int cap, bool exact,
+                                           int* __restrict__ stk, Sampler& smp) {
+    constexpr bool CHUNK = is_chunk<Sampler>::value;
+    Walker<Sampler::kClip, CHUNK> w;
+    int steps = 0, nt = 0;
+    bool live = walk, pending = false, stop = false;
+    r.more = false;
+    const Index ix(tr);
+    if (!walk) {  // any ray inside the box
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            r.og[k] = 0.0;
+            r.dg[k] = r.inv[k] = 1.0;
+            r.c[k] = 0;
+        }
+        r.s = r.s_end = 0.0;
+        r.len = 1.0;
+    }
+    w.start(ix, r, stk);
+    __builtin_amdgcn_sched_barrier(0);
+    smp.issue(-1, 0.0f, 0.0f, false);
+    do {
+        steps += live ? 1 : 0;
+        w.e = live ? w.e : 0;  // (past the end: no leaf)
+        w.inb |= !live;
+        const bool cell_cap = !live | (steps >= max_steps) | (SPLIT && exact && steps >= cap);
+        const Cell c = w.step(ix, r, exact, cell_cap, SPLIT && !exact && nt + 1 >= cap, stk, live);
+        __builtin_amdgcn_sched_barrier(0);
+        if (__ballot(pending) != 0ull) stop |= smp.consume(pending);
+        pending = live & !stop & (c.leaf >= 0) & (c.delta > 0.0f);
+        if constexpr (CHUNK) {
+            if (live) {
+                smp.cpl = c.cpl;
+                if (steps == 1) {
+                    if (smp.skip0 < 0) smp.skip0 = c.delta > 0.0f ? 0 : 1;
+                    if (!pending) stop = smp.test_first(c.cpl);
+                }
+            }
+        }
+        smp.issue(pending ? c.leaf : -1, c.delta, c.t_in, !c.cpl);
+        nt += pending ? 1 : 0;
+        live &= !(c.last | stop);
+    } while (__ballot(live) != 0ull);
+    const bool capped = r.more;
+    if (__ballot(pending) != 0ull) stop |= smp.consume(pending);
+    r.more &= !stop;
+    r.nt = exact ? steps : nt;
+    // a lane that met a malformed entry or the step cap is counted once
+    if (w.bad | (!SPLIT & capped)) atomicAdd(&g_po_errors, 1ull);
+    return steps;
+}
+
 // Which of the two a sampler takes (kQueued): the queue costs about 45
 // instructions a step, and saves the waits on gathers and the lanes without a
 // sample.  It pays where a sample is expensive: records over 192 bytes (SG-25
@@ -848,6 +917,8 @@ __device__ __forceinline__ int march(const KTree& tr, Ray& r, bool walk, int max
                                      int* __restrict__ stk, Sampler& smp) {
     if constexpr (Sampler::kQueued) {
         return march_queued<Sampler, SPLIT>(tr, r, walk, max_steps, cap, exact, stk, smp);
+    } else if constexpr (Sampler::kQuads) {
+        return march_quads<Sampler, SPLIT>(tr, r, walk, max_steps, cap, exact, stk, smp);
     } else {
         r.more = false;
         r.nt = 0;
@@ -857,10 +928,23 @@ __device__ __forceinline__ int march(const KTree& tr, Ray& r, bool walk, int max
 
 template <typename T, int K, int NW>
 __device__ __forceinline__ float dot_channel(const uint32_t (&w)[NW], int base, const float (&Y)[K]) {
-    float z = word_elem<T>(w, base) * Y[0];
+    if constexpr (std::is_same_v<T, float> && K == 16) {
+        // in four parts, as quad_dots adds them (the backward's colours and the
+        // render's have the same bits)
+        float z[4];
 #pragma unroll
-    for (int k = 1; k < K; ++k) z = fmaf(word_elem<T>(w, base + k), Y[k], z);
-    return z;
+        for (int q = 0; q < 4; ++q) {
+            z[q] = word_elem<T>(w, base + 4 * q) * Y[4 * q];
+#pragma unroll
+            for (int k = 1; k < 4; ++k) z[q] = fmaf(word_elem<T>(w, base + 4 * q + k), Y[4 * q + k], z[q]);
+        }
+        return (z[0] + z[1]) + (z[2] + z[3]);
+    } else {
+        float z = word_elem<T>(w, base) * Y[0];
+#pragma unroll
+        for (int k = 1; k < K; ++k) z = fmaf(word_elem<T>(w, base + k), Y[k], z);
+        return z;
+    }
 }
 
 // Loads one record (NL elements, a whole number of VEC-byte vectors) at byte
@@ -884,6 +968,25 @@ __device__ __forceinline__ void load_record(__amdgpu_buffer_rsrc_t rs, uint32_t 
             w[v] = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 4 * v, 0, 0);
         }
     }
+}
+
+// Value of x in lane I of this lane's quad, and in the lane whose number
+// differs from this one's in bit BIT.
+template <int I>
+__device__ __forceinline__ uint32_t quad_bcast(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x55 * I, 0xf, 0xf, true);
+}
+template <int BIT>
+__device__ __forceinline__ float quad_swap(float x) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), BIT == 0 ? 0xB1 : 0x4E, 0xf, 0xf, true));
+}
+// Basis values of the wave's rays as quads read them: [lane][k], the 16
+// float4 of four lanes padded to 20, so that the quads of 16 lanes read
+// different banks.
+constexpr int kQuadBasis = 20;
+__device__ __forceinline__ float4* quad_basis() {
+    __shared__ __align__(16) float4 s_Yq[kQuadBasis * kBlock / 4];
+    return s_Yq;
 }
 
 // Leaf arrays of a tree with float32 or float16 records, bound to buffers.
@@ -981,6 +1084,7 @@ struct FwdQueued : Rec {
     static constexpr bool kClip = VIEW;
     static constexpr bool kView = VIEW;
     static constexpr bool kQueued = true;
+    static constexpr bool kQuads = false;
     float stopT;
     float c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, Tl = 1.0f;
     float dep = 0.0f;
@@ -1014,7 +1118,7 @@ struct FwdQueued : Rec {
     __device__ __forceinline__ void finish(uint32_t, uint32_t) {}
 };
 
-// The same for samples shaded by their own ray's lane (march_inline).
+// The same for samples shaded by their own ray's lane (march_inline, march_quads).
 template <typename T, int K, int VEC, int NL, bool VIEW>
 struct FwdInline : Records<T, K, VEC, NL> {
     static constexpr bool kClip = VIEW;
@@ -1024,31 +1128,84 @@ struct FwdInline : Records<T, K, VEC, NL> {
     float c0 = 0.0f, c1 = 0.0f, c2 = 0.0f, Tl = 1.0f;
     float dep = 0.0f;
     int ns = 0;
+    // a record of 16 float32 per channel is loaded by the quad of lanes
+    static constexpr bool kQuads = std::is_same_v<T, float> && K == 16 && VEC == 16;
     // in flight
     uint32_t raw;
     float delta, ta;
     bool cut;
-    uint32_t w[Words<T, NL>::N];
+    uint32_t w[Words<T, NL>::N];  // kQuads: [channel][lane of the quad][4], this lane's quarter of its records
 
     __device__ __forceinline__ void issue(int leaf, float d, float t_in, bool is_cut) {
         raw = sigma_buf(this->sig, leaf < 0 ? this->sig_end : (uint32_t)leaf * (uint32_t)sizeof(T), (T*)nullptr);
-        load_record<T, NL, VEC>(this->shb, leaf < 0 ? this->sh_end : (uint32_t)leaf * this->rec_bytes, w);
+        const uint32_t off = leaf < 0 ? this->sh_end : (uint32_t)leaf * this->rec_bytes;
+        if constexpr (kQuads) {
+            const uint32_t l = 16u * (threadIdx.x & 3u);
+            const uint32_t rec[4] = {quad_bcast<0>(off) + l, quad_bcast<1>(off) + l, quad_bcast<2>(off) + l,
+                                     quad_bcast<3>(off) + l};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const auto q = __builtin_amdgcn_raw_buffer_load_b128(this->shb, rec[i] + 64 * c, 0, 0);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) w[16 * c + 4 * i + j] = q[j];
+                }
+        } else {
+            load_record<T, NL, VEC>(this->shb, off, w);
+        }
         delta = d;
         cut = is_cut;
         if constexpr (VIEW) ta = t_in;
     }
-    __device__ __forceinline__ bool consume() {
+    // The contraction of every lane's record, by the quads.
+    __device__ __forceinline__ void quad_dots(float (&z)[3]) const {
+        const uint32_t lane = threadIdx.x;
+        const bool b0 = (lane & 1u) != 0u, b1 = (lane & 2u) != 0u;
+        const float4* Yq = quad_basis() + (lane >> 2) * kQuadBasis + (lane & 3u);
+        float p[3][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 y = Yq[4 * i];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const uint32_t* x = w + 16 * c + 4 * i;
+                p[c][i] = fmaf(__uint_as_float(x[3]), y.w,
+                               fmaf(__uint_as_float(x[2]), y.z,
+                                    fmaf(__uint_as_float(x[1]), y.y, __uint_as_float(x[0]) * y.x)));
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            float t[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float keep = b0 ? p[c][2 * h + 1] : p[c][2 * h], give = b0 ? p[c][2 * h] : p[c][2 * h + 1];
+                t[h] = keep + quad_swap<0>(give);
+            }
+            const float keep = b1 ? t[1] : t[0], give = b1 ? t[0] : t[1];
+            z[c] = keep + quad_swap<1>(give);
+        }
+    }
+    __device__ __forceinline__ bool consume(bool pending = true) {
+        float z[3];
+        if constexpr (kQuads) quad_dots(z);
+        if (kQuads & !pending) return false;
         ++ns;
         const float s = fmaxf(sigma_of<T>(raw), 0.0f);
         if (!(s > 0.0f)) return false;
         const float tau = s * delta;
         const float ex = __expf(-tau);
         const float wgt = Tl * (1.0f - ex);
-        float Y[K];
-        read_basis<K>(threadIdx.x, Y);
-        c0 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, 0, Y)), c0);
-        c1 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, K, Y)), c1);
-        c2 = fmaf(wgt, sigmoid(dot_channel<T, K>(w, 2 * K, Y)), c2);
+        if constexpr (!kQuads) {
+            float Y[K];
+            read_basis<K>(threadIdx.x, Y);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) z[c] = dot_channel<T, K>(w, c * K, Y);
+        }
+        c0 = fmaf(wgt, sigmoid(z[0]), c0);
+        c1 = fmaf(wgt, sigmoid(z[1]), c1);
+        c2 = fmaf(wgt, sigmoid(z[2]), c2);
         if constexpr (VIEW) dep = fmaf(Tl, depth_term(tau, ex, delta, ta), dep);
         Tl = Tl * ex;
         return Tl < stopT;
@@ -1057,7 +1214,7 @@ struct FwdInline : Records<T, K, VEC, NL> {
 
 // The SH or SG basis of a variant at this lane's ray direction, into the
 // wave's LDS array.
-template <int K, int V>
+template <int K, int V, bool QUADS = false>
 __device__ __forceinline__ void init_basis(const KTree& tr, const KOpts& op, const Ray& r) {
     float Y[K];
     if constexpr (V == PO_FWD_SG)
@@ -1071,10 +1228,11 @@ __device__ __forceinline__ void init_basis(const KTree& tr, const KOpts& op, con
         for (int k = 0; k < K; ++k)
             if ((op.sh_off >> k) & 1u) Y[k] = 0.0f;
     }
-    float4* p = basis_values<K>() + threadIdx.x;
+    float4* p = QUADS ? quad_basis() + (threadIdx.x >> 2) * kQuadBasis + (threadIdx.x & 3u) * 4u
+                      : basis_values<K>() + threadIdx.x;
 #pragma unroll
     for (int q = 0; q < (K + 3) / 4; ++q)
-        p[q * kBlock] = make_float4(Y[4 * q], 4 * q + 1 < K ? Y[4 * q + 1] : 0.0f, 4 * q + 2 < K ? Y[4 * q + 2] : 0.0f,
+        p[QUADS ? q : q * kBlock] = make_float4(Y[4 * q], 4 * q + 1 < K ? Y[4 * q + 1] : 0.0f, 4 * q + 2 < K ? Y[4 * q + 2] : 0.0f,
                                     4 * q + 3 < K ? Y[4 * q + 3] : 0.0f);
 }
 
@@ -1102,9 +1260,9 @@ struct ChunkOf : Base {
     __device__ __forceinline__ bool composite(const Sample& q, uint32_t slot, uint32_t at) {
         return tested(Base::composite(q, slot, at), (q.info & 64u) != 0u);
     }
-    __device__ __forceinline__ bool consume() {
-        const bool st = Base::consume();
-        return tested(st, this->cut);
+    __device__ __forceinline__ bool consume(bool pending = true) {
+        const bool st = Base::consume(pending);
+        return pending && tested(st, this->cut);
     }
     __device__ __forceinline__ bool tested(bool st, bool is_cut) {
         smp_cut = is_cut;
@@ -1138,7 +1296,7 @@ template <int K, int V, class Smp>
 __device__ __forceinline__ void fwd_init(Smp& smp, const KTree& tr, const KOpts& op, bool ray, const Ray& r) {
     smp.bind(tr);
     smp.stopT = op.stop_T;
-    if (ray) init_basis<K, V>(tr, op, r);
+    if (ray) init_basis<K, V, Smp::kQuads>(tr, op, r);
 }
 
 // Renders the wave's rays (valid: this lane has one): colour (background
@@ -1559,14 +1717,11 @@ __device__ __forceinline__ void first_walk(const KJob& J, const KSplit& S, int i
     }
 }
 
-// The plain (SH, SG) chunk and sub-chunk walks of records up to 192 bytes
-// are held to 128 VGPRs (4 waves per SIMD; unconstrained the float32 K=16
-// chunk kernel takes 131 and 3 waves): 0.639 against 0.671 ms per depth-9
-// 800x800 frame; float16 SH records of K <= 16 with the basis values in
-// LDS, to 96 VGPRs (5 waves; 20 bytes of scratch outside the loop).  Larger
-// records and the viewer and codebook variants would spill (K=25 float32:
-// 180 bytes of scratch, half the frame rate; float16 K=25 at 5 waves: 144),
-// so they keep 4 waves or their natural count.
+// The plain (SH, SG) walks of records up to 192 bytes are held to 128 VGPRs
+// (4 waves per SIMD; float32 K = 16 then keeps up to 96 bytes of scratch, used
+// before and after the walk's loop).  Larger records and the viewer and
+// codebook variants would spill inside it (K=25 float32: 180 bytes of scratch,
+// half the frame rate), so they keep their natural count.
 template <typename T, int K, int V>
 constexpr int kPieceWaves = (V == PO_FWD_SH || V == PO_FWD_SG) && sizeof(T) * 3 * K <= 192
                                 ? 4
@@ -1906,6 +2061,7 @@ struct BwdSampler : Records<float, K, VEC, NL> {
     static constexpr bool kClip = false;
     static constexpr bool kView = false;
     static constexpr bool kQueued = true;
+    static constexpr bool kQuads = false;
     static constexpr int NE = 3 * K;
     static constexpr uint32_t kNone = 0xffffffffu;  // Sample::info: no gradient
     int stride;
@@ -2203,6 +2359,7 @@ struct WeightSampler {
     static constexpr bool kClip = false;
     static constexpr bool kView = false;
     static constexpr bool kQueued = false;
+    static constexpr bool kQuads = false;
     __amdgpu_buffer_rsrc_t sig;
     uint32_t sig_end;
     float stopT;
