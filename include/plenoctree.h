@@ -257,9 +257,13 @@ po_status po_render_rays(const po_tree* t, int64_t n, const float* d_origins, co
 /* po_render_camera: renders a camera image into d_rgb[height][width][3]
  * (and d_aux[height][width][4] with PO_OUT_AUX).  width, height in
  * [1, 16384]; fx, fy non-zero.
- * Images of at least 65536 pixels are rendered in pieces: every ray is walked
- * for a bounded number of data samples, the rays with cells left are cut into parameter intervals walked in parallel, and the
- * pieces are composited front to back (compositing is associative, Sec. 3
+ * Images of at least 65536 pixels whose longest walks would outlast the rest
+ * (up to a number of pixels that grows with the depth: 98,304 to depth 7,
+ * 98,304 or 327,680 at depth 8, 720,896 at 9 and 2,097,152 at 10; larger images
+ * are rendered in one pass), and all of them with PO_OUT_AUX or a
+ * caller's max_steps, are rendered in pieces: every ray is walked
+ * for a bounded number of data samples, the rays with cells left are cut into
+ * parameter intervals walked in parallel, and the pieces are composited front to back (compositing is associative, Sec. 3
  * eqn:quad), the piece holding the early stop walked again with the known
  * transmittance.  The colour equals the one-pass render (po_render_batch)
  * up to float rounding; where T lands within rounding of stop_T the two can
@@ -402,12 +406,11 @@ po_status po_draw_batch(int64_t n, uint64_t seed, uint64_t first, int64_t n_src,
  * One job renders the 16x16 tiles [tile_begin, tile_end) of one camera
  * image of one tree (tiles numbered row-major over ceil(W/16) x ceil(H/16)).
  * po_render_batch renders up to PO_BATCH_MAX_JOBS jobs, of any trees and
- * image sizes, all on `stream`.  Jobs of fewer than 256 tiles (65536 pixels)
- * are rendered with as few kernel launches as their (dtype, SH degree)
+ * image sizes, all on `stream`.  Jobs of fewer than 256 tiles (65536 pixels),
+ * and all others that po_render_camera would not render in pieces, are rendered with as few kernel launches as their (dtype, SH degree)
  * groups allow, each ray walked to its end in one pass by one lane; their
  * pixels equal po_render_camera's bit for bit for images under 65536
- * pixels.  A job of 256 tiles or more (without PO_ONE_PASS in its options)
- * is rendered in pieces on its own, as
+ * pixels.  A job of more tiles (without PO_ONE_PASS in its options) is rendered in pieces on its own, as
  * po_render_camera renders a large image (using the same work queue of
  * `stream`), and its pixels equal po_render_camera's up to float rounding
  * (bit for bit unless a region of the work queue filled up in one of the

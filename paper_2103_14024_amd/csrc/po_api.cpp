@@ -44,10 +44,10 @@ po_status device_fail(hipError_t e, const char* what) {
 
 bool finite(float v) { return std::isfinite(v); }
 
-// Camera renders of at least kSplitMinPixels pixels and ray-list renders of
-// at least kSplitMinRays rays use the split render.  Its five launches each
-// end with their own longest walk, which outweighs the shorter critical path
-// for small launches.
+// Camera renders of at least kSplitMinPixels pixels (and fewer than
+// split_max_pixels) and ray-list renders of at least kSplitMinRays rays use
+// the split render.  Its five launches each end with their own longest walk,
+// which outweighs the shorter critical path for small launches.
 constexpr int64_t kSplitMinPixels = 1 << 16;
 #ifndef PO_SPLIT_MIN_RAYS
 #define PO_SPLIT_MIN_RAYS (1 << 16)
@@ -788,6 +788,39 @@ po_status po_render_rays(const po_tree* t, int64_t n, const float* d_origins, co
     return ok();
 }
 
+// Pixels from which a camera render takes one pass again: its waves then keep
+// the chip busy for as long as the longest walk lasts, and the pieces only
+// cost.  That walk grows with the depth, and with what a sample costs (heavy:
+// records over 192 bytes, codebooks, viewer outputs).  Time of one pass over
+// time in pieces, blob bands, by pixels:
+//             256x256  400x400  512x512  640x480  800x800  1280x720  1920x1080
+//   depth 7    0.76     0.69              0.59     0.60      0.69      0.87  (heavy 0.9 .. 0.64)
+//   depth 8    1.02     0.93              0.83     0.75      0.72      0.81
+//     heavy    1.13     1.15     1.08     1.08     0.90
+//   depth 9    1.52     1.30              1.18     1.07      0.90      0.84  (heavy 1.6 .. 1.1, 0.94)
+//   depth 10   1.6               1.5               1.3       1.1       1.0
+// (Below depth 8 one pass wins at every size; images up to 98,304 pixels keep
+// to pieces there because programs that reserve or release a stream's queue
+// count on the smallest of them to use it.)
+// Renders that report or cap their steps keep to pieces at any size: a cell cut
+// exactly at a face by a piece may count as two there (1 pixel in 1000 of a fog
+// ball), and the counts of an image do not depend on this rule.
+int64_t split_max_pixels(const po_tree* t, const KOpts& k, int variant) {
+    if (k.flags & kOptExact) return INT64_MAX;
+    const bool heavy = variant == PO_FWD_VIEW || variant == PO_FWD_CB || elem_size(t->desc.dtype) * 3 * t->K > 192;
+    switch (t->desc.depth) {
+    case 8: return heavy ? 5 << 16 : 3 << 15;
+    case 9: return 11 << 16;
+    case 10: return 1 << 21;
+    default: return t->desc.depth < 8 ? 3 << 15 : INT64_MAX;
+    }
+}
+// Whether a camera render of so many pixels runs in pieces.
+bool in_pieces(const po_tree* t, const KOpts& k, int variant, int64_t pixels) {
+    return !(k.flags & PO_ONE_PASS) && k.max_steps > kSplitMinMaxSteps && pixels >= kSplitMinPixels &&
+           pixels < split_max_pixels(t, k, variant);
+}
+
 // po_render_camera and po_render_camera_noalloc: the same render, with the
 // per-stream queue (allocated on first use) or the fixed per-device one.
 static po_status render_camera_impl(const po_tree* t, const po_camera* cam, const po_render_opts* opts,
@@ -817,8 +850,7 @@ static po_status render_camera_impl(const po_tree* t, const po_camera* cam, cons
     const int variant = po_fwd_variant(j.op, j.aux, t->kt);
     KSplit S;
     hipError_t e;
-    const bool split = !(j.op.flags & PO_ONE_PASS) && (int64_t)cam->width * cam->height >= kSplitMinPixels &&
-                       j.op.max_steps > kSplitMinMaxSteps;
+    const bool split = in_pieces(t, j.op, variant, (int64_t)cam->width * cam->height);
     if (split && noalloc) {
         if ((e = po_noalloc_queue(&S)) != hipSuccess) return device_fail(e, "locating the fixed work queue");
         po_frame_piece_sizes(4 * (int64_t)tiles_of(cam), (j.op.flags & kOptExact) != 0u, &S);
@@ -1040,15 +1072,14 @@ po_status po_render_batch(int32_t n_jobs, const po_job* jobs, void* stream) {
         return 4 * po_plan_id(J.tree) + po_fwd_variant(kopts(J.tree, &J.opts), aux, J.tree->kt);
     };
     bool done[PO_BATCH_MAX_JOBS] = {false};
-    // jobs of at least kSplitMinPixels pixels (whole tiles) are rendered in
-    // pieces, each on its own, as po_render_camera renders a large image
+    // jobs that po_render_camera would render in pieces at their number of
+    // pixels (whole tiles) are rendered so, each on its own
     for (int i = 0; i < n_jobs; ++i) {
         const po_job& J = jobs[i];
         const int nt = J.tile_end - J.tile_begin;
         const KOpts k = kopts(J.tree, &J.opts);
         KSplit S;
-        if ((k.flags & PO_ONE_PASS) || (int64_t)nt * PO_TILE * PO_TILE < kSplitMinPixels ||
-            k.max_steps <= kSplitMinMaxSteps || !split_queue(stream, &S))
+        if (!in_pieces(J.tree, k, variant(i) % 4, (int64_t)nt * PO_TILE * PO_TILE) || !split_queue(stream, &S))
             continue;
         done[i] = true;
         KJob kj;
