@@ -223,6 +223,7 @@ po_status po_tree_bind_codebook(const po_tree_desc* desc, int64_t n_nodes, const
  * counting malformed entries as device errors), PO_ERR_UNSUPPORTED (2^29 - 2
  * leaves or more, or nodes and bricks of 4 GiB or more), PO_ERR_OOM,
  * PO_ERR_DEVICE. */
+po_status po_tree_build_index(po_tree* t, void* stream);
 /* po_tree_index_host: host only.  The nodes and bricks that
  * po_tree_build_index starts from (before it adds the grid and the empty
  * boxes), from a host copy of a child array of depth D >= 4: writes *n_top
