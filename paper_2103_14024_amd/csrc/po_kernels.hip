@@ -549,11 +549,14 @@ struct Walker {
         // next cell: axes whose face is reached step to the neighbouring cell;
         // the others take the finest cell of the exit point, kept inside the
         // current box and never moving against the ray (truncation equals
-        // floor here: the result is clamped)
+        // floor here: the result is clamped).  Clamped to the grid on both
+        // sides before it is mirrored: a ray that has just entered through the
+        // upper face of an axis it runs down is at 2^D up to rounding, which
+        // mirrored would lie past the far end of any box
         int nc[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            int q = max((int)fma(se, r.dg[k], r.og[k]), 0) ^ flip[k];
+            int q = min(max((int)fma(se, r.dg[k], r.og[k]), 0), ix.top) ^ flip[k];
             asm volatile("" : "+v"(q));  // (or the compiler branches around it)
             nc[k] = sk[k] <= se ? end[k] + 1 : max(min(q, end[k]), r.c[k]);
         }
