@@ -282,7 +282,7 @@ __device__ __forceinline__ bool exact_cells(const KOpts& op) { return (op.flags 
 // Entries.  With a grid (tr.grid_level() G > 0) the level-G cell holding c is
 // one read, and the 8x8x8 brick below it another, whatever the cell crossed
 // before: no node path is kept.  An empty entry names the box of empty space
-// around its cell, so that one step crosses it whole (see index_entry_box);
+// around its cell, so that one step crosses it whole (po_index_cube_entry);
 // exact keeps to the octree's own empty cubes, whose number is what the aux
 // output and po_traversal_stats count and max_steps caps.  The segments of
 // the data leaves are the same either way: a leaf is entered through one of
@@ -457,10 +457,10 @@ struct Walker {
     // A brick or grid entry.
     __device__ __forceinline__ void decode(const Index& ix, bool exact, int& leaf, int& u, uint32_t& ext) const {
         leaf = e < 0 ? -1 : (e >> 2) - 1;
-        u = e < 0 ? (int)(((uint32_t)e >> kIdxUnitShift) & 7u) : e & 3;
+        u = e < 0 ? po_index_unit(e) : e & 3;
         ext = e < 0 ? (uint32_t)e : 0u;
         if (exact) {
-            u += e < 0 ? (e >> kIdxUpShift) & 15 : 0;
+            u = e < 0 ? po_index_cube(e) : u;
             ext = 0;
         }
         if (ix.coarse) {
@@ -2622,17 +2622,6 @@ __device__ __forceinline__ void grow_box(int (&lo)[3], int (&hi)[3], int n, int 
     }
 }
 
-// Entry of an empty cell c (of edge 2^unit) whose empty octree cube lies `up`
-// levels higher, inside the empty box [lo, hi].
-__device__ __forceinline__ int32_t index_entry_box(const int (&c)[3], const int (&lo)[3], const int (&hi)[3], int up,
-                                                   int unit) {
-    uint32_t e = 0x80000000u | (uint32_t)unit << kIdxUnitShift | (uint32_t)up << kIdxUpShift;
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-        e |= (uint32_t)min(c[k] - lo[k], 15) << (8 * k) | (uint32_t)min(hi[k] - c[k], 15) << (8 * k + 4);
-    return (int32_t)e;
-}
-
 // One wave per brick: the boxes of its empty cells, inside the brick, and its
 // entries from the order of the host's child slots to x, y, z.  The
 // brick's occupancy is held as eight 64-bit masks (one per x, bit 8 y + z), so
@@ -2679,7 +2668,7 @@ __global__ __launch_bounds__(kBlock) void k_index_bricks(int32_t* __restrict__ b
             hi[k] = cx[i][k] | w;
         }
         grow_box(lo, hi, 8, 8, empty);
-        *out = index_entry_box(cx[i], lo, hi, up, 0);
+        *out = po_index_box_entry(cx[i], lo, hi, up, 0);
     }
 }
 
@@ -2700,7 +2689,7 @@ __global__ __launch_bounds__(256) void k_index_grid(const int32_t* __restrict__ 
     if (e < 0)
         e = kIdxCoarse | (-e - 1);
     else if (e == 0)
-        e = index_entry_box(c, c, c, G - L, unit);
+        e = po_index_box_entry(c, c, c, G - L, unit);
     else if (e >= n_top)
         e -= n_top;  // a brick: G == M
     grid[i] = e;
@@ -2733,7 +2722,8 @@ __global__ __launch_bounds__(256) void k_index_grid_boxes(const int32_t* __restr
     if (e >= 0) return;
     const int n = 1 << G;
     const int c[3] = {(int)(i >> (2 * G)), (int)(i >> G) & (n - 1), (int)i & (n - 1)};
-    const int up = (e >> kIdxUpShift) & 15, w = (1 << up) - 1;
+    // (as k_index_grid wrote it: a box of one cell, in cells of the grid)
+    const int up = po_index_cube(e) - unit, w = (1 << up) - 1;
     auto S = [&](int x, int y, int z) {  // cells occupied in [0, x] x [0, y] x [0, z]
         return (x < 0 || y < 0 || z < 0) ? 0 : sat[((((uint32_t)x << G) | (uint32_t)y) << G) | (uint32_t)z];
     };
@@ -2749,8 +2739,8 @@ __global__ __launch_bounds__(256) void k_index_grid_boxes(const int32_t* __restr
         lo[k] = c[k] & ~w;
         hi[k] = c[k] | w;
     }
-    grow_box(lo, hi, n, 15, empty);
-    grid[i] = index_entry_box(c, lo, hi, up, unit);
+    grow_box(lo, hi, n, kIdxReach, empty);
+    grid[i] = po_index_cube_entry(c, lo, hi, up, unit);
 }
 #endif
 
