@@ -327,7 +327,7 @@ struct Index {
     int D, M, G, q;                 // q = D - G
     int top;                        // 2^D - 1
     int n_top, n_leaves;
-    int direct, coarse;             // the grid reaches the bricks; it names leaves
+    int coarse;                     // the grid names leaves
 
     __device__ __forceinline__ explicit Index(const KTree& tr) {
         bytes = held(tr.index_bytes);
@@ -339,7 +339,6 @@ struct Index {
         q = held(D - G);
         top = held((1 << D) - 1);
         coarse = held((int)(levels >> 24));
-        direct = held((int)((G > 0) & (G == M)));
         n_top = tr.n_top;
         n_leaves = tr.n_leaves;
         node0 = G > 0 ? 4u << (3 * G) : 0u;
@@ -369,6 +368,25 @@ struct Index {
     }
 };
 
+// The three walks.  Kernels are compiled for direct trees and for the others
+// (which then choose by a branch of the wave in front of the loop), and the
+// batched ones also for mixed launches.  One loop that tested the way in every
+// step took 2 to 14 % longer on direct trees (64x64 23.3 against 20.4 us,
+// 800x800 410 against 391), and 20 to 30 % on trees without an index, whose
+// steps ran through the branches of the nodes'.  The three loops side by side
+// in one kernel cost it registers: float32 K = 16 at 800x800 lost 7 % to
+// spills around the loops.
+enum Way {
+    kDirect,  // the grid reaches the bricks (indexed trees of depth 4 to 11)
+    kPlain,   // the caller's child array
+    kNodes,   // an index with nodes between the grid and the bricks
+    kOther,   // kernels: kPlain or kNodes
+    kAny      // kernels: any of the three
+};
+__host__ __device__ inline Way way_of(int D, int M, int G) {
+    return G > 0 && G == M ? kDirect : G == 0 && M == D ? kPlain : kNodes;
+}
+
 // CLIP: the walk also ends at r.s_end.  CHUNK: r.s_end is a piece's end, and
 // cpl says whether the next piece starts outside this cell.
 //
@@ -378,7 +396,7 @@ struct Index {
 // on average.  So the step is kept short: mirrored axes, entries that carry
 // their own box, and a branch-free path for trees whose grid reaches the
 // bricks.
-template <bool CLIP, bool CHUNK>
+template <bool CLIP, bool CHUNK, Way WAY>
 struct Walker {
     int e;
     int bad;        // met a malformed entry
@@ -392,7 +410,7 @@ struct Walker {
         bad = 0;
         const int N = ix.top + 1;
         const int c[3] = {r.c[0] ^ r.flip(0, N), r.c[1] ^ r.flip(1, N), r.c[2] ^ r.flip(2, N)};
-        if (ix.G > 0) {
+        if (WAY == kDirect || (WAY == kNodes && ix.G > 0)) {
             bofs = 0xffffffffu;
             e = ix.entry(ix.grid_at(c));
         } else {
@@ -402,60 +420,61 @@ struct Walker {
         }
     }
 
-    // Resolves e, the entry of cell c: its leaf (-1: empty space), log2 of the
-    // edge u of its cube, and for empty space how far the box reaches beyond.
-    __device__ __forceinline__ void resolve(const Index& ix, const int (&c)[3], int* __restrict__ stk, bool exact,
-                                            int& leaf, int& u, uint32_t& ext) {
-        const int D = ix.D, M = ix.M, G = ix.G;
-        leaf = -1;
-        u = 0;
-        ext = 0;
-        bool boxed = inb;  // e is a brick or grid entry
-        if (!inb) {
-            bool descend = true;
-            int L = (int)bofs, node;
-            if (L < 0) {
-                descend = false;
-                if ((uint32_t)e < (uint32_t)kIdxCoarse) {
-                    L = G;
-                    node = e;
-                    stk[L * kBlock] = node;
-                    e = ix.entry_now(ix.slot_at(c, node, L));
-                    descend = true;
-                } else {
-                    boxed = true;
-                }
-            }
-            if (descend) {
-                ++L;  // e is the entry of the level-L cell holding c
-                while ((e > 0) & (e < ix.n_top) & (L < M)) {
-                    node = e;
-                    stk[L * kBlock] = node;
-                    e = ix.entry_now(ix.slot_at(c, node, L));
-                    ++L;
-                }
-                if ((e > 0) & (L == M) & (M < D) & (e >= ix.n_top)) {
-                    // the level-M cube holding c is a brick: one load gives the leaf
-                    bofs = ix.brick0 + (uint32_t)(e - ix.n_top) * 2048u;
-                    e = ix.entry_now(ix.brick_at(bofs, c));
-                    inb = boxed = true;
-                } else {
-                    // a leaf or empty cube of level L; any other positive entry
-                    // (past the nodes, or internal at the deepest level) is malformed
-                    if (e > 0) bad = 1;
-                    leaf = e > 0 ? -1 : -1 - e;
-                    u = D - L;
-                }
-            }
+    // The descent of a tree without an index: e is the entry of a cell below a
+    // level-bofs node.
+    __device__ __forceinline__ void descend(const Index& ix, const int (&c)[3], int* __restrict__ stk, int& leaf,
+                                            int& u) {
+        int L = (int)bofs + 1;
+        while ((e > 0) & (e < ix.n_top) & (L < ix.D)) {
+            const int node = e;
+            stk[L * kBlock] = node;
+            e = ix.entry_now(ix.slot_at(c, node, L));
+            ++L;
         }
-        if (boxed) decode(ix, exact, leaf, u, ext);
-        if (leaf >= ix.n_leaves) {
+        leaf = e < 0 ? -1 - e : -1;
+        u = ix.D - L;
+        if ((e > 0) | (leaf >= ix.n_leaves)) {  // past the nodes or leaves, or internal at the deepest level
             bad = 1;
             leaf = -1;
         }
     }
-    // A brick or grid entry.
-    __device__ __forceinline__ void decode(const Index& ix, bool exact, int& leaf, int& u, uint32_t& ext) const {
+
+    // The descent of an index that keeps nodes: from the grid, or from the
+    // deepest ancestor shared with the cell before, to a leaf, empty space or
+    // a brick.  (An index is made from a checked array: no entry is malformed.)
+    __device__ __forceinline__ void resolve(const Index& ix, const int (&c)[3], int* __restrict__ stk, bool exact,
+                                            int& leaf, int& u, uint32_t& ext) {
+        bool node = !inb & ((int)bofs >= 0);  // e is a node's entry
+        if (!inb & !node & ((uint32_t)e < (uint32_t)kIdxCoarse)) {  // the grid names a node
+            node = true;
+            bofs = (uint32_t)ix.G;
+            stk[ix.G * kBlock] = e;
+            e = ix.entry_now(ix.slot_at(c, e, ix.G));
+        }
+        int L = (int)bofs + 1;  // e is the entry of the level-L cell holding c
+        if (node) {
+            while ((e > 0) & (e < ix.n_top)) {
+                const int at = e;
+                stk[L * kBlock] = at;
+                e = ix.entry_now(ix.slot_at(c, at, L));
+                ++L;
+            }
+            if (e > 0) {  // the level-M cube holding c is a brick: one load gives the leaf
+                bofs = ix.brick0 + (uint32_t)(e - ix.n_top) * 2048u;
+                e = ix.entry_now(ix.brick_at(bofs, c));
+                inb = true;
+                node = false;
+            }
+        }
+        decode(ix, exact, node, leaf, u, ext);
+        leaf = node ? -1 - e : leaf;
+        u = node ? ix.D - L : u;
+        ext = node ? 0u : ext;
+    }
+    // The leaf of a brick or grid entry (node: neither), -1 for empty space, log2 of the
+    // edge of its cell, and for empty space how far the box reaches beyond.
+    __device__ __forceinline__ void decode(const Index& ix, bool exact, bool node, int& leaf, int& u,
+                                           uint32_t& ext) const {
         leaf = e < 0 ? -1 : (e >> 2) - 1;
         u = e < 0 ? po_index_unit(e) : e & 3;
         ext = e < 0 ? (uint32_t)e : 0u;
@@ -464,7 +483,7 @@ struct Walker {
             ext = 0;
         }
         if (ix.coarse) {
-            if (!inb & (e >= 0)) {
+            if (!inb & !node & (e >= 0)) {
                 // a leaf of level <= G: its number and level in a side table
                 const uint32_t at = ix.bytes - 8u - ((uint32_t)(e & (kIdxCoarse - 1)) << 3);
                 const auto q = __builtin_amdgcn_raw_buffer_load_b64(ix.rs, at, 0, 0);
@@ -498,13 +517,16 @@ struct Walker {
         }
         int leaf, u;
         uint32_t ext;
-        if (ix.direct) {
+        if constexpr (WAY == kDirect) {
             if (!inb & ((uint32_t)e < (uint32_t)kIdxCoarse)) {
                 bofs = ix.brick0 + (uint32_t)e * 2048u;
                 e = ix.entry_now(ix.brick_at(bofs, c));
                 inb = true;
             }
-            decode(ix, exact, leaf, u, ext);
+            decode(ix, exact, false, leaf, u, ext);
+        } else if constexpr (WAY == kPlain) {
+            descend(ix, c, stk, leaf, u);
+            ext = 0;
         } else {
             resolve(ix, c, stk, exact, leaf, u, ext);
         }
@@ -576,9 +598,15 @@ struct Walker {
         uint32_t at;
 #pragma unroll
         for (int k = 0; k < 3; ++k) c[k] = nc[k] ^ flip[k];
-        if (ix.direct) {
+        if constexpr (WAY == kDirect) {
             inb = inb & (diff < 8u);
             at = inb ? ix.brick_at(bofs, c) : ix.grid_at(c);
+        } else if constexpr (WAY == kPlain) {
+            at = 0;
+            if (!o.last) {
+                bofs = (uint32_t)(ix.D - 32 + __clz((int)diff));
+                at = ix.slot_at(c, stk[(int)bofs * kBlock], (int)bofs);
+            }
         } else {
             // the cells agree on the coordinate bits above the highest
             // differing one: without a grid the walk restarts below the deepest
@@ -694,12 +722,12 @@ struct is_chunk<S, std::void_t<decltype(S::kChunk)>> : std::bool_constant<S::kCh
 // resumed or handed on.  (Samples, so that the hand-off does not depend on how
 // empty space is crossed.)  So does reaching max_steps, which without SPLIT is
 // an error.
-template <class Sampler, bool SPLIT>
-__device__ __forceinline__ int march_queued(const KTree& tr, Ray& r, bool walk, int max_steps, int cap, bool exact,
+template <class Sampler, bool SPLIT, Way WAY>
+__device__ __forceinline__ int march_queued(const Index& ix, Ray& r, bool walk, int max_steps, int cap, bool exact,
                                             int* __restrict__ stk, Sampler& smp) {
     constexpr bool CHUNK = is_chunk<Sampler>::value;
     constexpr bool VIEW = Sampler::kView;
-    Walker<Sampler::kClip, CHUNK> w;
+    Walker<Sampler::kClip, CHUNK, WAY> w;
     Sample* Q = sample_queue();
     int steps = 0, nt = 0, bad_step = kNoCap;
     // this ray's samples in the queue: how many, the first and the last
@@ -708,7 +736,6 @@ __device__ __forceinline__ int march_queued(const KTree& tr, Ray& r, bool walk, 
     // the wave's queue: first slot and length
     uint32_t head = 0, count = 0;
     r.more = false;
-    const Index ix(tr);
     if (walk) w.start(ix, r, stk);
     while (true) {
         bool take = false;
@@ -797,14 +824,13 @@ __device__ __forceinline__ int march_queued(const KTree& tr, Ray& r, bool walk, 
 // smp.consume() shades and composites them and returns true to stop the walk.
 // The read of the next cell's entry is started before, so that compositing
 // runs while it is in flight.
-template <class Sampler, bool SPLIT>
-__device__ __forceinline__ int march_inline(const KTree& tr, Ray& r, int max_steps, int cap, bool exact,
+template <class Sampler, bool SPLIT, Way WAY>
+__device__ __forceinline__ int march_inline(const Index& ix, Ray& r, int max_steps, int cap, bool exact,
                                             int* __restrict__ stk, Sampler& smp) {
     constexpr bool CHUNK = is_chunk<Sampler>::value;
-    Walker<Sampler::kClip, CHUNK> w;
+    Walker<Sampler::kClip, CHUNK, WAY> w;
     int steps = 0, nt = 0;
     bool pending = false, stop = false;
-    const Index ix(tr);
     w.start(ix, r, stk);
     __builtin_amdgcn_sched_barrier(0);  // (the entry's load first)
     // an empty gather, so that every path into the loop has the same loads in
@@ -855,15 +881,14 @@ __device__ __forceinline__ int march_inline(const KTree& tr, Ray& r, int max_ste
 // to 403 us, 1920x1080 881 to 771.  Not for float16 (8 bytes a lane and so
 // twice the loads: 605 to 723 us at 1920x1080), nor for K = 9, whose channels
 // are no whole lines.
-template <class Sampler, bool SPLIT>
-__device__ __forceinline__ int march_quads(const KTree& tr, Ray& r, bool walk, int max_steps, int cap, bool exact,
+template <class Sampler, bool SPLIT, Way WAY>
+__device__ __forceinline__ int march_quads(const Index& ix, Ray& r, bool walk, int max_steps, int cap, bool exact,
                                            int* __restrict__ stk, Sampler& smp) {
     constexpr bool CHUNK = is_chunk<Sampler>::value;
-    Walker<Sampler::kClip, CHUNK> w;
+    Walker<Sampler::kClip, CHUNK, WAY> w;
     int steps = 0, nt = 0;
     bool live = walk, pending = false, stop = false;
     r.more = false;
-    const Index ix(tr);
     if (!walk) {  // any ray inside the box
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -915,17 +940,31 @@ __device__ __forceinline__ int march_quads(const KTree& tr, Ray& r, bool walk, i
 // 0.377) and gradients (8191 rays forward and backward: 0.291 against 0.486),
 // not for smaller records (800x800 float32 K = 16: 0.497 against 0.451) or the
 // densities alone (filter 800x800: 0.379 against 0.330).
-template <class Sampler, bool SPLIT = false>
-__device__ __forceinline__ int march(const KTree& tr, Ray& r, bool walk, int max_steps, int cap, bool exact,
-                                     int* __restrict__ stk, Sampler& smp) {
+template <class Sampler, bool SPLIT, Way WAY>
+__device__ __forceinline__ int march_way(const Index& ix, Ray& r, bool walk, int max_steps, int cap, bool exact,
+                                         int* __restrict__ stk, Sampler& smp) {
     if constexpr (Sampler::kQueued) {
-        return march_queued<Sampler, SPLIT>(tr, r, walk, max_steps, cap, exact, stk, smp);
+        return march_queued<Sampler, SPLIT, WAY>(ix, r, walk, max_steps, cap, exact, stk, smp);
     } else if constexpr (Sampler::kQuads) {
-        return march_quads<Sampler, SPLIT>(tr, r, walk, max_steps, cap, exact, stk, smp);
+        return march_quads<Sampler, SPLIT, WAY>(ix, r, walk, max_steps, cap, exact, stk, smp);
     } else {
         r.more = false;
         r.nt = 0;
-        return walk ? march_inline<Sampler, SPLIT>(tr, r, max_steps, cap, exact, stk, smp) : 0;
+        return walk ? march_inline<Sampler, SPLIT, WAY>(ix, r, max_steps, cap, exact, stk, smp) : 0;
+    }
+}
+template <bool SPLIT, Way WAY, class Sampler>
+__device__ __forceinline__ int march(const KTree& tr, Ray& r, bool walk, int max_steps, int cap, bool exact,
+                                     int* __restrict__ stk, Sampler& smp) {
+    const Index ix(tr);
+    if constexpr (WAY == kDirect) {
+        return march_way<Sampler, SPLIT, kDirect>(ix, r, walk, max_steps, cap, exact, stk, smp);
+    } else {
+        const Way way = way_of(ix.D, ix.M, ix.G);
+        if constexpr (WAY == kAny)
+            if (way == kDirect) return march_way<Sampler, SPLIT, kDirect>(ix, r, walk, max_steps, cap, exact, stk, smp);
+        if (way == kPlain) return march_way<Sampler, SPLIT, kPlain>(ix, r, walk, max_steps, cap, exact, stk, smp);
+        return march_way<Sampler, SPLIT, kNodes>(ix, r, walk, max_steps, cap, exact, stk, smp);
     }
 }
 
@@ -1306,7 +1345,7 @@ __device__ __forceinline__ void fwd_init(Smp& smp, const KTree& tr, const KOpts&
 // included), final T, samples, steps and, in the viewer variant, the expected
 // termination distance, SH subsets and the slicing plane.  V is a PO_FWD_*
 // variant.
-template <typename T, int K, int VEC, int NL, int V>
+template <typename T, int K, int VEC, int NL, int V, Way WAY>
 __device__ __forceinline__ void render_one(const KTree& tr, const KOpts& op, bool valid, const double (&o)[3],
                                            const double (&d)[3], int* __restrict__ stk, float (&C)[3], float& Tr,
                                            int& ns, int& steps, float& dep) {
@@ -1316,7 +1355,7 @@ __device__ __forceinline__ void render_one(const KTree& tr, const KOpts& op, boo
     const bool walk = valid && ray_setup(tr, o, d, r, s_lo, s_hi);
     FirstSampler<T, K, VEC, NL, V> smp;
     fwd_init<K, V>(smp, tr, op, walk, r);
-    steps = march(tr, r, walk, op.max_steps, kNoCap, exact_cells(op), stk, smp);
+    steps = march<false, WAY>(tr, r, walk, op.max_steps, kNoCap, exact_cells(op), stk, smp);
     Tr = smp.Tl;
     ns = smp.ns;
     dep = smp.dep;
@@ -1347,7 +1386,7 @@ __device__ __forceinline__ int64_t xcd_interleave(int64_t b, int64_t n_logical, 
     const int64_t l = ((j / chunk) * 8 + x) * chunk + (j % chunk);
     return l < n_logical ? l : -1;
 }
-template <typename T, int K, int VEC, int NL, int V>
+template <typename T, int K, int VEC, int NL, int V, Way WAY>
 __global__ __launch_bounds__(kBlock) void k_render_rays(KTree tr, int64_t n, int64_t n_blocks,
                                                         const float* __restrict__ o,
                                                         const float* __restrict__ d, KOpts op,
@@ -1367,7 +1406,7 @@ __global__ __launch_bounds__(kBlock) void k_render_rays(KTree tr, int64_t n, int
     float C[3], Tr, dep;
     int ns, steps;
     extern __shared__ int po_stack[];
-    render_one<T, K, VEC, NL, V>(tr, op, valid, ro, rd, po_stack + threadIdx.x, C, Tr, ns, steps, dep);
+    render_one<T, K, VEC, NL, V, WAY>(tr, op, valid, ro, rd, po_stack + threadIdx.x, C, Tr, ns, steps, dep);
     if (!valid) return;
     rgb[3 * i + 0] = C[0];
     rgb[3 * i + 1] = C[1];
@@ -1420,7 +1459,7 @@ static_assert(sizeof(KBatch<PO_BATCH_MAX_JOBS>) <= 4096, "batched kernel argumen
 
 // Camera jobs: a 16x16 tile is rendered by four single-wave workgroups, one
 // per 8x8 quadrant; lane l takes the pixel (l & 7, l >> 3) of its quadrant.
-template <typename T, int K, int VEC, int NL, int MAXJ, int V>
+template <typename T, int K, int VEC, int NL, int MAXJ, int V, Way WAY>
 __global__ __launch_bounds__(kBlock) void k_render_camera(KBatch<MAXJ> B) {
     // one camera: tile rows dealt over the XCDs; batches: one contiguous range per XCD
     const int64_t b = MAXJ == 1 ? xcd_interleave(blockIdx.x, B.n_blocks, 4 * (int64_t)B.job[0].tiles_x)
@@ -1444,7 +1483,7 @@ __global__ __launch_bounds__(kBlock) void k_render_camera(KBatch<MAXJ> B) {
     float C[3], Tr, dep;
     int ns, steps;
     extern __shared__ int po_stack[];
-    render_one<T, K, VEC, NL, V>(J.tr, J.op, valid, ro, rd, po_stack + threadIdx.x, C, Tr, ns, steps, dep);
+    render_one<T, K, VEC, NL, V, WAY>(J.tr, J.op, valid, ro, rd, po_stack + threadIdx.x, C, Tr, ns, steps, dep);
     if (!valid) return;
     const size_t p = (size_t)py * J.cam.W + px;
     J.rgb[3 * p + 0] = C[0];
@@ -1652,7 +1691,7 @@ __device__ __forceinline__ int claim_pieces(int32_t* count, int4* __restrict__ i
 // at most split_cap samples, then the ray is handed on or, if its region of
 // the queue is full, walked to its end here.  Every lane of the wave must
 // call it.
-template <typename T, int K, int VEC, int NL, int V, int SRC>
+template <typename T, int K, int VEC, int NL, int V, int SRC, Way WAY>
 __device__ __forceinline__ void first_walk(const KJob& J, const KSplit& S, int idx, bool valid) {
     const KTree& tr = J.tr;
     const KOpts& op = J.op;
@@ -1674,7 +1713,7 @@ __device__ __forceinline__ void first_walk(const KJob& J, const KSplit& S, int i
     fwd_init<K, V>(smp, tr, op, walk, r);
     // the second pass finishes the walks whose region is full
     for (int pass = 0; pass < 2; ++pass) {
-        steps += march<Smp, true>(tr, r, walk, op.max_steps - steps, pass ? kNoCap : S.split_cap, S.exact, stk, smp);
+        steps += march<true, WAY>(tr, r, walk, op.max_steps - steps, pass ? kNoCap : S.split_cap, S.exact, stk, smp);
         if (walk & r.more) {
             if (steps >= op.max_steps)
                 atomicAdd(&g_po_errors, 1ull);  // the step cap proper
@@ -1730,7 +1769,7 @@ constexpr int kPieceWaves = (V == PO_FWD_SH || V == PO_FWD_SG) && sizeof(T) * 3 
                                 ? 4
                                 : 1;
 
-template <typename T, int K, int VEC, int NL, int V>
+template <typename T, int K, int VEC, int NL, int V, Way WAY>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWaves<T, K, V>, 8))) void k_render_camera_split(KBatch<1> B, KSplit S) {
     const int64_t b = xcd_interleave(blockIdx.x, B.n_blocks, 4 * B.job[0].tiles_x);
     if (b < 0) return;
@@ -1742,16 +1781,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
     const int px = tx * 16 + (quad & 1) * 8 + (lane & 7);
     const int py = ty * 16 + (quad >> 1) * 8 + (lane >> 3);
     const bool valid = (px < J.cam.W) & (py < J.cam.H);
-    first_walk<T, K, VEC, NL, V, 0>(J, S, valid ? py * J.cam.W + px : 0, valid);
+    first_walk<T, K, VEC, NL, V, 0, WAY>(J, S, valid ? py * J.cam.W + px : 0, valid);
 }
 
-template <typename T, int K, int VEC, int NL, int V>
+template <typename T, int K, int VEC, int NL, int V, Way WAY>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWaves<T, K, V>, 8))) void k_render_rays_split(KBatch<1> B, KSplit S) {
     const int64_t b = xcd_swizzle(blockIdx.x, B.n_blocks);
     if (b < 0) return;
     const int64_t i = b * kBlock + threadIdx.x;
     const bool valid = i < S.n_rays;
-    first_walk<T, K, VEC, NL, V, 1>(B.job[0], S, valid ? (int)i : 0, valid);
+    first_walk<T, K, VEC, NL, V, 1, WAY>(B.job[0], S, valid ? (int)i : 0, valid);
 }
 
 __global__ void k_zero_i32(int32_t* __restrict__ p, int n) {
@@ -1786,7 +1825,7 @@ __device__ __forceinline__ int split_slot(const int32_t* count, int region_slots
     return -1;
 }
 
-template <typename T, int K, int VEC, int NL, int V, int SRC>
+template <typename T, int K, int VEC, int NL, int V, int SRC, Way WAY>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWaves<T, K, V>, 8))) void k_render_chunks(
     KBatch<1> B, KSplit S) {
     const int q = split_slot(S.count, S.region_slots);
@@ -1811,7 +1850,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
     fwd_init<K, V>(smp, J.tr, J.op, walk, r);
     // the second pass finishes the walks whose region is full
     for (int pass = 0; pass < 2; ++pass) {
-        steps += march<Smp, true>(J.tr, r, walk, J.op.max_steps - steps, pass ? kNoCap : S.chunk_cap, S.exact, stk, smp);
+        steps += march<true, WAY>(J.tr, r, walk, J.op.max_steps - steps, pass ? kNoCap : S.chunk_cap, S.exact, stk, smp);
         if (walk & r.more) {
             if (steps >= J.op.max_steps)
                 atomicAdd(&g_po_errors, 1ull);
@@ -1852,7 +1891,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
     }
 }
 
-template <typename T, int K, int VEC, int NL, int V, int SRC>
+template <typename T, int K, int VEC, int NL, int V, int SRC, Way WAY>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWaves<T, K, V>, 8))) void k_render_subchunks(
     KBatch<1> B, KSplit S) {
     const int q = split_slot(S.count2, S.region_slots);
@@ -1871,7 +1910,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
     }
     fwd_init<K, V>(smp, J.tr, J.op, walk, r);
     extern __shared__ int po_stack[];
-    const int steps = march(J.tr, r, walk, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
+    const int steps = march<false, WAY>(J.tr, r, walk, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
     if (h < 0) return;
     PieceOut o;
     o.c0 = smp.c0;
@@ -1905,7 +1944,7 @@ struct JoinAcc {
 // keep: over each piece's result the transmittance and colour prefix in front
 // of it is written, and whether it lies before the early stop (Tlast 1) or not
 // (-1): the prefixes a backward over these pieces differentiates from.
-template <typename T, int K, int VEC, int NL, int V, int SRC>
+template <typename T, int K, int VEC, int NL, int V, int SRC, Way WAY>
 __device__ __forceinline__ void join_ray(const KJob& J, const KSplit& S, int q, bool ray, int m, const ContHead& hd,
                                          bool keep, JoinAcc& A) {
     PieceOut* part = reinterpret_cast<PieceOut*>(S.part);
@@ -1987,7 +2026,7 @@ __device__ __forceinline__ void join_ray(const KJob& J, const KSplit& S, int q, 
         }
         fwd_init<K, V>(smp, J.tr, J.op, walk, r);
         extern __shared__ int po_stack[];
-        const int steps = march(J.tr, r, walk, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
+        const int steps = march<false, WAY>(J.tr, r, walk, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
         if (again) {
             A.c[0] += smp.c0;
             A.c[1] += smp.c1;
@@ -2007,7 +2046,7 @@ __device__ __forceinline__ void join_ray(const KJob& J, const KSplit& S, int q, 
     }
 }
 
-template <typename T, int K, int VEC, int NL, int V, int SRC>
+template <typename T, int K, int VEC, int NL, int V, int SRC, Way WAY>
 __global__ __launch_bounds__(kBlock) void k_render_join(KBatch<1> B, KSplit S) {
     const int q = split_slot(S.count, S.region_slots);
     const int4 in = q < 0 ? make_int4(-1, 0, -1, 0) : S.info[q];
@@ -2033,7 +2072,7 @@ __global__ __launch_bounds__(kBlock) void k_render_join(KBatch<1> B, KSplit S) {
             A.dep = J.aux[4 * p + 3];
         }
     }
-    join_ray<T, K, VEC, NL, V, SRC>(J, S, q, ray, in.y >> 8, hd, keep, A);
+    join_ray<T, K, VEC, NL, V, SRC, WAY>(J, S, q, ray, in.y >> 8, hd, keep, A);
     if (!ray) return;
     J.rgb[3 * p + 0] = fmaf(A.Tp, J.op.bg[0], A.c[0]);
     J.rgb[3 * p + 1] = fmaf(A.Tp, J.op.bg[1], A.c[1]);
@@ -2159,7 +2198,7 @@ __device__ __forceinline__ bool bwd_init(Smp& smp, const KTree& tr, const KOpts&
 }
 
 // Backward kernel: replays the forward walk of each ray.
-template <int K, int VEC, int NL>
+template <int K, int VEC, int NL, Way WAY>
 __global__ __launch_bounds__(kBlock) void k_backward(KTree tr, int64_t n, int64_t n_blocks,
                                                      const float* __restrict__ o,
                                                      const float* __restrict__ d, KOpts op,
@@ -2179,7 +2218,7 @@ __global__ __launch_bounds__(kBlock) void k_backward(KTree tr, int64_t n, int64_
     BwdSampler<K, VEC, NL> smp;
     ray = bwd_init<K>(smp, tr, op, ray, r, (size_t)i, rgb_fwd, grad, gsig, gsh);
     extern __shared__ int po_stack[];
-    march(tr, r, ray, op.max_steps, kNoCap, exact_cells(op), po_stack + threadIdx.x, smp);
+    march<false, WAY>(tr, r, ray, op.max_steps, kNoCap, exact_cells(op), po_stack + threadIdx.x, smp);
 }
 
 // ---------------------------------------------------------------------------
@@ -2201,7 +2240,7 @@ __global__ __launch_bounds__(kBlock) void k_backward(KTree tr, int64_t n, int64_
 //   k_backward_pieces     the backward of every piece before the stop, from
 //                         its T and P (chunks, then sub-chunks).
 // ---------------------------------------------------------------------------
-template <int K, int VEC, int NL>
+template <int K, int VEC, int NL, Way WAY>
 __global__ __launch_bounds__(kBlock) void k_backward_split(KBatch<1> B, KSplit S, const float* __restrict__ rgb_fwd,
                                                            const float* __restrict__ grad, float* __restrict__ gsig,
                                                            float* __restrict__ gsh) {
@@ -2226,7 +2265,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_split(KBatch<1> B, KSplit S
     if (live) *walk_range() = make_double2(r.s, r.s_exit);
     // the second pass finishes the walks whose region is full
     for (int pass = 0; pass < 2; ++pass) {
-        steps += march<Smp, true>(tr, r, live, J.op.max_steps - steps, pass ? kNoCap : S.split_cap, S.exact, stk, smp);
+        steps += march<true, WAY>(tr, r, live, J.op.max_steps - steps, pass ? kNoCap : S.split_cap, S.exact, stk, smp);
         if (live & r.more) {
             if (steps >= J.op.max_steps)
                 atomicAdd(&g_po_errors, 1ull);
@@ -2258,7 +2297,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_split(KBatch<1> B, KSplit S
 // split_cap samples and its pieces are not walked forward again; a ray it
 // did not hand on (ended within the first walk, or its region was full) is
 // differentiated to its end here.
-template <int K, int VEC, int NL>
+template <int K, int VEC, int NL, Way WAY>
 __global__ __launch_bounds__(kBlock) void k_backward_first_kept(KBatch<1> B, KSplit S,
                                                                 const float* __restrict__ rgb_fwd,
                                                                 const float* __restrict__ grad,
@@ -2280,13 +2319,13 @@ __global__ __launch_bounds__(kBlock) void k_backward_first_kept(KBatch<1> B, KSp
         live = ray_setup(tr, ro, rd, r);
     }
     live = bwd_init<K>(smp, tr, J.op, live, r, (size_t)i, rgb_fwd, grad, gsig, gsh);
-    const int steps = march<Smp, true>(tr, r, live, J.op.max_steps, handed ? S.split_cap : kNoCap, S.exact,
+    const int steps = march<true, WAY>(tr, r, live, J.op.max_steps, handed ? S.split_cap : kNoCap, S.exact,
                                        po_stack + threadIdx.x, smp);
     if (live & r.more & (steps >= J.op.max_steps)) atomicAdd(&g_po_errors, 1ull);  // the step cap proper
 }
 
 // The prefixes of a ray's pieces, as the join of a kept render writes them.
-template <int K, int VEC, int NL, int V>
+template <int K, int VEC, int NL, int V, Way WAY>
 __global__ __launch_bounds__(kBlock) void k_piece_prefix(KBatch<1> B, KSplit S) {
     const int q = split_slot(S.count, S.region_slots);
     const int4 in = q < 0 ? make_int4(-1, 0, -1, 0) : S.info[q];
@@ -2301,13 +2340,13 @@ __global__ __launch_bounds__(kBlock) void k_piece_prefix(KBatch<1> B, KSplit S) 
     A.c[2] = hd.c2;
     A.dep = 0.0f;
     A.ns = A.steps = A.cut_smp = A.cut = 0;
-    join_ray<float, K, VEC, NL, V, 1>(B.job[0], S, q, ray, in.y >> 8, hd, true, A);
+    join_ray<float, K, VEC, NL, V, 1, WAY>(B.job[0], S, q, ray, in.y >> 8, hd, true, A);
 }
 
 // The first kSplitRegions * region_slots / kBlock workgroups take the walked parts of the
 // chunks, the others the sub-chunks: the two sets are independent once their
 // prefixes are known, so one launch overlaps their tails.
-template <int K, int VEC, int NL>
+template <int K, int VEC, int NL, Way WAY>
 __global__ __launch_bounds__(kBlock) void k_backward_pieces(KBatch<1> B, KSplit S, const float* __restrict__ rgb_fwd,
                                                             const float* __restrict__ grad, float* __restrict__ gsig,
                                                             float* __restrict__ gsh) {
@@ -2348,7 +2387,7 @@ __global__ __launch_bounds__(kBlock) void k_backward_pieces(KBatch<1> B, KSplit 
     smp.P1 = o.c1;
     smp.P2 = o.c2;
     extern __shared__ int po_stack[];
-    march(J.tr, r, live, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
+    march<false, WAY>(J.tr, r, live, J.op.max_steps, kNoCap, S.exact, po_stack + threadIdx.x, smp);
 }
 
 // Visibility filter of the conversion (Sec. 4.2, "Filtering"): alpha
@@ -2392,7 +2431,7 @@ struct WeightSampler {
 
 // One camera, 16x16 tiles of four 8x8 single-wave workgroups as in
 // k_render_camera; alpha (or nullptr) receives 1 - T per pixel.
-template <typename T, int MODE>
+template <typename T, int MODE, Way WAY>
 __global__ __launch_bounds__(kBlock) void k_leaf_weights(KTree tr, KCam cam, KOpts op, int n_blocks,
                                                          unsigned* __restrict__ wt, float* __restrict__ alpha) {
     const int tiles_x = (cam.W + 15) / 16;
@@ -2413,8 +2452,56 @@ __global__ __launch_bounds__(kBlock) void k_leaf_weights(KTree tr, KCam cam, KOp
     smp.stopT = op.stop_T;
     smp.wt = wt;
     extern __shared__ int po_stack[];
-    march(tr, r, walk, op.max_steps, kNoCap, exact_cells(op), po_stack + threadIdx.x, smp);
+    march<false, WAY>(tr, r, walk, op.max_steps, kNoCap, exact_cells(op), po_stack + threadIdx.x, smp);
     if (valid && alpha) alpha[(size_t)py * cam.W + px] = 1.0f - smp.Tl;
+}
+
+// One ray of k_traversal_stats: adds its samples, cells and loads.
+template <typename T, Way WAY>
+__device__ __forceinline__ void stats_walk(const KTree& tr, const Index& ix, const KOpts& op, Ray& r, int* stk,
+                                           unsigned long long (&v)[4]) {
+    const __amdgpu_buffer_rsrc_t sig = raw_rsrc(tr.sigma, tr.sigma_bytes);
+    Walker<false, false, WAY> w;
+    w.start(ix, r, stk);
+    const int D = tr.depth(), M = tr.brick_level();
+    // la: level the descent to the cell starts from; was_in: the cell
+    // before lay in a brick
+    int steps = 0, ns = 0, loads = 0, la = 0;
+    bool was_in = false, pending = false, bad = false;
+    uint32_t raw = 0;
+    float Tl = 1.0f, delta = 0.0f;
+    while (true) {
+        ++steps;
+        const int from[3] = {r.c[0], r.c[1], r.c[2]};
+        const Cell c = w.step(ix, r, true, steps >= op.max_steps, false, stk);
+        const int lvl = D - c.u;
+        loads += (was_in & (la >= M)) ? 1 : (lvl <= M ? lvl - la : M - la + 1);
+        was_in = lvl > M;
+        la = D - 32 + __clz((from[0] ^ r.c[0]) | (from[1] ^ r.c[1]) | (from[2] ^ r.c[2]));
+        bad |= r.more;
+        // the previous sample is composited one cell later, as the
+        // render counts it
+        bool stop = false;
+        if (pending) {
+            ++ns;
+            const float s = fmaxf(sigma_of<T>(raw), 0.0f);
+            if (s > 0.0f) {
+                Tl = Tl * __expf(-(s * delta));
+                stop = Tl < op.stop_T;
+            }
+        }
+        pending = !stop & (c.leaf >= 0) & (c.delta > 0.0f);
+        if (pending) {
+            raw = sigma_buf(sig, (uint32_t)c.leaf * (uint32_t)sizeof(T), (T*)nullptr);
+            delta = c.delta;
+        }
+        if (c.last | stop) break;
+    }
+    if (pending) ++ns;
+    if (bad | (w.bad != 0)) atomicAdd(&g_po_errors, 1ull);
+    v[2] = (unsigned long long)steps;
+    v[1] = (unsigned long long)ns;
+    v[3] = (unsigned long long)loads;
 }
 
 // Traversal statistics of a camera render: the walk of the octree's own cells
@@ -2458,51 +2545,14 @@ __global__ __launch_bounds__(kBlock) void k_traversal_stats(KTree tr, KCam cam, 
     if (valid) {
         Ray r;
         if (ray_setup(tr, ro, rd, r)) {
-            const __amdgpu_buffer_rsrc_t sig = raw_rsrc(tr.sigma, tr.sigma_bytes);
             extern __shared__ int po_stack[];
             int* stk = po_stack + threadIdx.x;
-            Walker<false, false> w;
             const Index ix(tr);
-            w.start(ix, r, stk);
-            const int D = tr.depth(), M = tr.brick_level();
-            // la: level the descent to the cell starts from; was_in: the cell
-            // before lay in a brick
-            int steps = 0, ns = 0, loads = 0, la = 0;
-            bool was_in = false, pending = false, bad = false;
-            uint32_t raw = 0;
-            float Tl = 1.0f, delta = 0.0f;
-            while (true) {
-                ++steps;
-                const int from[3] = {r.c[0], r.c[1], r.c[2]};
-                const Cell c = w.step(ix, r, true, steps >= op.max_steps, false, stk);
-                const int lvl = D - c.u;
-                loads += (was_in & (la >= M)) ? 1 : (lvl <= M ? lvl - la : M - la + 1);
-                was_in = lvl > M;
-                la = D - 32 + __clz((from[0] ^ r.c[0]) | (from[1] ^ r.c[1]) | (from[2] ^ r.c[2]));
-                bad |= r.more;
-                // the previous sample is composited one cell later, as the
-                // render counts it
-                bool stop = false;
-                if (pending) {
-                    ++ns;
-                    const float s = fmaxf(sigma_of<T>(raw), 0.0f);
-                    if (s > 0.0f) {
-                        Tl = Tl * __expf(-(s * delta));
-                        stop = Tl < op.stop_T;
-                    }
-                }
-                pending = !stop & (c.leaf >= 0) & (c.delta > 0.0f);
-                if (pending) {
-                    raw = sigma_buf(sig, (uint32_t)c.leaf * (uint32_t)sizeof(T), (T*)nullptr);
-                    delta = c.delta;
-                }
-                if (c.last | stop) break;
+            switch (way_of(ix.D, ix.M, ix.G)) {
+            case kDirect: stats_walk<T, kDirect>(tr, ix, op, r, stk, v); break;
+            case kPlain: stats_walk<T, kPlain>(tr, ix, op, r, stk, v); break;
+            default: stats_walk<T, kNodes>(tr, ix, op, r, stk, v);
             }
-            if (pending) ++ns;
-            if (bad | (w.bad != 0)) atomicAdd(&g_po_errors, 1ull);
-            v[2] = (unsigned long long)steps;
-            v[1] = (unsigned long long)ns;
-            v[3] = (unsigned long long)loads;
         }
     }
 #pragma unroll
@@ -2758,10 +2808,16 @@ inline int64_t grid_for(int64_t n_blocks) { return 8 * ((n_blocks + 7) / 8); }
 // Grid of xcd_interleave over n_blocks logical workgroups in runs of chunk.
 inline int64_t rows_grid(int64_t n_blocks, int64_t chunk) { return 8 * chunk * (((n_blocks + chunk - 1) / chunk + 7) / 8); }
 
+inline bool is_direct(const KTree& t) { return way_of(t.depth(), t.brick_level(), t.grid_level()) == kDirect; }inline bool all_direct(int n_jobs, const KJob* jobs) {
+    for (int j = 0; j < n_jobs; ++j)
+        if (!is_direct(jobs[j].tr)) return false;
+    return true;
+}
+
 // Dynamic LDS of the node stack: one int per lane and tree level.  Trees whose
 // grid reaches the brick level keep no node path.
 inline size_t stack_bytes(const KTree& t) {
-    return t.grid_level() > 0 && t.grid_level() == t.brick_level() ? 0 : sizeof(int) * kBlock * (size_t)t.depth();
+    return is_direct(t) ? 0 : sizeof(int) * kBlock * (size_t)t.depth();
 }
 
 // Record-load plan: "fast" loads the padded record with the widest vectors,
@@ -2795,7 +2851,7 @@ bool use_fast_cb(const po_tree* t) {
     return t->vec_bytes >= P::FAST_VEC && t->stride >= P::FAST_NL && ((size_t)t->stride * 2) % P::FAST_VEC == 0;
 }
 
-template <typename T, int K>
+template <typename T, int K, Way W>
 hipError_t rays_t(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op, float* rgb,
                   float* aux, hipStream_t s) {
     using P = Plan<T, K>;
@@ -2809,10 +2865,10 @@ hipError_t rays_t(const po_tree* t, int64_t n, const float* o, const float* d, c
         if (v == PO_FWD_CB) {
             using Q = CbPlan<K>;
             if (use_fast_cb<K>(t))
-                hipLaunchKernelGGL((k_render_rays<T, K, Q::FAST_VEC, Q::FAST_NL, PO_FWD_CB>), grid, block, lds, s,
+                hipLaunchKernelGGL((k_render_rays<T, K, Q::FAST_VEC, Q::FAST_NL, PO_FWD_CB, W>), grid, block, lds, s,
                                    t->kt, n, nb, o, d, op, rgb, nullptr);
             else
-                hipLaunchKernelGGL((k_render_rays<T, K, 4, Q::GEN_NL, PO_FWD_CB>), grid, block, lds, s, t->kt, n, nb,
+                hipLaunchKernelGGL((k_render_rays<T, K, 4, Q::GEN_NL, PO_FWD_CB, W>), grid, block, lds, s, t->kt, n, nb,
                                    o, d, op, rgb, nullptr);
             return hipGetLastError();
         }
@@ -2820,10 +2876,10 @@ hipError_t rays_t(const po_tree* t, int64_t n, const float* o, const float* d, c
 #define PO_RAYS(V_)                                                                                              \
     do {                                                                                                        \
         if (fast)                                                                                               \
-            hipLaunchKernelGGL((k_render_rays<T, K, P::FAST_VEC, P::FAST_NL, V_>), grid, block, lds, s, t->kt, n, \
+            hipLaunchKernelGGL((k_render_rays<T, K, P::FAST_VEC, P::FAST_NL, V_, W>), grid, block, lds, s, t->kt, n, \
                                nb, o, d, op, rgb, aux);                                                         \
         else                                                                                                    \
-            hipLaunchKernelGGL((k_render_rays<T, K, 4, P::GEN_NL, V_>), grid, block, lds, s, t->kt, n, nb, o, d, \
+            hipLaunchKernelGGL((k_render_rays<T, K, 4, P::GEN_NL, V_, W>), grid, block, lds, s, t->kt, n, nb, o, d, \
                                op, rgb, aux);                                                                   \
     } while (0)
     if (v == PO_FWD_VIEW)
@@ -2836,7 +2892,7 @@ hipError_t rays_t(const po_tree* t, int64_t n, const float* o, const float* d, c
     return hipGetLastError();
 }
 
-template <typename T, int K, int MAXJ>
+template <typename T, int K, int MAXJ, Way W>
 hipError_t camera_t(const po_tree* t, int n_jobs, KJob* jobs, int n_blocks, int variant, hipStream_t s) {
     using P = Plan<T, K>;
     KBatch<MAXJ> B;
@@ -2852,10 +2908,10 @@ hipError_t camera_t(const po_tree* t, int n_jobs, KJob* jobs, int n_blocks, int 
         if (variant == PO_FWD_CB) {
             using Q = CbPlan<K>;
             if (use_fast_cb<K>(t))
-                hipLaunchKernelGGL((k_render_camera<T, K, Q::FAST_VEC, Q::FAST_NL, MAXJ, PO_FWD_CB>), grid, block, lds,
+                hipLaunchKernelGGL((k_render_camera<T, K, Q::FAST_VEC, Q::FAST_NL, MAXJ, PO_FWD_CB, W>), grid, block, lds,
                                    s, B);
             else
-                hipLaunchKernelGGL((k_render_camera<T, K, 4, Q::GEN_NL, MAXJ, PO_FWD_CB>), grid, block, lds, s, B);
+                hipLaunchKernelGGL((k_render_camera<T, K, 4, Q::GEN_NL, MAXJ, PO_FWD_CB, W>), grid, block, lds, s, B);
             return hipGetLastError();
         }
     }
@@ -2863,9 +2919,9 @@ hipError_t camera_t(const po_tree* t, int n_jobs, KJob* jobs, int n_blocks, int 
 #define PO_CAM(V_)                                                                                               \
     do {                                                                                                        \
         if (fast)                                                                                               \
-            hipLaunchKernelGGL((k_render_camera<T, K, P::FAST_VEC, P::FAST_NL, MAXJ, V_>), grid, block, lds, s, B); \
+            hipLaunchKernelGGL((k_render_camera<T, K, P::FAST_VEC, P::FAST_NL, MAXJ, V_, W>), grid, block, lds, s, B); \
         else                                                                                                    \
-            hipLaunchKernelGGL((k_render_camera<T, K, 4, P::GEN_NL, MAXJ, V_>), grid, block, lds, s, B);        \
+            hipLaunchKernelGGL((k_render_camera<T, K, 4, P::GEN_NL, MAXJ, V_, W>), grid, block, lds, s, B);        \
     } while (0)
     if (variant == PO_FWD_VIEW)
         PO_CAM(PO_FWD_VIEW);
@@ -2877,7 +2933,7 @@ hipError_t camera_t(const po_tree* t, int n_jobs, KJob* jobs, int n_blocks, int 
     return hipGetLastError();
 }
 
-template <typename T, int K, int SRC>
+template <typename T, int K, int SRC, Way W>
 hipError_t split_t(const po_tree* t, const KJob& job, int n_blocks, int variant, const KSplit& S, hipStream_t s) {
     using P = Plan<T, K>;
     KBatch<1> B;
@@ -2895,12 +2951,12 @@ hipError_t split_t(const po_tree* t, const KJob& job, int n_blocks, int variant,
 #define PO_SPLIT(VEC_, NL_, V_)                                                                        \
     do {                                                                                              \
         if constexpr (SRC == 0)                                                                       \
-            hipLaunchKernelGGL((k_render_camera_split<T, K, VEC_, NL_, V_>), g1, blk, lds, s, B, S);  \
+            hipLaunchKernelGGL((k_render_camera_split<T, K, VEC_, NL_, V_, W>), g1, blk, lds, s, B, S);  \
         else                                                                                          \
-            hipLaunchKernelGGL((k_render_rays_split<T, K, VEC_, NL_, V_>), g1, blk, lds, s, B, S);    \
-        hipLaunchKernelGGL((k_render_chunks<T, K, VEC_, NL_, V_, SRC>), g2, blk, lds, s, B, S);      \
-        hipLaunchKernelGGL((k_render_subchunks<T, K, VEC_, NL_, V_, SRC>), g2, blk, lds, s, B, S);   \
-        hipLaunchKernelGGL((k_render_join<T, K, VEC_, NL_, V_, SRC>), g2, blk, lds, s, B, S);        \
+            hipLaunchKernelGGL((k_render_rays_split<T, K, VEC_, NL_, V_, W>), g1, blk, lds, s, B, S);    \
+        hipLaunchKernelGGL((k_render_chunks<T, K, VEC_, NL_, V_, SRC, W>), g2, blk, lds, s, B, S);      \
+        hipLaunchKernelGGL((k_render_subchunks<T, K, VEC_, NL_, V_, SRC, W>), g2, blk, lds, s, B, S);   \
+        hipLaunchKernelGGL((k_render_join<T, K, VEC_, NL_, V_, SRC, W>), g2, blk, lds, s, B, S);        \
     } while (0)
     if constexpr (std::is_same_v<T, __half>) {
         if (variant == PO_FWD_CB) {
@@ -2932,7 +2988,7 @@ hipError_t split_t(const po_tree* t, const KJob& job, int n_blocks, int variant,
     return hipGetLastError();
 }
 
-template <int K>
+template <int K, Way W>
 hipError_t backward_split_t(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                             const float* rgb_fwd, const float* grad, float* gsig, float* gsh, const KSplit& S0,
                             hipStream_t s) {
@@ -2957,17 +3013,17 @@ hipError_t backward_split_t(const po_tree* t, int64_t n, const float* o, const f
     const bool sg = t->kt.lobes != nullptr;
 #define PO_BSPLIT(VEC_, NL_)                                                                                    \
     do {                                                                                                       \
-        hipLaunchKernelGGL((k_backward_split<K, VEC_, NL_>), g1, blk, lds, s, B, S, rgb_fwd, grad, gsig, gsh); \
+        hipLaunchKernelGGL((k_backward_split<K, VEC_, NL_, W>), g1, blk, lds, s, B, S, rgb_fwd, grad, gsig, gsh); \
         if (sg) {                                                                                              \
-            hipLaunchKernelGGL((k_render_chunks<float, K, VEC_, NL_, PO_FWD_SG, 1>), g2, blk, lds, s, B, S);   \
-            hipLaunchKernelGGL((k_render_subchunks<float, K, VEC_, NL_, PO_FWD_SG, 1>), g2, blk, lds, s, B, S); \
-            hipLaunchKernelGGL((k_piece_prefix<K, VEC_, NL_, PO_FWD_SG>), g2, blk, lds, s, B, S);              \
+            hipLaunchKernelGGL((k_render_chunks<float, K, VEC_, NL_, PO_FWD_SG, 1, W>), g2, blk, lds, s, B, S);   \
+            hipLaunchKernelGGL((k_render_subchunks<float, K, VEC_, NL_, PO_FWD_SG, 1, W>), g2, blk, lds, s, B, S); \
+            hipLaunchKernelGGL((k_piece_prefix<K, VEC_, NL_, PO_FWD_SG, W>), g2, blk, lds, s, B, S);              \
         } else {                                                                                               \
-            hipLaunchKernelGGL((k_render_chunks<float, K, VEC_, NL_, PO_FWD_SH, 1>), g2, blk, lds, s, B, S);   \
-            hipLaunchKernelGGL((k_render_subchunks<float, K, VEC_, NL_, PO_FWD_SH, 1>), g2, blk, lds, s, B, S); \
-            hipLaunchKernelGGL((k_piece_prefix<K, VEC_, NL_, PO_FWD_SH>), g2, blk, lds, s, B, S);              \
+            hipLaunchKernelGGL((k_render_chunks<float, K, VEC_, NL_, PO_FWD_SH, 1, W>), g2, blk, lds, s, B, S);   \
+            hipLaunchKernelGGL((k_render_subchunks<float, K, VEC_, NL_, PO_FWD_SH, 1, W>), g2, blk, lds, s, B, S); \
+            hipLaunchKernelGGL((k_piece_prefix<K, VEC_, NL_, PO_FWD_SH, W>), g2, blk, lds, s, B, S);              \
         }                                                                                                      \
-        hipLaunchKernelGGL((k_backward_pieces<K, VEC_, NL_>), g3, blk, lds, s, B, S, rgb_fwd, grad, gsig, gsh);    \
+        hipLaunchKernelGGL((k_backward_pieces<K, VEC_, NL_, W>), g3, blk, lds, s, B, S, rgb_fwd, grad, gsig, gsh);    \
     } while (0)
     if (use_fast<float, K>(t))
         PO_BSPLIT(P::FAST_VEC, P::FAST_NL);
@@ -2981,7 +3037,7 @@ hipError_t backward_split_t(const po_tree* t, int64_t n, const float* o, const f
 // its join wrote each piece's prefix over the piece's result, so neither
 // the chunk and sub-chunk kernels nor k_piece_prefix run again, and the
 // counters are not cleared.
-template <int K>
+template <int K, Way W>
 hipError_t backward_kept_t(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                            const float* rgb_fwd, const float* grad, float* gsig, float* gsh, const KSplit& S0,
                            hipStream_t s) {
@@ -3002,9 +3058,9 @@ hipError_t backward_kept_t(const po_tree* t, int64_t n, const float* o, const fl
     const size_t lds = stack_bytes(t->kt);
 #define PO_BKEPT(VEC_, NL_)                                                                                       \
     do {                                                                                                         \
-        hipLaunchKernelGGL((k_backward_first_kept<K, VEC_, NL_>), g1, blk, lds, s, B, S, rgb_fwd, grad, gsig,    \
+        hipLaunchKernelGGL((k_backward_first_kept<K, VEC_, NL_, W>), g1, blk, lds, s, B, S, rgb_fwd, grad, gsig,    \
                            gsh);                                                                                 \
-        hipLaunchKernelGGL((k_backward_pieces<K, VEC_, NL_>), g3, blk, lds, s, B, S, rgb_fwd, grad, gsig, gsh);  \
+        hipLaunchKernelGGL((k_backward_pieces<K, VEC_, NL_, W>), g3, blk, lds, s, B, S, rgb_fwd, grad, gsig, gsh);  \
     } while (0)
     if (use_fast<float, K>(t))
         PO_BKEPT(P::FAST_VEC, P::FAST_NL);
@@ -3014,23 +3070,25 @@ hipError_t backward_kept_t(const po_tree* t, int64_t n, const float* o, const fl
     return hipGetLastError();
 }
 
-template <int K>
+template <int K, Way W>
 hipError_t backward_t(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                       const float* rgb_fwd, const float* grad, float* gsig, float* gsh, hipStream_t s) {
     using P = Plan<float, K>;
     const int64_t nb = (n + kBlock - 1) / kBlock;
     dim3 grid((unsigned)grid_for(nb)), block(kBlock);
     if (use_fast<float, K>(t))
-        hipLaunchKernelGGL((k_backward<K, P::FAST_VEC, P::FAST_NL>), grid, block, stack_bytes(t->kt), s,
+        hipLaunchKernelGGL((k_backward<K, P::FAST_VEC, P::FAST_NL, W>), grid, block, stack_bytes(t->kt), s,
                            t->kt, n, nb, o, d, op, rgb_fwd, grad, gsig, gsh);
     else
-        hipLaunchKernelGGL((k_backward<K, 4, P::GEN_NL>), grid, block, stack_bytes(t->kt), s, t->kt, n, nb,
+        hipLaunchKernelGGL((k_backward<K, 4, P::GEN_NL, W>), grid, block, stack_bytes(t->kt), s, t->kt, n, nb,
                            o, d, op, rgb_fwd, grad, gsig, gsh);
     return hipGetLastError();
 }
 
 }  // namespace
 
+// EXPR with the coefficient count KK of a tree and, PO_DISPATCH, the walk W of
+// its kernels (OTHER: for trees that are not direct).
 #define PO_DISPATCH_K(K_, EXPR)                      \
     switch (K_) {                                    \
         case 1: { constexpr int KK = 1; return EXPR; }   \
@@ -3040,6 +3098,15 @@ hipError_t backward_t(const po_tree* t, int64_t n, const float* o, const float* 
         case 25: { constexpr int KK = 25; return EXPR; } \
         default: return hipErrorInvalidValue;        \
     }
+#define PO_DISPATCH(K_, DIRECT_, OTHER_, EXPR)       \
+    do {                                             \
+        if (DIRECT_) {                               \
+            constexpr Way W = kDirect;               \
+            PO_DISPATCH_K(K_, EXPR)                  \
+        }                                            \
+        constexpr Way W = OTHER_;                    \
+        PO_DISPATCH_K(K_, EXPR)                      \
+    } while (0)
 
 // Launchers of the parts, by leaf type (defined in the part named).
 hipError_t po_camera_jobs_f32(const po_tree* first, int n_jobs, KJob* jobs, int n_blocks, int variant,
@@ -3080,10 +3147,11 @@ PO_PART_ERRORS_DECL(7)
 PO_PART_ERRORS_DEF(1)
 hipError_t po_camera_jobs_f32(const po_tree* first, int n_jobs, KJob* jobs, int n_blocks, int variant,
                               hipStream_t s) {
-    if (n_jobs == 1) {
-        PO_DISPATCH_K(first->K, (camera_t<float, KK, 1>(first, n_jobs, jobs, n_blocks, variant, s)));
-    }
-    PO_DISPATCH_K(first->K, (camera_t<float, KK, PO_BATCH_MAX_JOBS>(first, n_jobs, jobs, n_blocks, variant, s)));
+    if (n_jobs == 1)
+        PO_DISPATCH(first->K, is_direct(first->kt), kOther,
+                    (camera_t<float, KK, 1, W>(first, n_jobs, jobs, n_blocks, variant, s)));
+    PO_DISPATCH(first->K, all_direct(n_jobs, jobs), kAny,
+                (camera_t<float, KK, PO_BATCH_MAX_JOBS, W>(first, n_jobs, jobs, n_blocks, variant, s)));
 }
 #endif
 
@@ -3091,10 +3159,11 @@ hipError_t po_camera_jobs_f32(const po_tree* first, int n_jobs, KJob* jobs, int 
 PO_PART_ERRORS_DEF(2)
 hipError_t po_camera_jobs_f16(const po_tree* first, int n_jobs, KJob* jobs, int n_blocks, int variant,
                               hipStream_t s) {
-    if (n_jobs == 1) {
-        PO_DISPATCH_K(first->K, (camera_t<__half, KK, 1>(first, n_jobs, jobs, n_blocks, variant, s)));
-    }
-    PO_DISPATCH_K(first->K, (camera_t<__half, KK, PO_BATCH_MAX_JOBS>(first, n_jobs, jobs, n_blocks, variant, s)));
+    if (n_jobs == 1)
+        PO_DISPATCH(first->K, is_direct(first->kt), kOther,
+                    (camera_t<__half, KK, 1, W>(first, n_jobs, jobs, n_blocks, variant, s)));
+    PO_DISPATCH(first->K, all_direct(n_jobs, jobs), kAny,
+                (camera_t<__half, KK, PO_BATCH_MAX_JOBS, W>(first, n_jobs, jobs, n_blocks, variant, s)));
 }
 #endif
 
@@ -3102,7 +3171,7 @@ hipError_t po_camera_jobs_f16(const po_tree* first, int n_jobs, KJob* jobs, int 
 PO_PART_ERRORS_DEF(3)
 hipError_t po_camera_split_f32(const po_tree* t, const KJob& job, int n_blocks, int variant, const KSplit& S,
                                hipStream_t s) {
-    PO_DISPATCH_K(t->K, (split_t<float, KK, 0>(t, job, n_blocks, variant, S, s)));
+    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (split_t<float, KK, 0, W>(t, job, n_blocks, variant, S, s)));
 }
 #endif
 
@@ -3110,7 +3179,7 @@ hipError_t po_camera_split_f32(const po_tree* t, const KJob& job, int n_blocks, 
 PO_PART_ERRORS_DEF(4)
 hipError_t po_camera_split_f16(const po_tree* t, const KJob& job, int n_blocks, int variant, const KSplit& S,
                                hipStream_t s) {
-    PO_DISPATCH_K(t->K, (split_t<__half, KK, 0>(t, job, n_blocks, variant, S, s)));
+    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (split_t<__half, KK, 0, W>(t, job, n_blocks, variant, S, s)));
 }
 #endif
 
@@ -3118,7 +3187,7 @@ hipError_t po_camera_split_f16(const po_tree* t, const KJob& job, int n_blocks, 
 PO_PART_ERRORS_DEF(5)
 hipError_t po_rays_split_f32(const po_tree* t, const KJob& job, int n_blocks, int variant, const KSplit& S,
                              hipStream_t s) {
-    PO_DISPATCH_K(t->K, (split_t<float, KK, 1>(t, job, n_blocks, variant, S, s)));
+    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (split_t<float, KK, 1, W>(t, job, n_blocks, variant, S, s)));
 }
 #endif
 
@@ -3126,7 +3195,7 @@ hipError_t po_rays_split_f32(const po_tree* t, const KJob& job, int n_blocks, in
 PO_PART_ERRORS_DEF(6)
 hipError_t po_rays_split_f16(const po_tree* t, const KJob& job, int n_blocks, int variant, const KSplit& S,
                              hipStream_t s) {
-    PO_DISPATCH_K(t->K, (split_t<__half, KK, 1>(t, job, n_blocks, variant, S, s)));
+    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (split_t<__half, KK, 1, W>(t, job, n_blocks, variant, S, s)));
 }
 #endif
 
@@ -3135,13 +3204,13 @@ PO_PART_ERRORS_DEF(7)
 hipError_t po_launch_backward_split(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                                     const float* rgb_fwd, const float* grad, float* gsig, float* gsh,
                                     const KSplit& S, hipStream_t s) {
-    PO_DISPATCH_K(t->K, (backward_split_t<KK>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, S, s)));
+    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (backward_split_t<KK, W>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, S, s)));
 }
 
 hipError_t po_launch_backward_kept(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                                    const float* rgb_fwd, const float* grad, float* gsig, float* gsh,
                                    const KSplit& S, hipStream_t s) {
-    PO_DISPATCH_K(t->K, (backward_kept_t<KK>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, S, s)));
+    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (backward_kept_t<KK, W>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, S, s)));
 }
 #endif
 
@@ -3150,9 +3219,9 @@ PO_PART_ERRORS_DEF(0)
 hipError_t po_launch_rays(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                           float* rgb, float* aux, hipStream_t s) {
     if (t->desc.dtype == PO_F32) {
-        PO_DISPATCH_K(t->K, (rays_t<float, KK>(t, n, o, d, op, rgb, aux, s)));
+        PO_DISPATCH(t->K, is_direct(t->kt), kOther, (rays_t<float, KK, W>(t, n, o, d, op, rgb, aux, s)));
     } else {
-        PO_DISPATCH_K(t->K, (rays_t<__half, KK>(t, n, o, d, op, rgb, aux, s)));
+        PO_DISPATCH(t->K, is_direct(t->kt), kOther, (rays_t<__half, KK, W>(t, n, o, d, op, rgb, aux, s)));
     }
 }
 
@@ -3193,7 +3262,7 @@ hipError_t po_launch_rays_split(const po_tree* t, int64_t n, const float* o, con
 
 hipError_t po_launch_backward(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                               const float* rgb_fwd, const float* grad, float* gsig, float* gsh, hipStream_t s) {
-    PO_DISPATCH_K(t->K, (backward_t<KK>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, s)));
+    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (backward_t<KK, W>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, s)));
 }
 
 hipError_t po_launch_index(const int32_t* nodes, int n_top, int G, int unit, int64_t n_bricks, int32_t* grid,
@@ -3215,17 +3284,28 @@ hipError_t po_launch_leaf_weights(const po_tree* t, const KCam& cam, const KOpts
     dim3 grid((unsigned)rows_grid(n_blocks, 4 * (int64_t)((cam.W + 15) / 16))), block(kBlock);
     const size_t lds = stack_bytes(t->kt);
     unsigned* wt = reinterpret_cast<unsigned*>(weight);
+    const bool direct = is_direct(t->kt);
+#define PO_WEIGHTS(T_, MODE_)                                                                                          \
+    do {                                                                                                             \
+        if (direct)                                                                                                  \
+            hipLaunchKernelGGL((k_leaf_weights<T_, MODE_, kDirect>), grid, block, lds, s, t->kt, cam, op, n_blocks, wt, \
+                               alpha);                                                                               \
+        else                                                                                                         \
+            hipLaunchKernelGGL((k_leaf_weights<T_, MODE_, kOther>), grid, block, lds, s, t->kt, cam, op, n_blocks, wt,  \
+                               alpha);                                                                               \
+    } while (0)
     if (t->desc.dtype == PO_F32) {
         if (mode == 0)
-            hipLaunchKernelGGL((k_leaf_weights<float, 0>), grid, block, lds, s, t->kt, cam, op, n_blocks, wt, alpha);
+            PO_WEIGHTS(float, 0);
         else
-            hipLaunchKernelGGL((k_leaf_weights<float, 1>), grid, block, lds, s, t->kt, cam, op, n_blocks, wt, alpha);
+            PO_WEIGHTS(float, 1);
     } else {
         if (mode == 0)
-            hipLaunchKernelGGL((k_leaf_weights<__half, 0>), grid, block, lds, s, t->kt, cam, op, n_blocks, wt, alpha);
+            PO_WEIGHTS(__half, 0);
         else
-            hipLaunchKernelGGL((k_leaf_weights<__half, 1>), grid, block, lds, s, t->kt, cam, op, n_blocks, wt, alpha);
+            PO_WEIGHTS(__half, 1);
     }
+#undef PO_WEIGHTS
     return hipGetLastError();
 }
 
