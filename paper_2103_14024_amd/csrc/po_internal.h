@@ -232,20 +232,28 @@ inline void po_frame_piece_sizes(int64_t waves, bool exact, KSplit* S) {
 // Piece sizes of a split pass over a list of n rays.  The render and the
 // backward of the same rays cut them alike: the transmittance in front of
 // every piece is then the same float product in both, so the backward stops
-// on the sample where the render that produced its colour stopped.
+// on the sample where the render that produced its colour stopped.  So the
+// sizes depend on n and the depth alone, never on the options: a render with
+// aux outputs or a step cap cuts as its backward, which has neither, does.
+// They count octree cells, which the walks then step (exact); the counts of
+// aux outputs so do not depend on how empty space is crossed either.
+// From 2^18 rays the sizes of a frame (in samples, boxes crossed whole, as
+// frames without aux: 300,000 rays at depth 8 0.326 against 0.307 ms, at depth
+// 9 with K = 16 0.763 against 0.529; 10^6 rays 0.927 against 0.959, 1.58
+// against 1.71).
 // A batch below 2^18 rays fills the chip for less time than a frame: a first
 // walk of a few cells and small pieces (training step of 65,536 rays, depth 8:
-// 0.558 ms with the frame's sizes, 0.460 with these).  Its first walk counts
-// cells: counted in samples it would cross the empty space in front of the
-// first leaf at one wave's speed (52 against 18 us).  Chunks of 8 cells, handed
-// on past 16: 0.304 ms for the training step (6 and 12: 0.311), 0.455 and 0.483
-// with 131,072 rays, and the render of 200,001 0.265 and 0.287.  As many pieces
+// 0.558 ms with the frame's sizes, 0.460 with these).  Its first walk counted
+// in samples would cross the empty space in front of the first leaf at one
+// wave's speed (52 against 18 us).  Chunks of 8 cells, handed on past 16: 0.304
+// ms for the training step (6 and 12: 0.311), 0.455 and 0.483 with 131,072
+// rays, and the render of 200,001 0.265 and 0.287.  As many pieces
 // as the queue's 2^20 slots hold: past that the walks that find their region
 // full finish in their lanes (200,001 rays, depth 8, chunks of 6: 0.535 ms at
 // ub_frac 0.2, 0.333 at 0.1; 65,536 rays 0.358 at 0.2, 0.383 at 0.1).
-inline void po_rays_piece_sizes(int64_t n, int depth, bool exact, KSplit* S) {
+inline void po_rays_piece_sizes(int64_t n, int depth, KSplit* S) {
     if (n >= (1 << 18)) {
-        po_frame_piece_sizes(0, exact, S);
+        po_frame_piece_sizes(0, true, S);
     } else {
         S->exact = true;
         S->split_cap = 4;

@@ -3005,7 +3005,7 @@ hipError_t backward_split_t(const po_tree* t, int64_t n, const float* o, const f
     S.n_rays = n;
     // the pieces of the render of the same rays (before the grids: they
     // cover the queue regions as this pass lays them out)
-    po_rays_piece_sizes(n, t->kt.depth(), (op.flags & kOptExact) != 0u, &S);
+    po_rays_piece_sizes(n, t->kt.depth(), &S);
     hipLaunchKernelGGL(k_zero_i32, dim3(2), dim3(kSplitRegions), 0, s, S.count, 2 * kSplitRegions);
     dim3 g1((unsigned)grid_for(B.n_blocks)), g2((unsigned)(kSplitRegions * (S.region_slots / kBlock))),
         g3(2u * g2.x), blk(kBlock);
@@ -3052,7 +3052,7 @@ hipError_t backward_kept_t(const po_tree* t, int64_t n, const float* o, const fl
     S.ray_o = o;
     S.ray_d = d;
     S.n_rays = n;
-    po_rays_piece_sizes(n, t->kt.depth(), (op.flags & kOptExact) != 0u, &S);
+    po_rays_piece_sizes(n, t->kt.depth(), &S);
     dim3 g1((unsigned)grid_for(B.n_blocks)), g3(2u * (unsigned)(kSplitRegions * (S.region_slots / kBlock))),
         blk(kBlock);
     const size_t lds = stack_bytes(t->kt);
@@ -3249,11 +3249,7 @@ hipError_t po_launch_rays_split(const po_tree* t, int64_t n, const float* o, con
     S.ray_o = o;
     S.ray_d = d;
     S.n_rays = n;
-    // a batch of rays below a frame's size fills the chip less: a shorter
-    // first walk and smaller pieces (65536 random rays of the depth-8
-    // training tree: 203 us with 8-cell pieces, 325 us with the frame's 32,
-    // 300 us in one pass)
-    po_rays_piece_sizes(n, t->kt.depth(), (op.flags & kOptExact) != 0u, &S);
+    po_rays_piece_sizes(n, t->kt.depth(), &S);
     const int n_blocks = (int)((n + kBlock - 1) / kBlock);
     const int variant = po_fwd_variant(op, aux, t->kt);
     return t->desc.dtype == PO_F32 ? po_rays_split_f32(t, job, n_blocks, variant, S, s)
