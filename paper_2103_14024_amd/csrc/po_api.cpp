@@ -123,7 +123,7 @@ void po_split_layout(void* base, int region_slots, KSplit* S) {
     S->part2 = p + n * 48;
     S->view_part2 = reinterpret_cast<int4*>(p + n * 80);
     S->region_slots = region_slots;
-    po_frame_piece_sizes(0, false, S);
+    po_cell_piece_sizes(0, S);
     S->ray_o = nullptr;
     S->ray_d = nullptr;
     S->n_rays = 0;

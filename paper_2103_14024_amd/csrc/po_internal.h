@@ -203,6 +203,16 @@ struct KSplit {
 // chip busy through its first walk, so its rays walk further before the
 // hand-off and fewer of them wait in the chunk queues.
 constexpr int64_t kResidentWaves = 4096;
+// In octree cells.
+inline void po_cell_piece_sizes(int64_t waves, KSplit* S) {
+    const int64_t s = 20 + 18 * waves / kResidentWaves;
+    S->exact = true;
+    S->split_cap = (int)(s < 28 ? 28 : s > 192 ? 192 : s);
+    S->chunk_target = 24;
+    S->sub_target = 10;
+    S->chunk_cap = 24;
+    S->ub_frac = 0.3f;
+}
 // The sizes in samples, measured (us; float32 800x800, 1280x720 and 512x512 of
 // the depth-9 scene, float16 1920x1080, codebook 640x480 and SG-25 400x400 of
 // depth 8; in cells, over the octree's own cells: 517 / 811 / 356 / 1006 / 392 /
@@ -211,16 +221,18 @@ constexpr int64_t kResidentWaves = 4096;
 // walk of 6 + 6 samples a round loses 8 % at 1920x1080.  Smaller sub-chunks or
 // a cap below the target overflow the queue where a dense volume fills every
 // chunk past its cap.
+//
+// In octree cells instead for renders that report or cap them (exact), and for
+// frames of less than half a round of waves (2^17 pixels), where the first
+// walk's way to its first sample is the longest part (in samples / in cells,
+// 256x256 and 300x300, float32: depth 8, K = 9 151 / 130 and 151 / 142; depth 9,
+// K = 16 224 / 167 and 246 / 193; depth 10 241 / 183 and 274 / 222; from
+// 400x400 as often slower, 160 / 157 at depth 8, 223 / 235 with K = 25).
 inline void po_frame_piece_sizes(int64_t waves, bool exact, KSplit* S) {
-    S->exact = exact;
-    if (exact) {
-        const int64_t s = 20 + 18 * waves / kResidentWaves;
-        S->split_cap = (int)(s < 28 ? 28 : s > 192 ? 192 : s);
-        S->chunk_target = 24;
-        S->sub_target = 10;
-        S->chunk_cap = 24;
-        S->ub_frac = 0.3f;
+    if (exact || waves < kResidentWaves / 2) {
+        po_cell_piece_sizes(waves, S);
     } else {
+        S->exact = false;
         const int64_t s = 10 + 10 * waves / kResidentWaves;
         S->split_cap = (int)(s < 12 ? 12 : s > 96 ? 96 : s);
         S->chunk_target = 16;
@@ -237,10 +249,9 @@ inline void po_frame_piece_sizes(int64_t waves, bool exact, KSplit* S) {
 // aux outputs or a step cap cuts as its backward, which has neither, does.
 // They count octree cells, which the walks then step (exact); the counts of
 // aux outputs so do not depend on how empty space is crossed either.
-// From 2^18 rays the sizes of a frame (in samples, boxes crossed whole, as
-// frames without aux: 300,000 rays at depth 8 0.326 against 0.307 ms, at depth
-// 9 with K = 16 0.763 against 0.529; 10^6 rays 0.927 against 0.959, 1.58
-// against 1.71).
+// From 2^18 rays a frame's (its sizes in samples, over boxes, against these in
+// cells: 300,000 rays at depth 8 0.326 against 0.307 ms, at depth 9 with K = 16
+// 0.763 against 0.529; 10^6 rays 0.927 against 0.959 and 1.58 against 1.71).
 // A batch below 2^18 rays fills the chip for less time than a frame: a first
 // walk of a few cells and small pieces (training step of 65,536 rays, depth 8:
 // 0.558 ms with the frame's sizes, 0.460 with these).  Its first walk counted
@@ -253,7 +264,7 @@ inline void po_frame_piece_sizes(int64_t waves, bool exact, KSplit* S) {
 // ub_frac 0.2, 0.333 at 0.1; 65,536 rays 0.358 at 0.2, 0.383 at 0.1).
 inline void po_rays_piece_sizes(int64_t n, int depth, KSplit* S) {
     if (n >= (1 << 18)) {
-        po_frame_piece_sizes(0, true, S);
+        po_cell_piece_sizes(0, S);
     } else {
         S->exact = true;
         S->split_cap = 4;
