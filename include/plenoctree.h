@@ -260,13 +260,15 @@ po_status po_render_rays(const po_tree* t, int64_t n, const float* d_origins, co
  * [1, 16384]; fx, fy non-zero.
  * Images of at least 65536 pixels whose longest walks would outlast the rest
  * (up to a number of pixels that grows with the depth: 98,304 to depth 7,
- * 98,304 or 327,680 at depth 8, 720,896 at 9 and 2,097,152 at 10; larger images
- * are rendered in one pass), and all of them with PO_OUT_AUX or a
- * caller's max_steps, are rendered in pieces: every ray is walked
- * for a bounded number of data samples, the rays with cells left are cut into
- * parameter intervals walked in parallel, and the pieces are composited front to back (compositing is associative, Sec. 3
- * eqn:quad), the piece holding the early stop walked again with the known
- * transmittance.  The colour equals the one-pass render (po_render_batch)
+ * 98,304 or 327,680 at depth 8, 720,896 at 9 and 2,097,152 at 10; without a
+ * traversal index 98,304 to depth 7, 327,680 or 589,824 at 8 and 1,572,864 at
+ * 9; larger images are rendered in one pass), and all of them with PO_OUT_AUX
+ * or a caller's max_steps, are rendered in pieces: every ray is walked for a
+ * bounded number of data samples or cells, the rays with cells left are cut
+ * into parameter intervals walked in parallel, and the pieces are composited
+ * front to back (compositing is associative, Sec. 3 eqn:quad), the piece
+ * holding the early stop walked again with the known transmittance.  The
+ * colour equals the one-pass render (PO_ONE_PASS)
  * up to float rounding; where T lands within rounding of stop_T the two can
  * stop one cell apart, which moves at most stop_T of weight.  For this the
  * library keeps a work queue of about 200 MB per (device, stream), made on

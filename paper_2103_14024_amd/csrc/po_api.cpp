@@ -799,6 +799,11 @@ po_status po_render_rays(const po_tree* t, int64_t n, const float* d_origins, co
 //     heavy    1.13     1.15     1.08     1.08     0.90
 //   depth 9    1.52     1.30              1.18     1.07      0.90      0.84  (heavy 1.6 .. 1.1, 0.94)
 //   depth 10   1.6               1.5               1.3       1.1       1.0
+// Without a grid (no index), float32 K = 9:
+//   depth 7    0.95     0.86              0.72     0.66      0.73      0.93
+//   depth 8    1.53     1.40              1.13     0.96      0.86      0.88
+//     heavy    1.47     1.32              0.96     0.84      0.74      0.75
+//   depth 9    2.5      2.2               1.64     1.37      1.05      0.94
 // (Below depth 8 one pass wins at every size; images up to 98,304 pixels keep
 // to pieces there because programs that reserve or release a stream's queue
 // count on the smallest of them to use it.)
@@ -808,6 +813,11 @@ po_status po_render_rays(const po_tree* t, int64_t n, const float* d_origins, co
 int64_t split_max_pixels(const po_tree* t, const KOpts& k, int variant) {
     if (k.flags & kOptExact) return INT64_MAX;
     const bool heavy = variant == PO_FWD_VIEW || variant == PO_FWD_CB || elem_size(t->desc.dtype) * 3 * t->K > 192;
+    if (t->kt.grid_level() == 0) switch (t->desc.depth) {
+        case 8: return heavy ? 5 << 16 : 9 << 16;
+        case 9: return 3 << 19;
+        default: return t->desc.depth < 8 ? 3 << 15 : INT64_MAX;
+        }
     switch (t->desc.depth) {
     case 8: return heavy ? 5 << 16 : 3 << 15;
     case 9: return 11 << 16;
@@ -853,10 +863,10 @@ static po_status render_camera_impl(const po_tree* t, const po_camera* cam, cons
     const bool split = in_pieces(t, j.op, variant, (int64_t)cam->width * cam->height);
     if (split && noalloc) {
         if ((e = po_noalloc_queue(&S)) != hipSuccess) return device_fail(e, "locating the fixed work queue");
-        po_frame_piece_sizes(4 * (int64_t)tiles_of(cam), (j.op.flags & kOptExact) != 0u, &S);
+        po_frame_piece_sizes(t->kt, 4 * (int64_t)tiles_of(cam), (j.op.flags & kOptExact) != 0u, &S);
         e = po_launch_camera_split(t, j, 4 * tiles_of(cam), variant, S, (hipStream_t)stream);
     } else if (split && split_queue(stream, &S)) {
-        po_frame_piece_sizes(4 * (int64_t)tiles_of(cam), (j.op.flags & kOptExact) != 0u, &S);
+        po_frame_piece_sizes(t->kt, 4 * (int64_t)tiles_of(cam), (j.op.flags & kOptExact) != 0u, &S);
         e = po_launch_camera_split(t, j, 4 * tiles_of(cam), variant, S, (hipStream_t)stream);
     } else {
         e = po_launch_camera_jobs(t, 1, &j, 4 * tiles_of(cam), variant, (hipStream_t)stream);
@@ -1092,7 +1102,7 @@ po_status po_render_batch(int32_t n_jobs, const po_job* jobs, void* stream) {
         kj.tile_begin = J.tile_begin;
         kj.block_begin = 0;
         kj.tiles_x = (J.cam.width + PO_TILE - 1) / PO_TILE;
-        po_frame_piece_sizes(4 * (int64_t)nt, (k.flags & kOptExact) != 0u, &S);
+        po_frame_piece_sizes(J.tree->kt, 4 * (int64_t)nt, (k.flags & kOptExact) != 0u, &S);
         hipError_t e = po_launch_camera_split(J.tree, kj, 4 * nt, variant(i) % 4, S, (hipStream_t)stream);
         if (e != hipSuccess) return device_fail(e, "render_batch launch");
     }

@@ -222,14 +222,16 @@ inline void po_cell_piece_sizes(int64_t waves, KSplit* S) {
 // a cap below the target overflow the queue where a dense volume fills every
 // chunk past its cap.
 //
-// In octree cells instead for renders that report or cap them (exact), and for
+// In octree cells instead for renders that report or cap them (exact), for
 // frames of less than half a round of waves (2^17 pixels), where the first
 // walk's way to its first sample is the longest part (in samples / in cells,
 // 256x256 and 300x300, float32: depth 8, K = 9 151 / 130 and 151 / 142; depth 9,
 // K = 16 224 / 167 and 246 / 193; depth 10 241 / 183 and 274 / 222; from
-// 400x400 as often slower, 160 / 157 at depth 8, 223 / 235 with K = 25).
-inline void po_frame_piece_sizes(int64_t waves, bool exact, KSplit* S) {
-    if (exact || waves < kResidentWaves / 2) {
+// 400x400 as often slower, 160 / 157 at depth 8, 223 / 235 with K = 25), and for
+// trees without a grid, whose walks step them anyway (depth 8 256x256 307 /
+// 218, depth 9 512x512 707 / 453).
+inline void po_frame_piece_sizes(const KTree& t, int64_t waves, bool exact, KSplit* S) {
+    if (exact || waves < kResidentWaves / 2 || t.grid_level() == 0) {
         po_cell_piece_sizes(waves, S);
     } else {
         S->exact = false;
