@@ -214,11 +214,14 @@ po_status po_tree_bind_codebook(const po_tree_desc* desc, int64_t n_nodes, const
  * their steps (PO_OUT_AUX, max_steps) still take cell by cell.
  * Reads the child array back to the host on `stream` (waiting for the
  * stream), checks it as po_tree_validate does, and allocates the index on
- * the current device (8^G * 4 + n_bricks * 2048 bytes, and n_top * 32 where
- * G < M, a few percent of the leaf records); the handle owns it until
- * po_tree_destroy.  Trees of depth < 4 need none (PO_OK, nothing built); a
- * second call is a no-op.  Must not run while work that uses the handle is
- * queued or running.  Errors: PO_ERR_INVALID (NULL), PO_ERR_TREE (malformed
+ * the current device: n_bricks * 2048 bytes, a few percent of the leaf
+ * records, the grid's 8^G * 4 whatever the number of leaves (64 MiB from depth
+ * 11 on), and n_top * 32 where G < M; building takes n_top * 32 + 8^G * 4 more
+ * until it returns.  Where that cannot be had a smaller G is taken, down to no
+ * grid at all.  The handle owns the index until po_tree_destroy.  Trees of
+ * depth < 4 need none (PO_OK, nothing built); a second call is a no-op.  Must
+ * not run while work that uses the handle is queued or running.  Errors:
+ * PO_ERR_INVALID (NULL), PO_ERR_TREE (malformed
  * child array: the handle is unchanged and renders walk the caller's array,
  * counting malformed entries as device errors), PO_ERR_UNSUPPORTED (2^29 - 2
  * leaves or more, or nodes and bricks of 4 GiB or more), PO_ERR_OOM,

@@ -691,35 +691,39 @@ po_status po_tree_build_index(po_tree* t, void* stream) {
     if (e != hipSuccess) return device_fail(e, "traversal index: reading the child array");
     if (po_status st = index_of(&t->desc, t->codebook, n, h.data(), t->n_leaves, index, n_top, n_bricks)) return st;
     // The grid reaches the bricks for D <= 11; deeper trees keep the nodes
-    // below it.  An index that the grid would take past 4 GiB does without.
+    // below it.  Where it does not fit, in the device's memory or below 4 GiB,
+    // a smaller one is taken (an eighth each, and the nodes kept), in the end
+    // none: only an index that does not fit by itself is refused.
     const int M = D - 3;
-    int G = std::min(M, kIdxMaxGrid);
     const size_t node_bytes = (size_t)n_top * 32, brick_bytes = (size_t)n_bricks * 2048;
-    size_t grid_bytes = (size_t)4 << (3 * G), kept_nodes = G < M ? node_bytes : 0;
+    int G = std::min(M, kIdxMaxGrid);
+    size_t grid_bytes, kept_nodes, bytes;
     std::vector<int32_t> nodes;
-    try {
-        nodes = grid_nodes(index, n_top, G, coarse);
-    } catch (const std::bad_alloc&) {
-        return fail(PO_ERR_OOM, "traversal index: host allocation");
-    }
-    if (grid_bytes + kept_nodes + brick_bytes + coarse.size() * 4 >= ((size_t)1 << 32) - 256) {
-        G = 0;
-        grid_bytes = 0;
-        kept_nodes = node_bytes;
-        coarse.clear();
-    }
-    const size_t bytes = grid_bytes + kept_nodes + brick_bytes + coarse.size() * 4;
     char* d = nullptr;
     char* tmp = nullptr;  // the grid's nodes, then scratch for its boxes
-    if ((e = hipMalloc(&d, bytes)) != hipSuccess || (G > 0 && (e = hipMalloc(&tmp, node_bytes + grid_bytes)) != hipSuccess)) {
-        (void)hipGetLastError();
-        if (d) (void)hipFree(d);
-        return fail(PO_ERR_OOM, "traversal index: %zu bytes of device memory", bytes + (G > 0 ? node_bytes + grid_bytes : 0));
+    for (;; --G) {
+        grid_bytes = G > 0 ? (size_t)4 << (3 * G) : 0;
+        kept_nodes = G < M ? node_bytes : 0;
+        coarse.clear();
+        try {
+            if (G > 0) nodes = grid_nodes(index, n_top, G, coarse);
+        } catch (const std::bad_alloc&) {
+            return fail(PO_ERR_OOM, "traversal index: host allocation");
+        }
+        bytes = grid_bytes + kept_nodes + brick_bytes + coarse.size() * 4;
+        if (G == 0 || bytes < ((size_t)1 << 32) - 256) {
+            e = hipMalloc(&d, bytes);
+            if (e == hipSuccess && G > 0) e = hipMalloc(&tmp, node_bytes + grid_bytes);
+            if (e == hipSuccess) break;
+            (void)hipGetLastError();
+            if (d) (void)hipFree(d);
+            d = nullptr;
+        }
+        if (G == 0) return fail(PO_ERR_OOM, "traversal index: %zu bytes of device memory", bytes);
     }
     auto put = [&](void* to, const void* from, size_t len) {
         if (e == hipSuccess && len > 0) e = hipMemcpyAsync(to, from, len, hipMemcpyHostToDevice, s);
     };
-    e = hipSuccess;
     if (G > 0) put(tmp, nodes.data(), node_bytes);
     put(d + grid_bytes, index.data(), kept_nodes);
     put(d + grid_bytes + kept_nodes, index.data() + n_top * 8, brick_bytes);
