@@ -271,9 +271,9 @@ po_status po_render_rays(const po_tree* t, int64_t n, const float* d_origins, co
  * into parameter intervals walked in parallel, and the pieces are composited
  * front to back (compositing is associative, Sec. 3 eqn:quad), the piece
  * holding the early stop walked again with the known transmittance.  The
- * colour equals the one-pass render (PO_ONE_PASS)
- * up to float rounding; where T lands within rounding of stop_T the two can
- * stop one cell apart, which moves at most stop_T of weight.  For this the
+ * colour equals the one-pass render (PO_ONE_PASS) up to float rounding; where T
+ * lands within rounding of stop_T the two can stop one cell apart, which moves
+ * at most stop_T of weight.  For this the
  * library keeps a work queue of about 200 MB per (device, stream), made on
  * the first such call and held until the process ends (if it cannot be
  * allocated, the image is rendered in one pass).  Calls on one stream are
@@ -413,14 +413,15 @@ po_status po_draw_batch(int64_t n, uint64_t seed, uint64_t first, int64_t n_src,
  * image of one tree (tiles numbered row-major over ceil(W/16) x ceil(H/16)).
  * po_render_batch renders up to PO_BATCH_MAX_JOBS jobs, of any trees and
  * image sizes, all on `stream`.  Jobs of fewer than 256 tiles (65536 pixels),
- * and all others that po_render_camera would not render in pieces, are rendered with as few kernel launches as their (dtype, SH degree)
- * groups allow, each ray walked to its end in one pass by one lane; their
- * pixels equal po_render_camera's bit for bit for images under 65536
- * pixels.  A job of more tiles (without PO_ONE_PASS in its options) is rendered in pieces on its own, as
- * po_render_camera renders a large image (using the same work queue of
- * `stream`), and its pixels equal po_render_camera's up to float rounding
- * (bit for bit unless a region of the work queue filled up in one of the
- * two).  Errors: as po_render_camera, plus PO_ERR_INVALID for n_jobs outside
+ * and all others that po_render_camera would not render in pieces, are rendered
+ * with as few kernel launches as their (dtype, SH degree) groups allow, each ray
+ * walked to its end in one pass by one lane; their pixels equal
+ * po_render_camera's bit for bit where that renders in one pass too.  A job of
+ * more tiles (without PO_ONE_PASS in its options) is rendered in pieces on its
+ * own, as po_render_camera renders such an image (using the same work queue of
+ * `stream`), and its pixels equal po_render_camera's up to float rounding (bit
+ * for bit unless a region of the work queue filled up in one of the two).
+ * Errors: as po_render_camera, plus PO_ERR_INVALID for n_jobs outside
  * [0, PO_BATCH_MAX_JOBS] or a tile range outside the image. */
 typedef struct {
     const po_tree* tree;

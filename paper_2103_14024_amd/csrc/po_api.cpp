@@ -796,18 +796,19 @@ po_status po_render_rays(const po_tree* t, int64_t n, const float* d_origins, co
 // the chip busy for as long as the longest walk lasts, and the pieces only
 // cost.  That walk grows with the depth, and with what a sample costs (heavy:
 // records over 192 bytes, codebooks, viewer outputs).  Time of one pass over
-// time in pieces, blob bands, by pixels:
+// time in pieces (below 400x400 cut in octree cells), blob bands, by pixels:
 //             256x256  400x400  512x512  640x480  800x800  1280x720  1920x1080
-//   depth 7    0.76     0.69              0.59     0.60      0.69      0.87  (heavy 0.9 .. 0.64)
-//   depth 8    1.02     0.93              0.83     0.75      0.72      0.81
-//     heavy    1.13     1.15     1.08     1.08     0.90
-//   depth 9    1.52     1.30              1.18     1.07      0.90      0.84  (heavy 1.6 .. 1.1, 0.94)
-//   depth 10   1.6               1.5               1.3       1.1       1.0
-// Without a grid (no index), float32 K = 9:
-//   depth 7    0.95     0.86              0.72     0.66      0.73      0.93
-//   depth 8    1.53     1.40              1.13     0.96      0.86      0.88
-//     heavy    1.47     1.32              0.96     0.84      0.74      0.75
-//   depth 9    2.5      2.2               1.64     1.37      1.05      0.94
+//   depth 7    0.74     0.70     0.64     0.60     0.62      0.69      0.87
+//   depth 8    1.21     0.97     0.92     0.88     0.78      0.77      0.82
+//     heavy    1.20     1.16     1.11     1.03     0.93      0.87      0.88
+//   depth 9    1.65     1.37     1.20     1.14     1.04      0.92      0.89
+//     heavy    1.78     1.46     1.27     1.17     1.05      0.94      0.91
+//   depth 10   1.94     1.56     1.47     1.29     1.16      0.92      0.95
+// and without a grid (no index; cut in octree cells):
+//   depth 7    0.91     0.84     0.78     0.74     0.72      0.72      0.88
+//   depth 8    1.46     1.32     1.18     1.05     0.94      0.80      0.84
+//     heavy    1.41     1.30     1.15     0.95     0.84      0.75      0.75
+//   depth 9    2.39     2.10     1.81     1.55     1.30      0.97      0.87
 // (Below depth 8 one pass wins at every size; images up to 98,304 pixels keep
 // to pieces there because programs that reserve or release a stream's queue
 // count on the smallest of them to use it.)

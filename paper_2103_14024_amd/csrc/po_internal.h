@@ -61,7 +61,6 @@ struct KTree {
     PO_HD int depth() const { return (int)(levels & 255u); }
     PO_HD int brick_level() const { return (int)(levels >> 8 & 255u); }
     PO_HD int grid_level() const { return (int)(levels >> 16 & 255u); }
-    PO_HD bool has_coarse() const { return (levels >> 24) != 0u; }
     void set_levels(int D, int M, int G, bool coarse) {
         levels = (uint32_t)D | (uint32_t)M << 8 | (uint32_t)G << 16 | (coarse ? 1u << 24 : 0u);
     }
@@ -225,11 +224,11 @@ inline void po_cell_piece_sizes(int64_t waves, KSplit* S) {
 // In octree cells instead for renders that report or cap them (exact), for
 // frames of less than half a round of waves (2^17 pixels), where the first
 // walk's way to its first sample is the longest part (in samples / in cells,
-// 256x256 and 300x300, float32: depth 8, K = 9 151 / 130 and 151 / 142; depth 9,
-// K = 16 224 / 167 and 246 / 193; depth 10 241 / 183 and 274 / 222; from
-// 400x400 as often slower, 160 / 157 at depth 8, 223 / 235 with K = 25), and for
-// trees without a grid, whose walks step them anyway (depth 8 256x256 307 /
-// 218, depth 9 512x512 707 / 453).
+// us, 256x256 and 320x280, float32: depth 8, K = 9 142 / 122 and 145 / 130; depth
+// 9, K = 16 183 / 150 and 207 / 179; depth 10 206 / 167 and 251 / 211; from
+// 400x400 as often slower: 154 / 144 at depth 8, 205 / 217 there with K = 25, 417
+// / 580 at depth 10 and 640x480), and for trees without a grid, whose walks step
+// them anyway (depth 8 256x256 251 / 185, depth 9 512x512 472 / 340).
 inline void po_frame_piece_sizes(const KTree& t, int64_t waves, bool exact, KSplit* S) {
     if (exact || waves < kResidentWaves / 2 || t.grid_level() == 0) {
         po_cell_piece_sizes(waves, S);

@@ -3,10 +3,11 @@
 // One ray per lane.  A ray is cut into the exact segments between voxel
 // boundaries of the sparse octree (Sec. 4.2, "Rendering"): the current
 // position is kept as integer coordinates of a finest-level cell; each step
-// descends from the root to the leaf containing it, computes the parameter at
-// which the ray leaves that leaf's cube (the nearest exit plane), composites
-// the segment if the leaf holds data, and moves the coordinates across the
-// exit face.  Large empty cubes are therefore crossed in one step.  Each data
+// reads what holds the cell (a leaf, or a box of empty space) from a traversal
+// index, or by a descent of the child array from the deepest ancestor shared
+// with the cell before, computes the parameter at which the ray leaves it (the
+// nearest exit plane), composites the segment if the leaf holds data, and moves
+// the coordinates across the exit face.  Each data
 // segment is shaded with the sigmoid of the real-SH expansion in the ray
 // direction (Sec. 4.1; SH of App. B.1) and composited front to back with
 // alpha = 1 - exp(-sigma delta) (Sec. 3, eqn:quad); marching stops once the
@@ -395,7 +396,8 @@ __host__ __device__ inline Way way_of(int D, int M, int G) {
 // issuing 25 % and waiting 75 % of their cycles, with 1.8 waves of 4 resident
 // on average.  So the step is kept short: mirrored axes, entries that carry
 // their own box, and a branch-free path for trees whose grid reaches the
-// bricks.
+// bricks, in kernels of its own (now about 210 instructions a step without the
+// shading, 153 vector and 55 scalar).
 template <bool CLIP, bool CHUNK, Way WAY>
 struct Walker {
     int e;
@@ -933,9 +935,10 @@ __device__ __forceinline__ int march_quads(const Index& ix, Ray& r, bool walk, i
     return steps;
 }
 
-// Which of the two a sampler takes (kQueued): the queue costs about 45
-// instructions a step, and saves the waits on gathers and the lanes without a
-// sample.  It pays where a sample is expensive: records over 192 bytes (SG-25
+// Which of the three a sampler takes: quads where its records are whole lines by
+// channel (kQuads); else the queue (kQueued) or its own lane.  The queue costs
+// about 45 instructions a step, and saves the waits on gathers and the lanes
+// without a sample.  It pays where a sample is expensive: records over 192 bytes (SG-25
 // 400x400, float32: 0.219 against 0.259 ms), codebooks (640x480: 0.306 against
 // 0.377) and gradients (8191 rays forward and backward: 0.291 against 0.486),
 // not for smaller records (800x800 float32 K = 16: 0.497 against 0.451) or the
@@ -1760,8 +1763,9 @@ __device__ __forceinline__ void first_walk(const KJob& J, const KSplit& S, int i
 }
 
 // The plain (SH, SG) walks of records up to 192 bytes are held to 128 VGPRs
-// (4 waves per SIMD; float32 K = 16 then keeps up to 96 bytes of scratch, used
-// before and after the walk's loop).  Larger records and the viewer and
+// (4 waves per SIMD; the kernels of direct trees then need no scratch, the
+// others up to 204 bytes at float32 K = 16, used before and after the walk's
+// loops).  Larger records and the viewer and
 // codebook variants would spill inside it (K=25 float32: 180 bytes of scratch,
 // half the frame rate), so they keep their natural count.
 template <typename T, int K, int V>

@@ -315,12 +315,13 @@ class Job:
     aux_out: object = None  # (H, W, 4) float32 device tensor or None
     sh_off: int = 0
     clip: object = None
-    one_pass: bool = False  # never in pieces (jobs of >= 256 tiles otherwise are)
+    one_pass: bool = False  # never in pieces (jobs that render_camera would render so otherwise are)
 
 
 def render_batch(jobs, stream=None) -> None:
     """Renders up to 16 camera jobs (any trees, any sizes, tile sub-ranges);
-    jobs of 256 tiles or more are rendered in pieces unless one_pass is set."""
+    jobs that render_camera would render in pieces are so here unless one_pass
+    is set."""
     arr = (L.po_job * max(1, len(jobs)))()
     for i, j in enumerate(jobs):
         _out(j.out, (j.cam.height, j.cam.width, 3), "Job.out")

@@ -2,9 +2,9 @@
 
 Requests (scene, camera) arrive over time.  The loop admits arrived requests
 while their output images fit an HBM budget and a slot cap.  A request of at
-least `split_tiles` 16x16 tiles is rendered whole by one job, which the
-library renders in pieces (long walks cut and walked in parallel); smaller
-requests are cut into chunks of tiles, and chunks of several requests -- of
+least `split_tiles` 16x16 tiles is rendered whole by one job, as render_camera
+renders it (in pieces, long walks cut and walked in parallel, or in one pass
+where the image is large for its tree's depth); smaller requests are cut into chunks of tiles, and chunks of several requests -- of
 any scene and resolution -- are packed into batched launches
 (po_render_batch, up to 16 jobs each), each ray of a chunk walked by one
 lane (one pass).  Launches go round-robin to a few HIP
@@ -100,7 +100,7 @@ class Stats:
     launches: int = 0
     jobs: int = 0
     max_jobs: int = 0                   # most jobs in one launch
-    whole: int = 0                      # requests rendered whole, in pieces
+    whole: int = 0                      # requests rendered whole, by one job
     max_active: int = 0
     max_bytes: int = 0
 
@@ -122,7 +122,7 @@ class Server:
     admitted-request slots; chunk_tiles: least tiles of one request per
     launch; launch_tiles: tiles per launch; streams: HIP streams used round-robin;
     max_inflight: launches queued on the GPU at once; split_tiles: requests of
-    at least this many tiles are rendered whole, in pieces (None: never)."""
+    at least this many tiles are rendered whole, by one job (None: never)."""
 
     def __init__(self, trees, budget_bytes=512 << 20, max_active=64, chunk_tiles=256, launch_tiles=2048,
                  streams=3, max_inflight=4, stop_T=1e-4, bg=(1.0, 1.0, 1.0), device="cuda", split_tiles=1024):
@@ -193,7 +193,7 @@ class Server:
             # shared among the requests with work left, but no request gets less
             # than chunk_tiles (so a lone request still fills the GPU)
             if len(inflight) < self.max_inflight:
-                # the oldest large request not started yet: whole, in pieces
+                # the oldest large request not started yet: whole, by one job
                 big = next((r for r in active if r.next_tile == 0 and r.tiles >= self.split_tiles), None)
                 if big is not None:
                     s = self.streams[k_stream % len(self.streams)]
