@@ -369,19 +369,18 @@ struct Index {
     }
 };
 
-// The three walks.  Kernels are compiled for direct trees and for the others
-// (which then choose by a branch of the wave in front of the loop), and the
-// batched ones also for mixed launches.  One loop that tested the way in every
-// step took 2 to 14 % longer on direct trees (64x64 23.3 against 20.4 us,
-// 800x800 410 against 391), and 20 to 30 % on trees without an index, whose
-// steps ran through the branches of the nodes'.  The three loops side by side
-// in one kernel cost it registers: float32 K = 16 at 800x800 lost 7 % to
-// spills around the loops.
+// The three walks.  Kernels are compiled for each, and the batched ones also for
+// launches that mix them (those choose by a branch of the wave in front of the
+// loop).  One loop that tested the way in every step took 2 to 14 % longer on
+// direct trees (64x64 23.3 against 20.4 us, 800x800 410 against 391), and 20 to
+// 30 % on trees without an index, whose steps ran through the branches of the
+// nodes'.  Loops side by side in one kernel cost it registers: all three, and
+// float32 K = 16 at 800x800 lost 7 % to spills around them; the last two, and
+// 300,000 rays without an index took 397 us for 358 (K = 9), 468 for 431.
 enum Way {
     kDirect,  // the grid reaches the bricks (indexed trees of depth 4 to 11)
     kPlain,   // the caller's child array
     kNodes,   // an index with nodes between the grid and the bricks
-    kOther,   // kernels: kPlain or kNodes
     kAny      // kernels: any of the three
 };
 __host__ __device__ inline Way way_of(int D, int M, int G) {
@@ -960,14 +959,14 @@ template <bool SPLIT, Way WAY, class Sampler>
 __device__ __forceinline__ int march(const KTree& tr, Ray& r, bool walk, int max_steps, int cap, bool exact,
                                      int* __restrict__ stk, Sampler& smp) {
     const Index ix(tr);
-    if constexpr (WAY == kDirect) {
-        return march_way<Sampler, SPLIT, kDirect>(ix, r, walk, max_steps, cap, exact, stk, smp);
+    if constexpr (WAY != kAny) {
+        return march_way<Sampler, SPLIT, WAY>(ix, r, walk, max_steps, cap, exact, stk, smp);
     } else {
-        const Way way = way_of(ix.D, ix.M, ix.G);
-        if constexpr (WAY == kAny)
-            if (way == kDirect) return march_way<Sampler, SPLIT, kDirect>(ix, r, walk, max_steps, cap, exact, stk, smp);
-        if (way == kPlain) return march_way<Sampler, SPLIT, kPlain>(ix, r, walk, max_steps, cap, exact, stk, smp);
-        return march_way<Sampler, SPLIT, kNodes>(ix, r, walk, max_steps, cap, exact, stk, smp);
+        switch (way_of(ix.D, ix.M, ix.G)) {
+        case kDirect: return march_way<Sampler, SPLIT, kDirect>(ix, r, walk, max_steps, cap, exact, stk, smp);
+        case kPlain: return march_way<Sampler, SPLIT, kPlain>(ix, r, walk, max_steps, cap, exact, stk, smp);
+        default: return march_way<Sampler, SPLIT, kNodes>(ix, r, walk, max_steps, cap, exact, stk, smp);
+        }
     }
 }
 
@@ -1327,14 +1326,20 @@ struct ChunkOf : Base {
     }
 };
 
-// Samplers of the split render: the first walk's, and a piece's.
-template <typename T, int K, int VEC, int NL, int V>
-using FirstSampler = std::conditional_t<
+// Samplers: a whole ray's, and of the split render the first walk's and a
+// piece's.  Pieces of plain walks shade records over 192 bytes in their own
+// lane: the queue costs by the step, of which they take half as many again
+// (300,000 rays, float32 K = 25, depth 8: 693 us through it, 555 without), while
+// whole rays, whose lanes drift apart, still gain by it (1920x1080: 995, 1210).
+template <typename T, int K, int VEC, int NL, int V, bool QUEUE = (sizeof(T) * 3 * K > 192)>
+using RaySampler = std::conditional_t<
     V == PO_FWD_CB, FwdQueued<CbRecords<K, VEC, NL>, false>,
-    std::conditional_t<(sizeof(T) * 3 * K > 192), FwdQueued<Records<T, K, VEC, NL>, V == PO_FWD_VIEW>,
+    std::conditional_t<QUEUE, FwdQueued<Records<T, K, VEC, NL>, V == PO_FWD_VIEW>,
                        FwdInline<T, K, VEC, NL, V == PO_FWD_VIEW>>>;
-template <typename T, int K, int VEC, int NL, int V>
-using ChunkSampler = ChunkOf<FirstSampler<T, K, VEC, NL, V>>;
+template <typename T, int K, int VEC, int NL, int V, Way WAY>
+using FirstSampler = RaySampler<T, K, VEC, NL, V, (sizeof(T) * 3 * K > 192 && WAY != kPlain)>;
+template <typename T, int K, int VEC, int NL, int V, Way WAY>
+using ChunkSampler = ChunkOf<FirstSampler<T, K, VEC, NL, V, WAY>>;
 
 // Binds a forward sampler to a tree (every lane), and a ray's basis.
 template <int K, int V, class Smp>
@@ -1356,7 +1361,7 @@ __device__ __forceinline__ void render_one(const KTree& tr, const KOpts& op, boo
     double s_lo = 0.0, s_hi = 1e300;
     if constexpr (V == PO_FWD_VIEW) clip_range(op, o, d, s_lo, s_hi);
     const bool walk = valid && ray_setup(tr, o, d, r, s_lo, s_hi);
-    FirstSampler<T, K, VEC, NL, V> smp;
+    RaySampler<T, K, VEC, NL, V> smp;
     fwd_init<K, V>(smp, tr, op, walk, r);
     steps = march<false, WAY>(tr, r, walk, op.max_steps, kNoCap, exact_cells(op), stk, smp);
     Tr = smp.Tl;
@@ -1700,7 +1705,7 @@ __device__ __forceinline__ void first_walk(const KJob& J, const KSplit& S, int i
     const KOpts& op = J.op;
     extern __shared__ int po_stack[];
     int* stk = po_stack + threadIdx.x;
-    using Smp = FirstSampler<T, K, VEC, NL, V>;
+    using Smp = FirstSampler<T, K, VEC, NL, V, WAY>;
     Smp smp;
     Ray r;
     int want = 0, steps = 0, h = -1;
@@ -1836,7 +1841,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
     const int4 in = q < 0 ? make_int4(-1, 0, -1, 0) : S.info[q];
     const int h = in.x;
     const KJob& J = B.job[0];
-    using Smp = ChunkSampler<T, K, VEC, NL, V>;
+    using Smp = ChunkSampler<T, K, VEC, NL, V, WAY>;
     Smp smp;
     Ray r;
     int want = 0, steps = 0, pix = 0, sub = -1;
@@ -1903,7 +1908,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPieceWa
     const int h = in.x;
     if (__ballot(h >= 0) == 0ull) return;
     const KJob& J = B.job[0];
-    using Smp = ChunkSampler<T, K, VEC, NL, V>;
+    using Smp = ChunkSampler<T, K, VEC, NL, V, WAY>;
     Smp smp;
     Ray r;
     bool walk = false;
@@ -1954,7 +1959,7 @@ __device__ __forceinline__ void join_ray(const KJob& J, const KSplit& S, int q, 
     PieceOut* part = reinterpret_cast<PieceOut*>(S.part);
     PieceOut* part2 = reinterpret_cast<PieceOut*>(S.part2);
     const SubHead* head2 = reinterpret_cast<const SubHead*>(S.head2);
-    using Smp = ChunkSampler<T, K, VEC, NL, V>;
+    using Smp = ChunkSampler<T, K, VEC, NL, V, WAY>;
     // next chunk j in slot qj; sub-chunk k of n_sub of the chunk before it, in slot qk
     int j = 0, qj = q, k = 0, n_sub = 0, sub = -1, qk = -1;
     bool more = ray, done = false;
@@ -2812,16 +2817,18 @@ inline int64_t grid_for(int64_t n_blocks) { return 8 * ((n_blocks + 7) / 8); }
 // Grid of xcd_interleave over n_blocks logical workgroups in runs of chunk.
 inline int64_t rows_grid(int64_t n_blocks, int64_t chunk) { return 8 * chunk * (((n_blocks + chunk - 1) / chunk + 7) / 8); }
 
-inline bool is_direct(const KTree& t) { return way_of(t.depth(), t.brick_level(), t.grid_level()) == kDirect; }inline bool all_direct(int n_jobs, const KJob* jobs) {
+inline Way way_of(const KTree& t) { return way_of(t.depth(), t.brick_level(), t.grid_level()); }
+// The kernels of a batch: direct ones, else those for any tree.
+inline Way way_of(int n_jobs, const KJob* jobs) {
     for (int j = 0; j < n_jobs; ++j)
-        if (!is_direct(jobs[j].tr)) return false;
-    return true;
+        if (way_of(jobs[j].tr) != kDirect) return kAny;
+    return kDirect;
 }
 
 // Dynamic LDS of the node stack: one int per lane and tree level.  Trees whose
 // grid reaches the brick level keep no node path.
 inline size_t stack_bytes(const KTree& t) {
-    return is_direct(t) ? 0 : sizeof(int) * kBlock * (size_t)t.depth();
+    return way_of(t) == kDirect ? 0 : sizeof(int) * kBlock * (size_t)t.depth();
 }
 
 // Record-load plan: "fast" loads the padded record with the widest vectors,
@@ -3092,7 +3099,7 @@ hipError_t backward_t(const po_tree* t, int64_t n, const float* o, const float* 
 }  // namespace
 
 // EXPR with the coefficient count KK of a tree and, PO_DISPATCH, the walk W of
-// its kernels (OTHER: for trees that are not direct).
+// its kernels.
 #define PO_DISPATCH_K(K_, EXPR)                      \
     switch (K_) {                                    \
         case 1: { constexpr int KK = 1; return EXPR; }   \
@@ -3102,15 +3109,17 @@ hipError_t backward_t(const po_tree* t, int64_t n, const float* o, const float* 
         case 25: { constexpr int KK = 25; return EXPR; } \
         default: return hipErrorInvalidValue;        \
     }
-#define PO_DISPATCH(K_, DIRECT_, OTHER_, EXPR)       \
-    do {                                             \
-        if (DIRECT_) {                               \
-            constexpr Way W = kDirect;               \
-            PO_DISPATCH_K(K_, EXPR)                  \
-        }                                            \
-        constexpr Way W = OTHER_;                    \
-        PO_DISPATCH_K(K_, EXPR)                      \
-    } while (0)
+#define PO_DISPATCH(K_, WAY_, EXPR)                                              \
+    switch (WAY_) {                                                              \
+        case kDirect: { constexpr Way W = kDirect; PO_DISPATCH_K(K_, EXPR) }     \
+        case kPlain: { constexpr Way W = kPlain; PO_DISPATCH_K(K_, EXPR) }       \
+        default: { constexpr Way W = kNodes; PO_DISPATCH_K(K_, EXPR) }           \
+    }
+#define PO_DISPATCH_BATCH(K_, WAY_, EXPR)                                        \
+    switch (WAY_) {                                                              \
+        case kDirect: { constexpr Way W = kDirect; PO_DISPATCH_K(K_, EXPR) }     \
+        default: { constexpr Way W = kAny; PO_DISPATCH_K(K_, EXPR) }             \
+    }
 
 // Launchers of the parts, by leaf type (defined in the part named).
 hipError_t po_camera_jobs_f32(const po_tree* first, int n_jobs, KJob* jobs, int n_blocks, int variant,
@@ -3151,11 +3160,12 @@ PO_PART_ERRORS_DECL(7)
 PO_PART_ERRORS_DEF(1)
 hipError_t po_camera_jobs_f32(const po_tree* first, int n_jobs, KJob* jobs, int n_blocks, int variant,
                               hipStream_t s) {
-    if (n_jobs == 1)
-        PO_DISPATCH(first->K, is_direct(first->kt), kOther,
+    if (n_jobs == 1) {
+        PO_DISPATCH(first->K, way_of(first->kt),
                     (camera_t<float, KK, 1, W>(first, n_jobs, jobs, n_blocks, variant, s)));
-    PO_DISPATCH(first->K, all_direct(n_jobs, jobs), kAny,
-                (camera_t<float, KK, PO_BATCH_MAX_JOBS, W>(first, n_jobs, jobs, n_blocks, variant, s)));
+    }
+    PO_DISPATCH_BATCH(first->K, way_of(n_jobs, jobs),
+                      (camera_t<float, KK, PO_BATCH_MAX_JOBS, W>(first, n_jobs, jobs, n_blocks, variant, s)));
 }
 #endif
 
@@ -3163,11 +3173,12 @@ hipError_t po_camera_jobs_f32(const po_tree* first, int n_jobs, KJob* jobs, int 
 PO_PART_ERRORS_DEF(2)
 hipError_t po_camera_jobs_f16(const po_tree* first, int n_jobs, KJob* jobs, int n_blocks, int variant,
                               hipStream_t s) {
-    if (n_jobs == 1)
-        PO_DISPATCH(first->K, is_direct(first->kt), kOther,
+    if (n_jobs == 1) {
+        PO_DISPATCH(first->K, way_of(first->kt),
                     (camera_t<__half, KK, 1, W>(first, n_jobs, jobs, n_blocks, variant, s)));
-    PO_DISPATCH(first->K, all_direct(n_jobs, jobs), kAny,
-                (camera_t<__half, KK, PO_BATCH_MAX_JOBS, W>(first, n_jobs, jobs, n_blocks, variant, s)));
+    }
+    PO_DISPATCH_BATCH(first->K, way_of(n_jobs, jobs),
+                      (camera_t<__half, KK, PO_BATCH_MAX_JOBS, W>(first, n_jobs, jobs, n_blocks, variant, s)));
 }
 #endif
 
@@ -3175,7 +3186,7 @@ hipError_t po_camera_jobs_f16(const po_tree* first, int n_jobs, KJob* jobs, int 
 PO_PART_ERRORS_DEF(3)
 hipError_t po_camera_split_f32(const po_tree* t, const KJob& job, int n_blocks, int variant, const KSplit& S,
                                hipStream_t s) {
-    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (split_t<float, KK, 0, W>(t, job, n_blocks, variant, S, s)));
+    PO_DISPATCH(t->K, way_of(t->kt), (split_t<float, KK, 0, W>(t, job, n_blocks, variant, S, s)));
 }
 #endif
 
@@ -3183,7 +3194,7 @@ hipError_t po_camera_split_f32(const po_tree* t, const KJob& job, int n_blocks, 
 PO_PART_ERRORS_DEF(4)
 hipError_t po_camera_split_f16(const po_tree* t, const KJob& job, int n_blocks, int variant, const KSplit& S,
                                hipStream_t s) {
-    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (split_t<__half, KK, 0, W>(t, job, n_blocks, variant, S, s)));
+    PO_DISPATCH(t->K, way_of(t->kt), (split_t<__half, KK, 0, W>(t, job, n_blocks, variant, S, s)));
 }
 #endif
 
@@ -3191,7 +3202,7 @@ hipError_t po_camera_split_f16(const po_tree* t, const KJob& job, int n_blocks, 
 PO_PART_ERRORS_DEF(5)
 hipError_t po_rays_split_f32(const po_tree* t, const KJob& job, int n_blocks, int variant, const KSplit& S,
                              hipStream_t s) {
-    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (split_t<float, KK, 1, W>(t, job, n_blocks, variant, S, s)));
+    PO_DISPATCH(t->K, way_of(t->kt), (split_t<float, KK, 1, W>(t, job, n_blocks, variant, S, s)));
 }
 #endif
 
@@ -3199,7 +3210,7 @@ hipError_t po_rays_split_f32(const po_tree* t, const KJob& job, int n_blocks, in
 PO_PART_ERRORS_DEF(6)
 hipError_t po_rays_split_f16(const po_tree* t, const KJob& job, int n_blocks, int variant, const KSplit& S,
                              hipStream_t s) {
-    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (split_t<__half, KK, 1, W>(t, job, n_blocks, variant, S, s)));
+    PO_DISPATCH(t->K, way_of(t->kt), (split_t<__half, KK, 1, W>(t, job, n_blocks, variant, S, s)));
 }
 #endif
 
@@ -3208,13 +3219,13 @@ PO_PART_ERRORS_DEF(7)
 hipError_t po_launch_backward_split(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                                     const float* rgb_fwd, const float* grad, float* gsig, float* gsh,
                                     const KSplit& S, hipStream_t s) {
-    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (backward_split_t<KK, W>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, S, s)));
+    PO_DISPATCH(t->K, way_of(t->kt), (backward_split_t<KK, W>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, S, s)));
 }
 
 hipError_t po_launch_backward_kept(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                                    const float* rgb_fwd, const float* grad, float* gsig, float* gsh,
                                    const KSplit& S, hipStream_t s) {
-    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (backward_kept_t<KK, W>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, S, s)));
+    PO_DISPATCH(t->K, way_of(t->kt), (backward_kept_t<KK, W>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, S, s)));
 }
 #endif
 
@@ -3223,9 +3234,9 @@ PO_PART_ERRORS_DEF(0)
 hipError_t po_launch_rays(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                           float* rgb, float* aux, hipStream_t s) {
     if (t->desc.dtype == PO_F32) {
-        PO_DISPATCH(t->K, is_direct(t->kt), kOther, (rays_t<float, KK, W>(t, n, o, d, op, rgb, aux, s)));
+        PO_DISPATCH(t->K, way_of(t->kt), (rays_t<float, KK, W>(t, n, o, d, op, rgb, aux, s)));
     } else {
-        PO_DISPATCH(t->K, is_direct(t->kt), kOther, (rays_t<__half, KK, W>(t, n, o, d, op, rgb, aux, s)));
+        PO_DISPATCH(t->K, way_of(t->kt), (rays_t<__half, KK, W>(t, n, o, d, op, rgb, aux, s)));
     }
 }
 
@@ -3262,7 +3273,7 @@ hipError_t po_launch_rays_split(const po_tree* t, int64_t n, const float* o, con
 
 hipError_t po_launch_backward(const po_tree* t, int64_t n, const float* o, const float* d, const KOpts& op,
                               const float* rgb_fwd, const float* grad, float* gsig, float* gsh, hipStream_t s) {
-    PO_DISPATCH(t->K, is_direct(t->kt), kOther, (backward_t<KK, W>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, s)));
+    PO_DISPATCH(t->K, way_of(t->kt), (backward_t<KK, W>(t, n, o, d, op, rgb_fwd, grad, gsig, gsh, s)));
 }
 
 hipError_t po_launch_index(const int32_t* nodes, int n_top, int G, int unit, int64_t n_bricks, int32_t* grid,
@@ -3284,15 +3295,17 @@ hipError_t po_launch_leaf_weights(const po_tree* t, const KCam& cam, const KOpts
     dim3 grid((unsigned)rows_grid(n_blocks, 4 * (int64_t)((cam.W + 15) / 16))), block(kBlock);
     const size_t lds = stack_bytes(t->kt);
     unsigned* wt = reinterpret_cast<unsigned*>(weight);
-    const bool direct = is_direct(t->kt);
-#define PO_WEIGHTS(T_, MODE_)                                                                                          \
-    do {                                                                                                             \
-        if (direct)                                                                                                  \
-            hipLaunchKernelGGL((k_leaf_weights<T_, MODE_, kDirect>), grid, block, lds, s, t->kt, cam, op, n_blocks, wt, \
-                               alpha);                                                                               \
-        else                                                                                                         \
-            hipLaunchKernelGGL((k_leaf_weights<T_, MODE_, kOther>), grid, block, lds, s, t->kt, cam, op, n_blocks, wt,  \
-                               alpha);                                                                               \
+    const Way way = way_of(t->kt);
+#define PO_WEIGHTS_WAY(T_, MODE_, W_)                                                                            \
+    hipLaunchKernelGGL((k_leaf_weights<T_, MODE_, W_>), grid, block, lds, s, t->kt, cam, op, n_blocks, wt, alpha)
+#define PO_WEIGHTS(T_, MODE_)                     \
+    do {                                          \
+        if (way == kDirect)                       \
+            PO_WEIGHTS_WAY(T_, MODE_, kDirect);   \
+        else if (way == kPlain)                   \
+            PO_WEIGHTS_WAY(T_, MODE_, kPlain);    \
+        else                                      \
+            PO_WEIGHTS_WAY(T_, MODE_, kNodes);    \
     } while (0)
     if (t->desc.dtype == PO_F32) {
         if (mode == 0)
@@ -3306,6 +3319,7 @@ hipError_t po_launch_leaf_weights(const po_tree* t, const KCam& cam, const KOpts
             PO_WEIGHTS(__half, 1);
     }
 #undef PO_WEIGHTS
+#undef PO_WEIGHTS_WAY
     return hipGetLastError();
 }
 
