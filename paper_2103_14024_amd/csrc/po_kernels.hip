@@ -1768,9 +1768,9 @@ __device__ __forceinline__ void first_walk(const KJob& J, const KSplit& S, int i
 }
 
 // The plain (SH, SG) walks of records up to 192 bytes are held to 128 VGPRs
-// (4 waves per SIMD; the kernels of direct trees then need no scratch, the
-// others up to 204 bytes at float32 K = 16, used before and after the walk's
-// loops).  Larger records and the viewer and
+// (4 waves per SIMD; float32 K = 16 in dword loads or with nodes, and float16
+// K = 25, then keep up to 112 bytes of scratch, used before and after the walk's
+// loop).  Larger records and the viewer and
 // codebook variants would spill inside it (K=25 float32: 180 bytes of scratch,
 // half the frame rate), so they keep their natural count.
 template <typename T, int K, int V>
